@@ -200,6 +200,8 @@ k_edge_weights(EmitArgs a) {
   if (e < a.counts_out[1]) a.ew[e] = a.edge_start[e + 1] - a.edge_start[e];
 }
 
+constexpr int EDGE_TILE = TT_BLOCK * 4;  // pairs per workgroup of the run-head kernels
+
 size_t pad64(size_t ints) { return (ints + 63) & ~(size_t)63; }
 
 struct EdgeLayout {
@@ -216,7 +218,7 @@ EdgeLayout edge_layout(long long num_bags, long long cap) {
   L.ka = take((size_t)cap); L.va = take((size_t)cap); L.kb = take((size_t)cap); L.vb = take((size_t)cap);
   L.hist = take(tiles << TT_SORT_MAX_BITS);
   L.bin_total = take((size_t)1 << TT_SORT_MAX_BITS);
-  L.tile_sums = take(tiles);
+  L.tile_sums = take((size_t)tt_ceil_div(cap, EDGE_TILE) + 1);
   L.edge_start = take((size_t)cap + 1);
   L.total = at * sizeof(int32_t);
   return L;
@@ -285,7 +287,7 @@ tt_status ttk_index_graph_edges(const int64_t *indices, const int64_t *offsets, 
   em.tile_sums = w + L.tile_sums;
   em.edge_start = w + L.edge_start;
   em.eu = eu; em.ev = ev; em.ew = ew;
-  em.tiles = tt_ceil_div(max_pairs, TT_SORT_TILE) > 0 ? tt_ceil_div(max_pairs, TT_SORT_TILE) : 1;
+  em.tiles = tt_ceil_div(max_pairs, EDGE_TILE) > 0 ? tt_ceil_div(max_pairs, EDGE_TILE) : 1;
   hipLaunchKernelGGL(k_edge_heads, dim3(em.tiles), dim3(TT_BLOCK), 0, s, em);
   hipLaunchKernelGGL(k_edge_scan_tiles, dim3(1), dim3(TT_BLOCK), 0, s, em);
   hipLaunchKernelGGL(k_edge_emit, dim3(em.tiles), dim3(TT_BLOCK), 0, s, em);

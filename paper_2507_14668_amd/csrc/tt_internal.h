@@ -30,10 +30,13 @@ struct TTShape {
 #define TT_BLOCK 256
 
 // ---- radix sort geometry ----------------------------------------------------------------
-#ifndef TT_SORT_ITEMS
-#define TT_SORT_ITEMS 4
-#endif
-#define TT_SORT_TILE (TT_BLOCK * TT_SORT_ITEMS)  // keys per workgroup per pass
+#define TT_SORT_THREADS 512
+#define TT_SORT_ITEMS 2
+#define TT_SORT_TILE (TT_SORT_THREADS * TT_SORT_ITEMS)  // keys per workgroup per pass
+#define TT_SUPER_TILES 32    // tiles whose digit counts are also added up in one row
+#define TT_SUPER_SLOTS 6     // four passes of the main sort, two groupings
+#define TT_SMALL_MAX_LOOKUPS 2048  // batches of at most this many lookups get their plan from one workgroup
+#define TT_SMALL_MAX_BAGS 16384    // ... if they also have at most this many bags (it walks them alone)
 #define TT_SORT_MAX_BITS 10                      // digit width limit (1024 bins)
 
 // ---- matrix-core kernels -------------------------------------------------------------------
@@ -66,6 +69,8 @@ struct TTSortTmp {
   int32_t *hist;                   // [bins][tiles] per-tile digit histograms
   int32_t *bin_total;              // [bins]
   int32_t *tile_sums;              // [2][tiles] head counts per tile of the unique pass
+  int32_t *tile_base;              // [2][tiles + 1] first row / prefix slot of each tile
+  int32_t *super;                  // [TT_SUPER_SLOTS][tiles / TT_SUPER_TILES + 1][bins] counts of groups of tiles
 };
 TTSortTmp tt_sort_tmp_view(const tt_plan *plan);
 size_t tt_sort_tmp_bytes(int64_t nnz, int64_t max_rows, int64_t max_prefixes);
@@ -147,6 +152,16 @@ template <> struct TTArg<true> {
                          lds, s, TTArg<true>{(batch).dev}, ##__VA_ARGS__);                        \
     else                                                                                          \
       hipLaunchKernelGGL((K<false, TARGS>), dim3((unsigned)(gx)), dim3(bs), lds, s,               \
+                         TTArg<false>{(batch).host[0]}, ##__VA_ARGS__);                           \
+  } while (0)
+// ... two further template arguments
+#define TT_LAUNCH_T2(K, T1, T2, gx, bs, lds, s, batch, ...)                                        \
+  do {                                                                                            \
+    if ((batch).dev)                                                                              \
+      hipLaunchKernelGGL((K<true, T1, T2>), dim3((unsigned)(gx), (unsigned)(batch).T), dim3(bs),  \
+                         lds, s, TTArg<true>{(batch).dev}, ##__VA_ARGS__);                        \
+    else                                                                                          \
+      hipLaunchKernelGGL((K<false, T1, T2>), dim3((unsigned)(gx)), dim3(bs), lds, s,              \
                          TTArg<false>{(batch).host[0]}, ##__VA_ARGS__);                           \
   } while (0)
 
@@ -278,17 +293,18 @@ __device__ __forceinline__ int tt_wave_incl_scan(int v) {
   return v;
 }
 
-// Exclusive scan of one int per thread over a TT_BLOCK-thread workgroup.
-// `tmp` is LDS with at least TT_BLOCK/TT_WAVE + 1 ints.  Returns the exclusive prefix;
-// *total receives the workgroup sum.  Contains two barriers.
-__device__ __forceinline__ int tt_block_excl_scan(int v, int *tmp, int *total) {
+// Exclusive scan of one int per thread over a workgroup of NT threads.  `tmp` is LDS with at least
+// NT/TT_WAVE + 1 ints.  Returns the exclusive prefix; *total receives the workgroup sum.  Contains two
+// barriers.
+template <int NT>
+__device__ __forceinline__ int tt_block_excl_scan_n(int v, int *tmp, int *total) {
   const int lane = threadIdx.x & (TT_WAVE - 1), wave = threadIdx.x / TT_WAVE;
   int incl = tt_wave_incl_scan(v);
   if (lane == TT_WAVE - 1) tmp[wave] = incl;
   __syncthreads();
   int base = 0, tot = 0;
 #pragma unroll
-  for (int w = 0; w < TT_BLOCK / TT_WAVE; ++w) {
+  for (int w = 0; w < NT / TT_WAVE; ++w) {
     int x = tmp[w];
     if (w < wave) base += x;
     tot += x;
@@ -296,6 +312,9 @@ __device__ __forceinline__ int tt_block_excl_scan(int v, int *tmp, int *total) {
   __syncthreads();
   *total = tot;
   return base + incl - v;
+}
+__device__ __forceinline__ int tt_block_excl_scan(int v, int *tmp, int *total) {
+  return tt_block_excl_scan_n<TT_BLOCK>(v, tmp, total);
 }
 
 __device__ __forceinline__ float tt_wave_sum(float v) {
