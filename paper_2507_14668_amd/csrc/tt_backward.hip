@@ -10,6 +10,8 @@
 //      segmented sums (core 2 by i3, core 0 by i1) and a per-i2 accumulation (core 1).
 //   No floating-point atomics: every output element is written once, in a fixed order.
 // Naive arm: one workgroup per lookup, full chain, atomicAdd into the core gradients.
+#include <type_traits>
+
 #include "tt_internal.h"
 
 namespace {
@@ -431,17 +433,34 @@ tt_status seg_sum(const TTBatch &b, int kind, int chunk, int prof_kernel, hipStr
 // flight each, and their sums are added in group order through LDS, so the result does not depend on
 // timing.  (The lookups of one hot row can be a fifth of a batch, which is why the gradient merge
 // keeps the two-stage sum.)  A long segment is summed by its workgroups alone: correct, only slow.
+#ifndef TT_SEG_WHOLE_PARTS
+#define TT_SEG_WHOLE_PARTS 8  // column parts of a core-0 segment
+#endif
+// Column parts per segment and lanes per part.  Core 0: as many parts (at most TT_SEG_WHOLE_PARTS) as leave a
+// part 8 lanes wide; core 2 only as many as bring its workgroups to about two per compute unit.  A table's
+// own numbers decide, so its sums are the same alone and in a batch.
+struct WholeSplit { int parts, lanes; };
+__host__ __device__ __forceinline__ WholeSplit whole_split(int W, int vec, int want) {
+  WholeSplit w = {1, 1};
+  while (w.parts * 2 <= want && w.parts * 2 <= TT_SEG_WHOLE_PARTS && W % (w.parts * 2 * vec) == 0 &&
+         W / (w.parts * 2 * vec) >= 8)
+    w.parts *= 2;
+  while (w.lanes < TT_WAVE && w.lanes * vec < W / w.parts) w.lanes <<= 1;
+  return w;
+}
+__host__ __device__ __forceinline__ int whole_want3(int n3) { return (512 + n3 - 1) / n3; }
+
 template <bool BATCHED, int VEC>
 __global__ void __launch_bounds__(TT_BLOCK)
-k_seg_whole(TTArg<BATCHED> arg, int nseg_a, int lanes_a, int parts_a, int lanes_b, int parts_b) {
+k_seg_whole(TTArg<BATCHED> arg, int blocks_a) {
   const TTDev &d = arg.get();
-  const bool second = (int)blockIdx.x >= nseg_a * parts_a;
+  const bool second = (int)blockIdx.x >= blocks_a;
   const SegView sv = seg_view(d, second ? SEG_DG1 : SEG_DG3);
-  const int parts = second ? parts_b : parts_a;
-  const int wg = second ? (int)blockIdx.x - nseg_a * parts_a : (int)blockIdx.x;
+  const WholeSplit split = whole_split(sv.W, VEC, second ? TT_SEG_WHOLE_PARTS : whole_want3(d.sh.n3));
+  const int parts = split.parts, lanes = split.lanes;
+  const int wg = second ? (int)blockIdx.x - blocks_a : (int)blockIdx.x;
   const int s = wg / parts, part = wg - s * parts;
   if (s >= sv.nseg) return;  // uniform: a table of the batch with fewer segments
-  const int lanes = second ? lanes_b : lanes_a;
   const int W = sv.W, nsub = sv.nsub, out_inner = sv.out_inner, nseg = sv.nseg;
   const int Wp = W / parts, e0 = part * Wp;  // this workgroup's columns
   const int32_t *__restrict__ gidx = sv.gidx, *__restrict__ seg_off = sv.seg_off;
@@ -499,9 +518,6 @@ k_seg_whole(TTArg<BATCHED> arg, int nseg_a, int lanes_a, int parts_a, int lanes_
     }
 }
 
-#ifndef TT_SEG_WHOLE_PARTS
-#define TT_SEG_WHOLE_PARTS 8  // column parts of a core-0 segment
-#endif
 #ifndef TT_SEG_WHOLE_MAX_AVG
 #define TT_SEG_WHOLE_MAX_AVG 4096  // positions per segment (capacity / segments) up to which whole segments are used
 #endif
@@ -510,36 +526,31 @@ k_seg_whole(TTArg<BATCHED> arg, int nseg_a, int lanes_a, int parts_a, int lanes_
 // launch of whole-segment workgroups; otherwise the two-stage sum, sharing its launches when their
 // vectors have the same width (the smaller one would otherwise pay two launches for a few workgroups).
 tt_status seg_sum_dg3_dg1(const TTBatch &b, hipStream_t s) {
-  const SegParams p3 = seg_params(b, SEG_DG3, 0), p1 = seg_params(b, SEG_DG1, 0);
-  bool whole = p3.vec == p1.vec;
+  SegParams p3 = seg_params(b, SEG_DG3, 0), p1 = seg_params(b, SEG_DG1, 0);
+  bool whole = true;
   for (int t = 0; t < b.T && whole; ++t) {
     const TTDev &d = b.host[t];
     whole = d.plan.max_rows / d.sh.n3 <= TT_SEG_WHOLE_MAX_AVG &&
             d.plan.max_prefixes * d.strips / d.sh.n1 <= TT_SEG_WHOLE_MAX_AVG;
   }
   if (whole) {
-    const long long n3max = tt_batch_max(b, [](const TTDev &d) { return (long long)d.sh.n3; });
-    const long long n1max = tt_batch_max(b, [](const TTDev &d) { return (long long)d.sh.n1; });
-    // column parts per segment: core 0 as many (at most TT_SEG_WHOLE_PARTS) as leave a part 8 lanes wide;
-    // core 2 only as many as bring its workgroups to about two per compute unit
-    auto parts_for = [](const SegParams &p, int want) {
-      int parts = 1;
-      while (parts * 2 <= want && p.W % (parts * 2 * p.vec) == 0 && p.W / (parts * 2 * p.vec) >= 8) parts *= 2;
-      return parts;
-    };
-    auto lanes_for = [](const SegParams &p, int parts) {
-      int lanes = 1;
-      while (lanes < TT_WAVE && lanes * p.vec < p.W / parts) lanes <<= 1;
-      return lanes;
-    };
-    const int parts3 = parts_for(p3, tt_ceil_div(512, n3max) < TT_SEG_WHOLE_PARTS ? tt_ceil_div(512, n3max) : TT_SEG_WHOLE_PARTS);
-    const int parts1 = parts_for(p1, TT_SEG_WHOLE_PARTS);
-    const int lanes3 = lanes_for(p3, parts3), lanes1 = lanes_for(p1, parts1);
-    const size_t g3 = (size_t)(TT_BLOCK / lanes3) * (p3.W / parts3), g1 = (size_t)(TT_BLOCK / lanes1) * (p1.W / parts1);
-    const size_t lds = sizeof(float) * (g3 > g1 ? g3 : g1);
-    const long long grid = n3max * parts3 + n1max * parts1;
-    if (p3.vec == 4) TT_LAUNCH_T(k_seg_whole, 4, grid, TT_BLOCK, lds, s, b, (int)n3max, lanes3, parts3, lanes1, parts1);
-    else TT_LAUNCH_T(k_seg_whole, 1, grid, TT_BLOCK, lds, s, b, (int)n3max, lanes3, parts3, lanes1, parts1);
+    // one launch has one vector width (d3 = 6 beside ranks of four, 12 k lookups: 26 us in the four launches of
+    // two separate two-stage sums, 7 us here)
+    if (p3.vec != p1.vec) p3.vec = p1.vec = 1;
+    const int vec = p3.vec, W3 = p3.W;
+    const WholeSplit w1 = whole_split(p1.W, vec, TT_SEG_WHOLE_PARTS);
+    const long long blocks3 = tt_batch_max(b, [=](const TTDev &d) {
+      return (long long)d.sh.n3 * whole_split(W3, vec, whole_want3(d.sh.n3)).parts; });
+    const long long blocks1 = tt_batch_max(b, [](const TTDev &d) { return (long long)d.sh.n1; }) * w1.parts;
+    // floats of LDS: one part's sums per lane group
+    const long long lds3 = tt_batch_max(b, [=](const TTDev &d) {
+      const WholeSplit w = whole_split(W3, vec, whole_want3(d.sh.n3));
+      return (long long)(TT_BLOCK / w.lanes) * (W3 / w.parts); });
+    const long long lds1 = (long long)(TT_BLOCK / w1.lanes) * (p1.W / w1.parts);
+    const size_t lds = sizeof(float) * (size_t)(lds3 > lds1 ? lds3 : lds1);
+    const long long grid = blocks3 + blocks1;
+    if (vec == 4) TT_LAUNCH_T(k_seg_whole, 4, grid, TT_BLOCK, lds, s, b, (int)blocks3);
+    else TT_LAUNCH_T(k_seg_whole, 1, grid, TT_BLOCK, lds, s, b, (int)blocks3);
     return tt_launch_status();
   }
   if (p3.W == p1.W && p3.vec == p1.vec && p3.lanes == p1.lanes && p3.blocks1 > 0 && p1.blocks1 > 0)
@@ -625,49 +636,302 @@ k_bwd_prefix(TTArg<BATCHED> a) {
   }
 }
 
+// The same for shapes whose operands are small: one WAVEFRONT per distinct prefix, four per workgroup, no
+// barrier on the way; a prefix with more than PW_SOLO_ROWS distinct rows is worked on by all four.
+// The work per prefix is a chain of five dependent round trips around a few hundred LDS reads, so what
+// counts is how many chains are in flight (sixteen to twenty wavefronts per compute unit) and the number
+// of LDS instructions: the core-1 slice is read from memory once (product and T1), j1 and rows come in
+// groups of four per 16-byte read, and T1 is a lane (or two, or four) per element, where a wavefront
+// reduction per element (six dependent lane exchanges for each of d1*R1 values) was most of the time.
+// LDS per wavefront (floats): g1s[R1][j1, padded to fours] | gs[D][4 rows] | g3s[S3][4 rows] | p12[d1*d2*R2p] |
+// hs[P] | g2s[R1][S2|1], rounded up to fours
+constexpr int PW_WAVES = 4, PW_ROWS = 4, PW_SOLO_ROWS = 16;
+struct PrefixWaveLds {
+  int gs, g3s, p12, hs, g2s, floats, d1p;
+  __host__ __device__ __forceinline__ explicit PrefixWaveLds(const TTShape &sh) {
+    d1p = (sh.d1 + 3) & ~3;
+    gs = sh.R1 * d1p;
+    g3s = gs + PW_ROWS * sh.D;
+    p12 = g3s + PW_ROWS * sh.S3;
+    hs = p12 + sh.d1 * sh.d2 * sh.R2p;
+    g2s = hs + sh.P;
+    floats = (g2s + sh.R1 * (sh.S2 | 1) + 3) & ~3;
+  }
+};
+// The rule: four wavefronts' operands fit the 64 KB of LDS a launch gets without asking.  Larger shapes have
+// enough work per prefix for a workgroup.
+static inline bool prefix_wave_fits(const TTShape &sh) {
+  return PW_WAVES * (PrefixWaveLds(sh).floats + 1) * (long long)sizeof(float) <= 65536;
+}
+
+template <bool BATCHED>
+__global__ void __launch_bounds__(TT_WAVE * PW_WAVES)
+k_bwd_prefix_wave(TTArg<BATCHED> a) {
+  const TTDev &d = a.get();
+  const TTShape &sh = d.sh;
+  const float *__restrict__ g1 = d.g[0], *__restrict__ g2 = d.g[1], *__restrict__ g3 = d.g[2];
+  const int32_t *__restrict__ counts = d.plan.counts, *__restrict__ uniq_pref = d.plan.uniq_pref,
+                *__restrict__ pref_seg = d.plan.pref_seg, *__restrict__ uniq_row = d.plan.uniq_row;
+  const float *__restrict__ gagg = d.plan.gagg;
+  float *__restrict__ t3buf = d.plan.t3buf, *__restrict__ hbuf = d.plan.hbuf, *__restrict__ t1buf = d.plan.t1buf;
+  extern __shared__ float lds[];
+  __shared__ __align__(16) int s_rows[PW_WAVES];
+  const int lane = threadIdx.x & (TT_WAVE - 1), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / TT_WAVE);
+  const PrefixWaveLds L(sh);
+  float *g1s = lds + wave * L.floats, *gs = g1s + L.gs, *g3s = g1s + L.g3s, *p12 = g1s + L.p12, *hs = g1s + L.hs,
+        *g2s = g1s + L.g2s;
+  const int up = counts[1], S2p = sh.S2 | 1, JJ = sh.d1 * sh.d2;
+
+  // T1[j1][r1] = sum_c H[j1][c] G2[r1][i2][c] by `threads` threads, `parts` of them per element when the
+  // elements would leave most of a wavefront idle (a wavefront then holds 64 / parts elements)
+  auto core0 = [&](int q, const float *h, int tid, int threads) __attribute__((always_inline)) {
+    const int parts = sh.S1 <= 16 ? 4 : (sh.S1 <= 32 ? 2 : 1), width = TT_WAVE / parts;
+    const int part = lane / width, per = (sh.S2 + parts - 1) / parts;
+    const int c0 = part * per, c1 = c0 + per < sh.S2 ? c0 + per : sh.S2;
+    for (int o0 = tid / TT_WAVE * width; o0 < sh.S1; o0 += threads / parts) {  // uniform per wavefront
+      const int o = o0 + (lane & (width - 1)), oc = o < sh.S1 ? o : 0, j1 = oc / sh.R1, r1 = oc - j1 * sh.R1;
+      const float *hp = h + j1 * sh.S2, *gp = g2s + r1 * S2p;
+      float acc[4] = {0.f, 0.f, 0.f, 0.f};
+      int c = c0;
+      for (; c + 8 <= c1; c += 8)
+#pragma unroll
+        for (int k = 0; k < 8; ++k) acc[k & 3] = fmaf(hp[c + k], gp[c + k], acc[k & 3]);
+      for (; c < c1; ++c) acc[0] = fmaf(hp[c], gp[c], acc[0]);
+      float sum = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+      for (int w = width; w < TT_WAVE; w <<= 1) sum += __shfl_xor(sum, w, TT_WAVE);
+      if (part == 0 && o < sh.S1) t1buf[(size_t)q * sh.S1 + o] = sum;
+    }
+  };
+  // NR rows of a batch (one, or up to four of which n exist; the others' values are computed and dropped)
+  auto batch_math = [&](auto nr, int ub, int n) __attribute__((always_inline)) {
+    constexpr int NR = decltype(nr)::value;
+    // T3[r2][j3] = sum_{j1,j2} P12[j1][j2][r2] g[j1][j2][j3]
+    for (int o = lane; o < sh.S3; o += TT_WAVE) {
+      const int r2 = o / sh.d3, j3 = o - r2 * sh.d3;
+      float acc[NR] = {};
+#pragma unroll 4
+      for (int jj = 0; jj < JJ; ++jj) {
+        const float x = p12[jj * sh.R2p + r2], *gp = gs + (jj * sh.d3 + j3) * PW_ROWS;
+        if constexpr (NR == 1) {
+          acc[0] = fmaf(x, gp[0], acc[0]);
+        } else {
+          const float4 y = *reinterpret_cast<const float4 *>(gp);
+          acc[0] = fmaf(x, y.x, acc[0]); acc[1] = fmaf(x, y.y, acc[1]);
+          acc[2] = fmaf(x, y.z, acc[2]); acc[3] = fmaf(x, y.w, acc[3]);
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < NR; ++k)
+        if (k < n) t3buf[(size_t)(ub + k) * sh.S3 + o] = acc[k];
+    }
+    // H[j1][j2][r2] += sum_j3 g[j1][j2][j3] G3[r2][i3][j3], row after row
+    for (int o = lane; o < sh.P; o += TT_WAVE) {
+      const int jj = o / sh.R2, r2 = o - jj * sh.R2;
+      const float *gp = gs + jj * sh.d3 * PW_ROWS, *sp = g3s + r2 * sh.d3 * PW_ROWS;
+      float acc[NR] = {}, h = hs[o];
+#pragma unroll 4
+      for (int j3 = 0; j3 < sh.d3; ++j3) {
+        if constexpr (NR == 1) {
+          acc[0] = fmaf(gp[j3 * PW_ROWS], sp[j3 * PW_ROWS], acc[0]);
+        } else {
+          const float4 x = *reinterpret_cast<const float4 *>(gp + j3 * PW_ROWS), y = *reinterpret_cast<const float4 *>(sp + j3 * PW_ROWS);
+          acc[0] = fmaf(x.x, y.x, acc[0]); acc[1] = fmaf(x.y, y.y, acc[1]);
+          acc[2] = fmaf(x.z, y.z, acc[2]); acc[3] = fmaf(x.w, y.w, acc[3]);
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < NR; ++k)
+        if (k < n) h += acc[k];
+      hs[o] = h;
+    }
+  };
+  // product, T3 of the row batches first, first + step, ..., and their right partial in hs
+  auto prefix = [&](int q, int u0, int u1, int first, int step) __attribute__((always_inline)) {
+    const int p = uniq_pref[q], i1 = tt_div(p, sh.mul2, sh.sh2), i2 = p - i1 * sh.n2;
+    int ub = u0 + first * PW_ROWS;
+    int id = uniq_row[ub + lane < u1 ? ub + lane : u1 - 1];  // lane k < 4: the batch's k-th row (past the end: the last one)
+    for (int e = lane; e < sh.S1; e += TT_WAVE) {
+      const int j1 = e / sh.R1;
+      g1s[(e - j1 * sh.R1) * L.d1p + j1] = g1[(size_t)i1 * sh.S1 + e];
+    }
+    for (int c = lane; c < sh.S2; c += TT_WAVE) {
+      const float *col = g2 + (size_t)i2 * sh.S2 + c;
+      for (int r0 = 0; r0 < sh.R1; r0 += 16) {
+        float v[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v[k] = col[(size_t)(r0 + k < sh.R1 ? r0 + k : r0) * sh.n2 * sh.S2];
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+          if (r0 + k < sh.R1) g2s[(r0 + k) * S2p + c] = v[k];
+      }
+    }
+    for (int o = lane; o < sh.P; o += TT_WAVE) hs[o] = 0.f;
+    tt_wave_lds_order();
+    for (int c = lane; c < sh.S2; c += TT_WAVE) {
+      const int j2 = c / sh.R2, r2 = c - j2 * sh.R2;
+      for (int j0 = 0; j0 < sh.d1; j0 += 4) {  // (the padding columns of g1s are never stored from)
+        float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+        for (int r1 = 0; r1 < sh.R1; ++r1) {
+          const float x = g2s[r1 * S2p + c];
+          const float4 y = *reinterpret_cast<const float4 *>(g1s + r1 * L.d1p + j0);
+          acc[0] = fmaf(y.x, x, acc[0]); acc[1] = fmaf(y.y, x, acc[1]);
+          acc[2] = fmaf(y.z, x, acc[2]); acc[3] = fmaf(y.w, x, acc[3]);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (j0 + j < sh.d1) p12[((j0 + j) * sh.d2 + j2) * sh.R2p + r2] = acc[j];
+      }
+    }
+    for (; ub < u1; ub += step * PW_ROWS) {  // uniform
+      const int n = u1 - ub < PW_ROWS ? u1 - ub : PW_ROWS;
+      const int i3 = id - tt_div(id, sh.mul3, sh.sh3) * sh.n3, ubn = ub + step * PW_ROWS;
+      if (ubn < u1) id = uniq_row[ubn + lane < u1 ? ubn + lane : u1 - 1];
+      const float *src[PW_ROWS];
+#pragma unroll
+      for (int k = 0; k < PW_ROWS; ++k) src[k] = g3 + (size_t)__builtin_amdgcn_readlane(i3, k) * sh.d3;
+      for (int e = lane; e < sh.D; e += TT_WAVE) {
+        float v[PW_ROWS];
+#pragma unroll
+        for (int k = 0; k < PW_ROWS; ++k) v[k] = gagg[(size_t)(ub + (k < n ? k : 0)) * sh.D + e];
+        *reinterpret_cast<float4 *>(gs + e * PW_ROWS) = make_float4(v[0], v[1], v[2], v[3]);
+      }
+      for (int e = lane; e < sh.S3; e += TT_WAVE) {
+        const int r2 = e / sh.d3;
+        const size_t at = (size_t)r2 * sh.n3 * sh.d3 + (e - r2 * sh.d3);
+        float v[PW_ROWS];
+#pragma unroll
+        for (int k = 0; k < PW_ROWS; ++k) v[k] = src[k][at];
+        *reinterpret_cast<float4 *>(g3s + e * PW_ROWS) = make_float4(v[0], v[1], v[2], v[3]);
+      }
+      tt_wave_lds_order();
+      if (n == 1) batch_math(std::integral_constant<int, 1>{}, ub, n);
+      else batch_math(std::integral_constant<int, PW_ROWS>{}, ub, n);
+      tt_wave_lds_order();  // the next batch overwrites gs and g3s
+    }
+  };
+
+  for (int q0 = blockIdx.x * PW_WAVES; q0 < up; q0 += gridDim.x * PW_WAVES) {  // uniform
+    const int q = q0 + wave;
+    const int u0 = q < up ? pref_seg[q] : 0, u1 = q < up ? pref_seg[q + 1] : 0;
+    const bool solo = u1 - u0 <= PW_SOLO_ROWS;
+    if (lane == 0) s_rows[wave] = solo ? 0 : u1 - u0;
+    if (solo && u1 > u0) {
+      prefix(q, u0, u1, 0, 1);
+      for (int o = lane; o < sh.P; o += TT_WAVE) hbuf[(size_t)q * sh.P + o] = hs[o];
+      core0(q, hs, lane, TT_WAVE);
+    }
+    __syncthreads();
+    for (int w = 0; w < PW_WAVES; ++w)  // prefixes of many rows: all wavefronts, each on its own copy of the product
+      if (s_rows[w] > 0) {
+        const int v0 = pref_seg[q0 + w];
+        prefix(q0 + w, v0, v0 + s_rows[w], wave, PW_WAVES);
+        __syncthreads();
+        float *h0 = lds + L.hs;  // the first wavefront's partial takes the sum, in wavefront order
+        for (int o = threadIdx.x; o < sh.P; o += TT_WAVE * PW_WAVES) {
+          float sum = h0[o];
+          for (int v = 1; v < PW_WAVES; ++v) sum += h0[v * L.floats + o];
+          h0[o] = sum;
+          hbuf[(size_t)(q0 + w) * sh.P + o] = sum;
+        }
+        __syncthreads();
+        core0(q0 + w, h0, threadIdx.x, TT_WAVE * PW_WAVES);
+        __syncthreads();  // h0 is rewritten
+      }
+    __syncthreads();  // s_rows is rewritten
+  }
+}
+
 // Core-1 gradient: dG2[r1][i2][j2][r2] = sum over the prefixes (i1,i2) of the batch of
-// sum_j1 G1[i1][j1][r1] H[(i1,i2)][j1][j2][r2].  Workgroup (i2, column tile, r1 tile); thread
-// owns one (j2,r2) column and RT values of r1; prefixes are visited in increasing i1.
-#define TT_DG2_RT 8
+// sum_j1 G1[i1][j1][r1] H[(i1,i2)][j1][j2][r2], a product with K = (prefix, j1) for every i2.
+// Workgroup (i2, 64 columns, 16 values of r1); K goes through LDS in chunks of 64, whose loads are in
+// flight while the previous chunk is multiplied, and every output is one thread's sum in increasing K.
+// Latency bound: one dependent plan read and one round trip of loads per chunk.  3000 prefixes of rank 16 under
+// 100 i2: 8.9 us (one thread per column that walked the prefixes alone, three dependent loads each: 59.8 us).
+#define TT_DG2_C 64
+#define TT_DG2_R 16
+#define TT_DG2_K 64
 template <bool BATCHED>
 __global__ void __launch_bounds__(TT_BLOCK)
-k_bwd_dg2(TTArg<BATCHED> a, int col_tiles) {
+k_bwd_dg2(TTArg<BATCHED> a, int col_tiles, unsigned dmul, unsigned dsh) {
   const TTDev &d = a.get();
   const TTShape &sh = d.sh;
   const float *__restrict__ g1 = d.g[0], *__restrict__ hbuf = d.plan.hbuf;
-  const int32_t *__restrict__ uniq_pref = d.plan.uniq_pref, *__restrict__ prefs_by_i2 = d.plan.prefs_by_i2,
-                *__restrict__ i2_seg = d.plan.i2_seg;
+  const int4 *__restrict__ pref_meta = reinterpret_cast<const int4 *>(d.plan.pref_meta);
+  const int32_t *__restrict__ i2_seg = d.plan.i2_seg;
   float *__restrict__ dg2 = d.fused ? const_cast<float *>(d.g[1]) : d.dg[1];
   const int fused = d.fused;
   const float lr = d.lr;
   // grid.x enumerates (i2, column tile, r1 tile); grid.y is the table in a batched launch
-  const int r1_tiles = (sh.R1 + TT_DG2_RT - 1) / TT_DG2_RT;
+  const int r1_tiles = (sh.R1 + TT_DG2_R - 1) / TT_DG2_R;
   if ((int)blockIdx.x >= sh.n2 * col_tiles * r1_tiles) return;
-  const int bz = blockIdx.x % r1_tiles, by = (blockIdx.x / r1_tiles) % col_tiles,
-            bx = blockIdx.x / (r1_tiles * col_tiles);
-  const int i2 = bx, c = by * TT_BLOCK + threadIdx.x, r1b = bz * TT_DG2_RT;
-  if (c >= sh.S2) return;
-  float acc[TT_DG2_RT];
-#pragma unroll
-  for (int k = 0; k < TT_DG2_RT; ++k) acc[k] = 0.f;
-  const int s0 = i2_seg[i2], s1 = i2_seg[i2 + 1];
-  if (fused && s0 == s1) return;  // untouched slice: nothing to apply
-  for (int s = s0; s < s1; ++s) {
-    const int q = prefs_by_i2[s], i1 = uniq_pref[q] / sh.n2;
-    for (int j1 = 0; j1 < sh.d1; ++j1) {
-      const float h = hbuf[(size_t)q * sh.P + j1 * sh.S2 + c];
-      const float *gp = g1 + (size_t)i1 * sh.S1 + j1 * sh.R1 + r1b;
-#pragma unroll
-      for (int k = 0; k < TT_DG2_RT; ++k)
-        if (r1b + k < sh.R1) acc[k] = fmaf(gp[k], h, acc[k]);
+  const int bz = blockIdx.x % r1_tiles, by = (blockIdx.x / r1_tiles) % col_tiles, i2 = blockIdx.x / (r1_tiles * col_tiles);
+  const int s0 = i2_seg[i2], nq = i2_seg[i2 + 1] - s0;
+  if (fused && nq == 0) return;  // untouched slice: nothing to apply
+  const int K = nq * sh.d1;      // at most n1*d1
+  __shared__ __align__(16) float Hs[TT_DG2_K][TT_DG2_C], Gs[TT_DG2_K][TT_DG2_R];
+  __shared__ int s_i1[2][TT_DG2_K], s_q[2][TT_DG2_K], s_j1[2][TT_DG2_K];
+  const int c = threadIdx.x % TT_DG2_C, rg = threadIdx.x / TT_DG2_C;  // 4 values of r1 per thread
+  const int col = by * TT_DG2_C + c, r1b = bz * TT_DG2_R;
+  constexpr int HL = TT_DG2_K * TT_DG2_C / TT_BLOCK, GL = TT_DG2_K * TT_DG2_R / TT_BLOCK;
+  auto plan_of = [&](int t) __attribute__((always_inline)) {  // K entries of chunk t -> LDS
+    const int k = t * TT_DG2_K + threadIdx.x;
+    if (threadIdx.x < TT_DG2_K && k < K) {
+      const int s = tt_div(k, dmul, dsh);
+      const int4 m = pref_meta[s0 + s];
+      s_i1[t & 1][threadIdx.x] = m.x; s_q[t & 1][threadIdx.x] = m.w; s_j1[t & 1][threadIdx.x] = k - s * sh.d1;
     }
-  }
+  };
+  float h[HL], g[GL];
+  auto fetch = [&](int t) __attribute__((always_inline)) {  // operands of chunk t -> registers (zero past the end)
 #pragma unroll
-  for (int k = 0; k < TT_DG2_RT; ++k)
-    if (r1b + k < sh.R1) {
-      float *dst = dg2 + ((size_t)(r1b + k) * sh.n2 + i2) * sh.S2 + c;
+    for (int i = 0; i < HL; ++i) {
+      const int kk = rg + i * (TT_BLOCK / TT_DG2_C);
+      const bool in = t * TT_DG2_K + kk < K && col < sh.S2;
+      h[i] = in ? hbuf[(size_t)s_q[t & 1][kk] * sh.P + s_j1[t & 1][kk] * sh.S2 + col] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < GL; ++i) {
+      const int kk = threadIdx.x / TT_DG2_R + i * (TT_BLOCK / TT_DG2_R), r1 = r1b + threadIdx.x % TT_DG2_R;
+      const bool in = t * TT_DG2_K + kk < K && r1 < sh.R1;
+      g[i] = in ? g1[(size_t)s_i1[t & 1][kk] * sh.S1 + s_j1[t & 1][kk] * sh.R1 + r1] : 0.f;
+    }
+  };
+  float acc[4] = {0.f, 0.f, 0.f, 0.f};
+  const int chunks = (K + TT_DG2_K - 1) / TT_DG2_K;
+  if (chunks > 0) {  // uniform
+    plan_of(0);
+    __syncthreads();
+    fetch(0);
+    plan_of(1);
+  }
+  for (int t = 0; t < chunks; ++t) {
+#pragma unroll
+    for (int i = 0; i < HL; ++i) Hs[rg + i * (TT_BLOCK / TT_DG2_C)][c] = h[i];
+#pragma unroll
+    for (int i = 0; i < GL; ++i) Gs[threadIdx.x / TT_DG2_R + i * (TT_BLOCK / TT_DG2_R)][threadIdx.x % TT_DG2_R] = g[i];
+    __syncthreads();  // the chunk and the next one's plan entries are visible
+    if (t + 1 < chunks) fetch(t + 1);
+    plan_of(t + 2);   // over this chunk's entries, which were last read before the barrier
+    const int n = K - t * TT_DG2_K < TT_DG2_K ? K - t * TT_DG2_K : TT_DG2_K;
+#pragma unroll 4
+    for (int kk = 0; kk < n; ++kk) {
+      const float x = Hs[kk][c];
+      const float4 y = *reinterpret_cast<const float4 *>(&Gs[kk][4 * rg]);
+      acc[0] = fmaf(y.x, x, acc[0]); acc[1] = fmaf(y.y, x, acc[1]);
+      acc[2] = fmaf(y.z, x, acc[2]); acc[3] = fmaf(y.w, x, acc[3]);
+    }
+    __syncthreads();  // the next chunk overwrites the tiles
+  }
+  if (col >= sh.S2) return;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int r1 = r1b + 4 * rg + k;
+    if (r1 < sh.R1) {
+      float *dst = dg2 + ((size_t)r1 * sh.n2 + i2) * sh.S2 + col;
       *dst = fused ? fmaf(-lr, acc[k], *dst) : acc[k];
     }
+  }
 }
 
 // ------------------------------------------------------------------ naive arm
@@ -832,6 +1096,10 @@ tt_status ttk_backward_plan(const TTBatch &b, hipStream_t s) {
   const long long max_pref = tt_batch_max(b, [](const TTDev &d) { return (long long)d.plan.max_prefixes; });
   if (mfma) {
     if ((st = ttk_backward_mfma(b, s)) != TT_OK) return st;
+  } else if (max_pref > 0 && prefix_wave_fits(sh)) {
+    const long long wgs = (max_pref + PW_WAVES - 1) / PW_WAVES, blocks = wgs < 4096 ? wgs : 4096;
+    TTProfScope prof(&b.host[0].plan, TT_KERNEL_BWD_CONTRACT, s);
+    TT_LAUNCH(k_bwd_prefix_wave, blocks, TT_WAVE * PW_WAVES, sizeof(float) * PW_WAVES * PrefixWaveLds(sh).floats, s, b);
   } else if (max_pref > 0) {
     const long long blocks = max_pref < 4096 ? max_pref : 4096;
     TTProfScope prof(&b.host[0].plan, TT_KERNEL_BWD_CONTRACT, s);
@@ -840,9 +1108,11 @@ tt_status ttk_backward_plan(const TTBatch &b, hipStream_t s) {
   // 3. core 1: per-i2 accumulation over prefixes (inside the matrix-core kernel, else here).  It
   //    reads core 0, so with the fused update it has to run before the core-0 reduction below.
   if (!mfma) {
-    const int col_tiles = tt_ceil_div(sh.S2, TT_BLOCK), r1_tiles = tt_ceil_div(sh.R1, TT_DG2_RT);
+    const int col_tiles = tt_ceil_div(sh.S2, TT_DG2_C), r1_tiles = tt_ceil_div(sh.R1, TT_DG2_R);
     const long long n2max = tt_batch_max(b, [](const TTDev &d) { return (long long)d.sh.n2; });
-    TT_LAUNCH(k_bwd_dg2, n2max * col_tiles * r1_tiles, TT_BLOCK, 0, s, b, col_tiles);
+    unsigned dmul, dsh;
+    tt_div_constants(sh.d1, &dmul, &dsh);
+    TT_LAUNCH(k_bwd_dg2, n2max * col_tiles * r1_tiles, TT_BLOCK, 0, s, b, col_tiles, dmul, dsh);
   }
   // 4. core 2: sum the per-row contributions of all rows sharing i3; core 0: sum the per-prefix
   //    contributions of all prefixes sharing i1 (contiguous)
