@@ -10,6 +10,7 @@
 //                P12[q] x S to the bag's row, which is written once.  No atomics, no row buffer, no
 //                separate bag-sum launch; the price is one read of a whole prefix product per
 //                (bag, prefix) group instead of one read of a finished row per lookup.
+//   k_bag_chains_4x8x4  the same for the matrix-core shapes, products in registers, several wavefronts per long bag
 #include "tt_internal.h"
 
 namespace {
@@ -139,6 +140,117 @@ k_bag_chains(TTArg<BATCHED> a, int lds_per_wave) {
   }
 }
 
+// Bags of the matrix-core shapes (d = 4x8x4, R2 = 32 or 64, core 2 16-byte aligned).  The product of a group
+// goes from memory to registers, a float4 along r2 per lane and step: lane = (jj0, r4) holds rows
+// jj0 + (64/L)*k, columns 4*r4 .. 4*r4+3 of the product (L = R2/4), and needs the four rows of S with the same
+// r2, which it gathers from core 2 itself as float4.  A group of up to REPL lookups is gathered by every row
+// of lanes alike; a larger one is dealt to the 64/L rows of lanes, whose sums are added by lane exchanges.
+// Sums over r2 across the L lanes are formed once per bag.  WPB wavefronts share a bag, 64 lookups each at
+// a time, and add their results in wavefront order.
+// Bound by the reads of the products (R2 = 32: 4 KB per group of a 64-lookup round, about 13 groups a round
+// at a Zipf exponent of 1.2), out of the infinity cache, and by how many of those chains are in flight;
+// 2000 bags of 100-300 lookups: 110 us (through LDS, one wavefront per bag: 256 us).
+template <bool BATCHED, int R2, int WPB>
+__global__ void __launch_bounds__(TT_BLOCK)
+k_bag_chains_4x8x4(TTArg<BATCHED> a) {
+  constexpr int L = R2 / 4, ROWS = TT_WAVE / L, NK = 32 / ROWS, REPL = 6, D = 128, P = 32 * R2;
+  const TTDev &d = a.get();
+  const TTShape &sh = d.sh;
+  const float4 *__restrict__ g3 = reinterpret_cast<const float4 *>(d.g[2]);
+  const float *__restrict__ p12buf = d.p12buf;
+  const int64_t *__restrict__ offsets = d.offsets;
+  const int32_t *__restrict__ lookup2row = d.plan.lookup2row, *__restrict__ row2pref = d.plan.row2pref,
+                *__restrict__ uniq_row = d.plan.uniq_row;
+  __shared__ float s_out[TT_BLOCK / TT_WAVE][D];
+  __shared__ int s_i3[TT_BLOCK / TT_WAVE][TT_WAVE];
+  const int lane = threadIdx.x & (TT_WAVE - 1), wave = threadIdx.x / TT_WAVE;
+  const int r4 = lane & (L - 1), jj0 = lane / L;
+  const int b = WPB == 1 ? (int)blockIdx.x * (TT_BLOCK / TT_WAVE) + wave : (int)blockIdx.x;
+  if (b >= d.num_bags) return;  // uniform for the workgroup, or (WPB == 1) for a wavefront that meets no barrier
+  float acc[NK][4];
+#pragma unroll
+  for (int k = 0; k < NK; ++k) acc[k][0] = acc[k][1] = acc[k][2] = acc[k][3] = 0.f;
+  // offsets are clamped to [0, nnz] so that a malformed CSR array cannot index out of bounds
+  const long long o0 = offsets[b], o1 = offsets[b + 1], nnz = d.nnz;
+  const long long lo = o0 < 0 ? 0 : (o0 > nnz ? nnz : o0), hi = o1 < lo ? lo : (o1 > nnz ? nnz : o1);
+  const size_t rstep = (size_t)sh.n3;  // float4 between consecutive r2 of core 2
+  for (long long base = lo + (WPB == 1 ? 0 : wave) * TT_WAVE; base < hi; base += WPB * TT_WAVE) {  // uniform
+    // this lane's lookup: prefix slot and i3 (an invalid lookup has no row slot and takes no part)
+    const long long l = base + lane;
+    const int u = l < hi ? lookup2row[l] : -1;
+    const int q = u >= 0 ? row2pref[u] : -1;
+    const int row = u >= 0 ? uniq_row[u] : 0, i3 = row - tt_div(row, sh.mul3, sh.sh3) * sh.n3;
+    unsigned long long left = __ballot(q >= 0);
+    while (left) {  // uniform: one round per distinct prefix among the 64 lookups
+      const int first = __ffsll(left) - 1;
+      const int qg = __builtin_amdgcn_readlane(q, first);
+      const unsigned long long members = __ballot(q == qg);
+      left &= ~members;
+      const float4 *src = reinterpret_cast<const float4 *>(p12buf + (size_t)qg * P) + lane;
+      float4 p[NK];
+#pragma unroll
+      for (int k = 0; k < NK; ++k) p[k] = src[TT_WAVE * k];
+      float4 s[4];  // rows 4*r4 + i of the summed core-2 slices
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      auto add = [&](int m_i3) __attribute__((always_inline)) {
+        const float4 *gp = g3 + (size_t)(4 * r4) * rstep + m_i3;
+        float4 x[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = gp[(size_t)i * rstep];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { s[i].x += x[i].x; s[i].y += x[i].y; s[i].z += x[i].z; s[i].w += x[i].w; }
+      };
+      const int cnt = __popcll(members);
+      if (cnt <= REPL) {  // uniform
+        for (unsigned long long mm = members; mm; mm &= mm - 1) add(__builtin_amdgcn_readlane(i3, __ffsll(mm) - 1));
+      } else {
+        if (q == qg) s_i3[wave][__popcll(members & ((1ull << lane) - 1))] = i3;
+        tt_wave_lds_order();
+        for (int m = jj0; m < cnt; m += ROWS) add(s_i3[wave][m]);
+        tt_wave_lds_order();  // the next group overwrites the list
+#pragma unroll
+        for (int o = L; o < TT_WAVE; o <<= 1)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            s[i].x += __shfl_xor(s[i].x, o, TT_WAVE); s[i].y += __shfl_xor(s[i].y, o, TT_WAVE);
+            s[i].z += __shfl_xor(s[i].z, o, TT_WAVE); s[i].w += __shfl_xor(s[i].w, o, TT_WAVE);
+          }
+      }
+#pragma unroll
+      for (int k = 0; k < NK; ++k) {
+        const float pk[4] = {p[k].x, p[k].y, p[k].z, p[k].w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          acc[k][0] = fmaf(pk[i], s[i].x, acc[k][0]); acc[k][1] = fmaf(pk[i], s[i].y, acc[k][1]);
+          acc[k][2] = fmaf(pk[i], s[i].z, acc[k][2]); acc[k][3] = fmaf(pk[i], s[i].w, acc[k][3]);
+        }
+      }
+    }
+  }
+  // over r2: the L lanes of a row; one of them leaves the row's four columns
+#pragma unroll
+  for (int k = 0; k < NK; ++k)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+#pragma unroll
+      for (int o = 1; o < L; o <<= 1) acc[k][j] += __shfl_xor(acc[k][j], o, TT_WAVE);
+      if (r4 == (k & (L - 1))) s_out[wave][4 * (jj0 + ROWS * k) + j] = acc[k][j];
+    }
+  if constexpr (WPB == 1) {
+    tt_wave_lds_order();
+    for (int o = lane; o < D; o += TT_WAVE) d.out[(size_t)b * D + o] = s_out[wave][o];
+  } else {
+    __syncthreads();
+    if (threadIdx.x < D) {
+      float sum = s_out[0][threadIdx.x];
+#pragma unroll
+      for (int w = 1; w < WPB; ++w) sum += s_out[w][threadIdx.x];
+      d.out[(size_t)b * D + threadIdx.x] = sum;
+    }
+  }
+}
+
 }  // namespace
 
 size_t ttk_bag_chains_lds_per_wave(const TTShape &sh) {
@@ -157,6 +269,24 @@ tt_status ttk_forward_sample(const TTBatch &b, hipStream_t s) {
     TTProfScope prof(&b.host[0].plan, TT_KERNEL_P12_FILL, s);
     TT_LAUNCH(k_p12_fill, grid, TT_BLOCK, sh.S1 * sizeof(float), s, b);
     if (tt_launch_status() != TT_OK) return TT_ERR_HIP;
+  }
+  if (ttk_batch_mfma(b)) {
+    const long long bags = tt_batch_max(b, [](const TTDev &d) { return (long long)d.num_bags; });
+    if (bags == 0) return TT_OK;
+    // bags of more than one 64-lookup round on average are shared by a workgroup's four wavefronts; its
+    // wavefronts serve a bag each otherwise (the longest bags of the batch's tables decide)
+    bool long_bags = false;
+    for (int t = 0; t < b.T; ++t) long_bags = long_bags || b.host[t].nnz / TT_WAVE >= b.host[t].num_bags;
+    const long long grid = long_bags ? bags : (bags + TT_BLOCK / TT_WAVE - 1) / (TT_BLOCK / TT_WAVE);
+    TTProfScope prof(&b.host[0].plan, TT_KERNEL_BAG_CHAINS, s);
+    if (sh.R2 == 32) {
+      if (long_bags) TT_LAUNCH_T2(k_bag_chains_4x8x4, 32, 4, grid, TT_BLOCK, 0, s, b);
+      else TT_LAUNCH_T2(k_bag_chains_4x8x4, 32, 1, grid, TT_BLOCK, 0, s, b);
+    } else {
+      if (long_bags) TT_LAUNCH_T2(k_bag_chains_4x8x4, 64, 4, grid, TT_BLOCK, 0, s, b);
+      else TT_LAUNCH_T2(k_bag_chains_4x8x4, 64, 1, grid, TT_BLOCK, 0, s, b);
+    }
+    return tt_launch_status();
   }
   // bags: as many wavefronts per workgroup (4, 2 or 1) as fit in 64 KB of LDS
   const size_t per_wave = ttk_bag_chains_lds_per_wave(sh);
