@@ -343,6 +343,9 @@ tt_status tt_core_sgd_update_batched(int num_tables, tt_batch_item *items, float
  *                     offset other than 0 or a last one other than nnz[t] is written as -1, which
  *                     tt_index_reorder reports as an invalid CSR array.
  * One launch on `stream`; nothing is read on the host.  At most TT_FUSE_MAX_TABLES members.
+ *
+ * tt_fuse_lookups_starts is the same for members whose offsets hold the bag STARTS only
+ * (int64[num_bags[t]], torch.nn.EmbeddingBag's default): member t's last bag ends at nnz[t].
  */
 #define TT_FUSE_MAX_TABLES 32
 typedef struct {
@@ -356,6 +359,10 @@ tt_status tt_fuse_lookups(const tt_fuse_members *members, const int64_t *const *
                           const int64_t *const *offsets, const int64_t *const *remaps,
                           const int64_t *nnz, const int64_t *num_bags, int64_t *fused_indices,
                           int64_t *fused_offsets, void *stream);
+tt_status tt_fuse_lookups_starts(const tt_fuse_members *members, const int64_t *const *indices,
+                                 const int64_t *const *starts, const int64_t *const *remaps,
+                                 const int64_t *nnz, const int64_t *num_bags, int64_t *fused_indices,
+                                 int64_t *fused_offsets, void *stream);
 
 /*
  * Index-graph edges of one batch (Section III-G, index-graph generation algorithm): the weighted

@@ -26,7 +26,7 @@ TT_ERR_UNAVAILABLE = -6
 EXPORTS = ("tt_workspace_bytes", "tt_index_reorder", "tt_emb_bag_forward", "tt_emb_bag_backward",
            "tt_core_sgd_update", "tt_emb_bag_backward_sgd", "tt_emb_bag_forward_static", "tt_reuse_buffer_bytes", "tt_emb_bag_forward_sample",
            "tt_bf16_cores_bytes", "tt_cores_to_bf16", "tt_emb_bag_forward_bf16",
-           "tt_index_graph_workspace_bytes", "tt_index_graph_edges", "tt_fuse_shape", "tt_fuse_lookups", "tt_plan_status", "tt_strerror", "tt_prof_create", "tt_prof_destroy",
+           "tt_index_graph_workspace_bytes", "tt_index_graph_edges", "tt_fuse_shape", "tt_fuse_lookups", "tt_fuse_lookups_starts", "tt_plan_status", "tt_strerror", "tt_prof_create", "tt_prof_destroy",
            "tt_prof_collect", "tt_kernel_name", "tt_batch_desc_bytes", "tt_index_reorder_batched",
            "tt_emb_bag_forward_batched", "tt_emb_bag_backward_batched", "tt_core_sgd_update_batched")
 KERNELS = {"fwd_contract": 0, "bag_sum": 1, "grad_merge": 2, "bwd_contract": 3, "sort_scatter": 4, "sgd": 5,
@@ -122,6 +122,8 @@ def load_library():
         lib.tt_fuse_shape.argtypes = [vp, vp]
         lib.tt_fuse_lookups.restype = ctypes.c_int
         lib.tt_fuse_lookups.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, vp]
+        lib.tt_fuse_lookups_starts.restype = ctypes.c_int
+        lib.tt_fuse_lookups_starts.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, vp]
         lib.tt_plan_status.restype = ctypes.c_int
         lib.tt_plan_status.argtypes = [vp, vp, vp]
         lib.tt_prof_create.restype = vp
@@ -156,12 +158,12 @@ def _check(status: int, where: str):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    # the current stream's handle without a stream object (four microseconds a call)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) if stream is None else stream.cuda_stream
 
 
 def _dev_i64(t, name):
@@ -456,9 +458,10 @@ class FusedLayout:
             b0 += int(nb)
         return out
 
-    def fuse_lookups(self, indices, offsets, remaps=None, out=None, stream=None):
+    def fuse_lookups(self, indices, offsets, remaps=None, out=None, stream=None, starts=False):
         """Maps the members' `(indices[t], offsets[t])` (CSR offsets, `bags + 1` long) into the fused
-        table: returns `(fused_indices, fused_offsets)`; `out` may bring the two tensors to write."""
+        table: returns `(fused_indices, fused_offsets)`; `out` may bring the two tensors to write.
+        `starts=True`: the offsets hold the bag starts only (`bags` long)."""
         T = len(self.members)
         if len(indices) != T or len(offsets) != T:
             raise ValueError("one (indices, offsets) pair per member table")
@@ -466,7 +469,7 @@ class FusedLayout:
         off = [_dev_i64(x, "offsets") for x in offsets]
         rm = [None] * T if remaps is None else [_dev_i64(x, "remap") for x in remaps]
         nnz = [x.numel() for x in idx]
-        nb = [x.numel() - 1 for x in off]
+        nb = [x.numel() - (0 if starts else 1) for x in off]
         dev = off[0].device
         if out is None:
             out = (torch.empty(sum(nnz), dtype=torch.int64, device=dev),
@@ -476,8 +479,9 @@ class FusedLayout:
             raise ValueError("fused_indices / fused_offsets have the wrong length")
         ptrs = lambda ts: (ctypes.c_void_p * T)(*[None if x is None or x.numel() == 0 else x.data_ptr() for x in ts])
         i64s = lambda vs: (ctypes.c_int64 * T)(*vs)
-        st = load_library().tt_fuse_lookups(ctypes.byref(self.c), ptrs(idx), ptrs(off), ptrs(rm) if remaps is not None else None,
-                                            i64s(nnz), i64s(nb), _ptr(f_idx), _ptr(f_off), _stream(stream))
+        call = load_library().tt_fuse_lookups_starts if starts else load_library().tt_fuse_lookups
+        st = call(ctypes.byref(self.c), ptrs(idx), ptrs(off), ptrs(rm) if remaps is not None else None,
+                  i64s(nnz), i64s(nb), _ptr(f_idx), _ptr(f_off), _stream(stream))
         _check(st, "tt_fuse_lookups")
         return f_idx, f_off
 

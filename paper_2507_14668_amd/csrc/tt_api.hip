@@ -431,7 +431,15 @@ tt_status tt_fuse_lookups(const tt_fuse_members *members, const int64_t *const *
                           const int64_t *const *offsets, const int64_t *const *remaps,
                           const int64_t *nnz, const int64_t *num_bags, int64_t *fused_indices,
                           int64_t *fused_offsets, void *stream) {
-  return ttk_fuse_lookups(members, indices, offsets, remaps, nnz, num_bags, fused_indices, fused_offsets,
+  return ttk_fuse_lookups(members, indices, offsets, remaps, nnz, num_bags, false, fused_indices, fused_offsets,
+                          (hipStream_t)stream);
+}
+
+tt_status tt_fuse_lookups_starts(const tt_fuse_members *members, const int64_t *const *indices,
+                                 const int64_t *const *starts, const int64_t *const *remaps,
+                                 const int64_t *nnz, const int64_t *num_bags, int64_t *fused_indices,
+                                 int64_t *fused_offsets, void *stream) {
+  return ttk_fuse_lookups(members, indices, starts, remaps, nnz, num_bags, true, fused_indices, fused_offsets,
                           (hipStream_t)stream);
 }
 

@@ -10,14 +10,15 @@ namespace {
 struct FuseMember {
   int n2, n3;             // row factors 2 and 3 of the member (factor 1 follows from the quotient)
   int o1, o2, o3;         // the member's first index in every fused core
-  int pad;
+  unsigned mul3, sh3, mul2, sh2;  // exact division by n3 / n2 (tt_div)
   long long num_rows;     // valid rows of the member
   long long l0, b0;       // first fused lookup / first fused bag of the member
   long long nnz, bags;
   const int64_t *idx, *off, *remap;
 };
 struct FuseArgs {
-  int T, N2, N3, pad;
+  int T, N2, N3;
+  int starts_only;        // the members' offsets hold the bag starts; a member's last bag ends at its nnz
   long long total_nnz, total_bags;
   FuseMember m[TT_FUSE_MAX_TABLES];
 };
@@ -35,15 +36,16 @@ k_fuse_lookups(FuseArgs a, int64_t *__restrict__ fused_idx, int64_t *__restrict_
       if (m.remap && i >= 0 && i < m.num_rows) i = m.remap[i];
       long long v = -1;
       if (i >= 0 && i < m.num_rows) {
-        const long long pre = i / m.n3, i3 = i - pre * m.n3, i1 = pre / m.n2, i2 = pre - i1 * m.n2;
-        v = ((m.o1 + i1) * a.N2 + m.o2 + i2) * a.N3 + m.o3 + i3;
+        const int pre = tt_div((int)i, m.mul3, m.sh3), i3 = (int)i - pre * m.n3;  // (a table has fewer than 2^31 rows)
+        const int i1 = tt_div(pre, m.mul2, m.sh2), i2 = pre - i1 * m.n2;
+        v = ((long long)(m.o1 + i1) * a.N2 + m.o2 + i2) * a.N3 + m.o3 + i3;
       }
       fused_idx[m.l0 + p] = v;
     }
     if (p < m.bags) {  // offset p of the member; its last one (== nnz) is the next member's first
       const long long o = m.off[p];
       bool ok = o >= 0 && o <= m.nnz && (p != 0 || o == 0);
-      if (p == m.bags - 1) ok = ok && m.off[m.bags] == m.nnz;
+      if (p == m.bags - 1 && !a.starts_only) ok = ok && m.off[m.bags] == m.nnz;
       fused_off[m.b0 + p] = ok ? m.l0 + o : -1;
     }
   }
@@ -72,21 +74,24 @@ tt_status ttk_fuse_shape(const tt_fuse_members *mem, long long N[3]) {
 
 tt_status ttk_fuse_lookups(const tt_fuse_members *mem, const int64_t *const *indices,
                            const int64_t *const *offsets, const int64_t *const *remaps,
-                           const int64_t *nnz, const int64_t *num_bags, int64_t *fused_indices,
+                           const int64_t *nnz, const int64_t *num_bags, bool starts_only, int64_t *fused_indices,
                            int64_t *fused_offsets, hipStream_t s) {
   long long N[3];
   tt_status st = ttk_fuse_shape(mem, N);
   if (st != TT_OK) return st;
   if (!indices || !offsets || !nnz || !num_bags || !fused_offsets) return TT_ERR_INVALID_ARG;
   FuseArgs a = {};
-  a.T = mem->num_tables; a.N2 = (int)N[1]; a.N3 = (int)N[2];
+  a.T = mem->num_tables; a.N2 = (int)N[1]; a.N3 = (int)N[2]; a.starts_only = starts_only ? 1 : 0;
   long long o[3] = {0, 0, 0}, l0 = 0, b0 = 0, span = 1;
   for (int t = 0; t < a.T; ++t) {
     if (nnz[t] < 0 || num_bags[t] < 0 || (num_bags[t] == 0 && nnz[t] != 0)) return TT_ERR_INVALID_ARG;
-    if (!offsets[t] || (nnz[t] > 0 && !indices[t])) return TT_ERR_INVALID_ARG;
+    const bool reads_offsets = !starts_only || num_bags[t] > 0;
+    if ((reads_offsets && !offsets[t]) || (nnz[t] > 0 && !indices[t])) return TT_ERR_INVALID_ARG;
     FuseMember &m = a.m[t];
     m.n2 = mem->n[t][1]; m.n3 = mem->n[t][2];
     m.o1 = (int)o[0]; m.o2 = (int)o[1]; m.o3 = (int)o[2];
+    tt_div_constants(m.n3, &m.mul3, &m.sh3);
+    tt_div_constants(m.n2, &m.mul2, &m.sh2);
     m.num_rows = mem->num_rows[t];
     m.l0 = l0; m.b0 = b0; m.nnz = nnz[t]; m.bags = num_bags[t];
     m.idx = indices[t]; m.off = offsets[t]; m.remap = remaps ? remaps[t] : nullptr;

@@ -181,7 +181,7 @@ size_t ttk_index_graph_workspace_bytes(long long num_bags, long long max_pairs);
 tt_status ttk_fuse_shape(const tt_fuse_members *members, long long N[3]);
 tt_status ttk_fuse_lookups(const tt_fuse_members *members, const int64_t *const *indices,
                            const int64_t *const *offsets, const int64_t *const *remaps,
-                           const int64_t *nnz, const int64_t *num_bags, int64_t *fused_indices,
+                           const int64_t *nnz, const int64_t *num_bags, bool starts_only, int64_t *fused_indices,
                            int64_t *fused_offsets, hipStream_t s);
 tt_status ttk_index_graph_edges(const int64_t *indices, const int64_t *offsets, long long nnz, long long num_bags,
                                 const int32_t *rank, long long num_rows, long long hot, int max_group,
