@@ -32,6 +32,7 @@
 // MFMA operand layout (D = A[16x4] * B[4x16] + C): lane l supplies A[m = l%16][k = l/16] and
 // B[k = l/16][n = l%16] and holds C[m = 4*(l/16) + v][n = l%16] in component v.
 #include <mutex>
+#include <type_traits>
 
 #include "tt_internal.h"
 
@@ -307,25 +308,31 @@ k_bwd_mfma(TTArg<BATCHED> a) {
     int id_next_batch = fetch_row_id(1, mo);
     const int id_next_chunk = (more && !refill) ? fetch_row_id(0, mo + TT_MP) : 0;
 
+    // A chunk of at most 4 prefixes (the last one of an i2, and the only one of many in a small batch) fills one
+    // of the two row tiles: F1, T1 and dG2 leave the other out.  At R1 = 64 only (nine fused tables at batch 4096:
+    // 120.8 -> 109.4 us a launch, one table with 65 k one-hot lookups: 119.1 -> 115.5); at R1 = 32 the tiles are too
+    // short to pay for the branches (multi-hot, 10 k bags: 94.3 -> 96.8).
+    const bool half = R1 == 64 && cnt <= TT_MP / 2;  // uniform
     // ---- F1: P12 of the chunk, this wavefront's 32 columns -> P12s[p][cc = (j1, j2)][r2l] ----------
-    {
-      f32x4 acc[2][2];
+    auto f1 = [&](auto tiles) __attribute__((always_inline)) {
+      constexpr int MT = decltype(tiles)::value;
+      f32x4 acc[MT][2];
 #pragma unroll
-      for (int mt = 0; mt < 2; ++mt)
+      for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt) acc[mt][nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int ks = 0; ks < G::KS1; ++ks) {
-        float av[2];
+        float av[MT];
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt) av[mt] = As[(16 * mt + lm) * G::RS + 4 * ks + lq];
+        for (int mt = 0; mt < MT; ++mt) av[mt] = As[(16 * mt + lm) * G::RS + 4 * ks + lq];
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
+        for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
           for (int nt = 0; nt < 2; ++nt) acc[mt][nt] = MFMA(av[mt], breg[ks][nt], acc[mt][nt]);
       }
 #pragma unroll
-      for (int mt = 0; mt < 2; ++mt) {
+      for (int mt = 0; mt < MT; ++mt) {
         const int p = 4 * mt + lq;  // C row 4*lq + v -> prefix 4*mt + lq, j1 = v
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt) {
@@ -334,7 +341,8 @@ k_bwd_mfma(TTArg<BATCHED> a) {
           for (int v = 0; v < 4; ++v) P12s[p * G::PS + (v * 8 + j2) * RB + lm] = acc[mt][nt][v];
         }
       }
-    }
+    };
+    if (half) f1(std::integral_constant<int, 1>{}); else f1(std::integral_constant<int, 2>{});
     land_batch();
     __syncthreads();
 
@@ -471,22 +479,23 @@ k_bwd_mfma(TTArg<BATCHED> a) {
     }
 
     // ---- T1: this wavefront's tile(s) [16 (p,j1)] x [16 r1], K = the strip's 128 columns ------------
-    {
-      f32x4 acc1[G::T1_MT];
+    auto t1 = [&](auto tiles) __attribute__((always_inline)) {
+      constexpr int MT = decltype(tiles)::value;
+      f32x4 acc1[MT];
 #pragma unroll
-      for (int mt = 0; mt < G::T1_MT; ++mt) acc1[mt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+      for (int mt = 0; mt < MT; ++mt) acc1[mt] = (f32x4){0.f, 0.f, 0.f, 0.f};
       const int mt0 = G::NT1 == 4 ? 0 : (wave >> 1);
 #pragma unroll
       for (int ks = 0; ks < 32; ++ks) {
-        float av[G::T1_MT];
+        float av[MT];
 #pragma unroll
-        for (int mt = 0; mt < G::T1_MT; ++mt) av[mt] = Hs[(16 * (mt0 + mt) + lm) * G::HR + 4 * ks + lq];
+        for (int mt = 0; mt < MT; ++mt) av[mt] = Hs[(16 * (mt0 + mt) + lm) * G::HR + 4 * ks + lq];
 #pragma unroll
-        for (int mt = 0; mt < G::T1_MT; ++mt) acc1[mt] = MFMA(av[mt], breg2[ks], acc1[mt]);
+        for (int mt = 0; mt < MT; ++mt) acc1[mt] = MFMA(av[mt], breg2[ks], acc1[mt]);
       }
       // C[m = (p, j1) = 4*lq + v][n = r1 = 16*t1_nt + lm]: one contribution per prefix and strip
 #pragma unroll
-      for (int mt = 0; mt < G::T1_MT; ++mt) {
+      for (int mt = 0; mt < MT; ++mt) {
         const int p = 4 * (mt0 + mt) + lq;
         if (p < cnt) {
           float *dst = t1buf + ((size_t)s_q[mo + p] * G::NSB + sblk) * G::S1 + 16 * t1_nt + lm;
@@ -494,23 +503,29 @@ k_bwd_mfma(TTArg<BATCHED> a) {
           for (int v = 0; v < 4; ++v) dst[v * R1] = acc1[mt][v];
         }
       }
-    }
+    };
+    if (half) t1(std::integral_constant<int, 1>{}); else t1(std::integral_constant<int, G::T1_MT>{});
     // ---- dG2 += G1^T H: M = r1, N = this wavefront's 32 columns, K = the chunk's 32 (p, j1) rows ----
     // Row m of the tile stands for r1 = 16*mt + 4*(m%4) + m/4, so that a lane's component v of tile (mt, nt) is
     // the gradient of the core-1 element it holds in breg[4*mt + v][nt].
     const int dg2_r1 = 4 * (lm & 3) + (lm >> 2);
+    auto dg2_rows = [&](int k0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      float av[G::NT1], bv[2];
+      for (int kk = 0; kk < 4; ++kk) {
+        const int ks = k0 + kk;
+        float av[G::NT1], bv[2];
 #pragma unroll
-      for (int mt = 0; mt < G::NT1; ++mt) av[mt] = As[(4 * ks + lq) * G::RS + 16 * mt + dg2_r1];
+        for (int mt = 0; mt < G::NT1; ++mt) av[mt] = As[(4 * ks + lq) * G::RS + 16 * mt + dg2_r1];
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt) bv[nt] = Hs[(4 * ks + lq) * G::HR + 32 * wave + 16 * nt + lm];
+        for (int nt = 0; nt < 2; ++nt) bv[nt] = Hs[(4 * ks + lq) * G::HR + 32 * wave + 16 * nt + lm];
 #pragma unroll
-      for (int mt = 0; mt < G::NT1; ++mt)
+        for (int mt = 0; mt < G::NT1; ++mt)
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) acc2[mt][nt] = MFMA(av[mt], bv[nt], acc2[mt][nt]);
-    }
+          for (int nt = 0; nt < 2; ++nt) acc2[mt][nt] = MFMA(av[mt], bv[nt], acc2[mt][nt]);
+      }
+    };
+    dg2_rows(0);
+    if (!half) dg2_rows(4);
     if (more && refill) {  // uniform: the staged plan entries are used up, fetch the next 64
       __syncthreads();  // every reader of the plan entries is done
       fetch_meta(cs + TT_MP);
