@@ -145,15 +145,19 @@ k_bag_chains(TTArg<BATCHED> a, int lds_per_wave) {
 // jj0 + (64/L)*k, columns 4*r4 .. 4*r4+3 of the product (L = R2/4), and needs the four rows of S with the same
 // r2, which it gathers from core 2 itself as float4.  A group of up to REPL lookups is gathered by every row
 // of lanes alike; a larger one is dealt to the 64/L rows of lanes, whose sums are added by lane exchanges.
-// Sums over r2 across the L lanes are formed once per bag.  WPB wavefronts share a bag, 64 lookups each at
-// a time, and add their results in wavefront order.
-// Bound by the reads of the products (R2 = 32: 4 KB per group of a 64-lookup round, about 13 groups a round
-// at a Zipf exponent of 1.2), out of the infinity cache, and by how many of those chains are in flight;
-// 2000 bags of 100-300 lookups: 110 us (through LDS, one wavefront per bag: 256 us).
+// Sums over r2 across the L lanes are formed once per bag.
+// A round is 64 lookups of a wavefront's own bag (WPB = 1), or 256 lookups of the workgroup's bag, whose groups
+// belong to the wavefront their prefix slot names (slot mod 4: a prefix is read once per 256 lookups, and the
+// hot prefixes, neighbours in slot order, go to different wavefronts); the four results are added in wavefront order.
+// Bound by the reads of the products (R2 = 32: 4 KB per group), out of the infinity cache, and by how many of
+// those chains are in flight.  2000 bags of 100-300 lookups, Zipf exponent 1.2: 101.5 us (one slice
+// in flight instead of two: 105; a round of 64 for each wavefront of a shared bag: 110; one wavefront per bag and
+// products through LDS: 256).
 template <bool BATCHED, int R2, int WPB>
-__global__ void __launch_bounds__(TT_BLOCK)
+__global__ void __launch_bounds__(TT_BLOCK, 4)
 k_bag_chains_4x8x4(TTArg<BATCHED> a) {
   constexpr int L = R2 / 4, ROWS = TT_WAVE / L, NK = 32 / ROWS, REPL = 6, D = 128, P = 32 * R2;
+  constexpr bool PAIR = R2 == 32;
   const TTDev &d = a.get();
   const TTShape &sh = d.sh;
   const float4 *__restrict__ g3 = reinterpret_cast<const float4 *>(d.g[2]);
@@ -162,7 +166,9 @@ k_bag_chains_4x8x4(TTArg<BATCHED> a) {
   const int32_t *__restrict__ lookup2row = d.plan.lookup2row, *__restrict__ row2pref = d.plan.row2pref,
                 *__restrict__ uniq_row = d.plan.uniq_row;
   __shared__ float s_out[TT_BLOCK / TT_WAVE][D];
-  __shared__ int s_i3[TT_BLOCK / TT_WAVE][TT_WAVE];
+  __shared__ int s_list[TT_BLOCK / TT_WAVE][WPB * TT_WAVE];              // i3 of the lookups of a large group
+  __shared__ int s_q[WPB == 1 ? 1 : TT_BLOCK], s_i3[WPB == 1 ? 1 : TT_BLOCK];  // the round's lookups
+  static_assert(WPB == 1 || WPB == TT_BLOCK / TT_WAVE, "a wavefront per bag, or the workgroup");
   const int lane = threadIdx.x & (TT_WAVE - 1), wave = threadIdx.x / TT_WAVE;
   const int r4 = lane & (L - 1), jj0 = lane / L;
   const int b = WPB == 1 ? (int)blockIdx.x * (TT_BLOCK / TT_WAVE) + wave : (int)blockIdx.x;
@@ -174,40 +180,95 @@ k_bag_chains_4x8x4(TTArg<BATCHED> a) {
   const long long o0 = offsets[b], o1 = offsets[b + 1], nnz = d.nnz;
   const long long lo = o0 < 0 ? 0 : (o0 > nnz ? nnz : o0), hi = o1 < lo ? lo : (o1 > nnz ? nnz : o1);
   const size_t rstep = (size_t)sh.n3;  // float4 between consecutive r2 of core 2
-  for (long long base = lo + (WPB == 1 ? 0 : wave) * TT_WAVE; base < hi; base += WPB * TT_WAVE) {  // uniform
-    // this lane's lookup: prefix slot and i3 (an invalid lookup has no row slot and takes no part)
-    const long long l = base + lane;
-    const int u = l < hi ? lookup2row[l] : -1;
-    const int q = u >= 0 ? row2pref[u] : -1;
-    const int row = u >= 0 ? uniq_row[u] : 0, i3 = row - tt_div(row, sh.mul3, sh.sh3) * sh.n3;
-    unsigned long long left = __ballot(q >= 0);
-    while (left) {  // uniform: one round per distinct prefix among the 64 lookups
-      const int first = __ffsll(left) - 1;
-      const int qg = __builtin_amdgcn_readlane(q, first);
-      const unsigned long long members = __ballot(q == qg);
-      left &= ~members;
+  for (long long base = lo; base < hi; base += WPB * TT_WAVE) {  // uniform
+    // prefix slot and i3 of the round's lookups, lane + 64*j (an invalid lookup has no row slot and takes no part)
+    int q[WPB], i3[WPB];
+    {
+      const long long l = base + (WPB == 1 ? lane : (int)threadIdx.x);
+      const int u = l < hi ? lookup2row[l] : -1;
+      q[0] = u >= 0 ? row2pref[u] : -1;
+      const int row = u >= 0 ? uniq_row[u] : 0;
+      i3[0] = row - tt_div(row, sh.mul3, sh.sh3) * sh.n3;
+    }
+    unsigned long long left[WPB];
+    if constexpr (WPB > 1) {
+      __syncthreads();  // the previous round has been read
+      s_q[threadIdx.x] = q[0];
+      s_i3[threadIdx.x] = i3[0];
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < WPB; ++j) {
+        q[j] = s_q[j * TT_WAVE + lane];
+        i3[j] = s_i3[j * TT_WAVE + lane];
+        left[j] = __ballot(q[j] >= 0 && (q[j] & (WPB - 1)) == wave);
+      }
+    } else {
+      left[0] = __ballot(q[0] >= 0);
+    }
+    while (true) {  // uniform: one turn per distinct prefix of this wavefront
+      int qg = -1;
+#pragma unroll
+      for (int j = WPB - 1; j >= 0; --j)
+        if (left[j]) qg = __builtin_amdgcn_readlane(q[j], __ffsll(left[j]) - 1);
+      if (qg < 0) break;
       const float4 *src = reinterpret_cast<const float4 *>(p12buf + (size_t)qg * P) + lane;
       float4 p[NK];
 #pragma unroll
       for (int k = 0; k < NK; ++k) p[k] = src[TT_WAVE * k];
+      unsigned long long members[WPB];
+      int cnt = 0;
+#pragma unroll
+      for (int j = 0; j < WPB; ++j) {
+        members[j] = __ballot(q[j] == qg);
+        left[j] &= ~members[j];
+        cnt += __popcll(members[j]);
+      }
       float4 s[4];  // rows 4*r4 + i of the summed core-2 slices
 #pragma unroll
       for (int i = 0; i < 4; ++i) s[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-      auto add = [&](int m_i3) __attribute__((always_inline)) {
-        const float4 *gp = g3 + (size_t)(4 * r4) * rstep + m_i3;
-        float4 x[4];
+      // slices of two lookups, all eight loads in flight (R2 = 64 has no registers left for the second four)
+      auto add = [&](int m, int m2, bool two) __attribute__((always_inline)) {
+        const float4 *gp = g3 + (size_t)(4 * r4) * rstep;
+        float4 x[4], y[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) x[i] = gp[(size_t)i * rstep];
+        for (int i = 0; i < 4; ++i) x[i] = gp[(size_t)i * rstep + m];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (PAIR) y[i] = gp[(size_t)i * rstep + m2];
 #pragma unroll
         for (int i = 0; i < 4; ++i) { s[i].x += x[i].x; s[i].y += x[i].y; s[i].z += x[i].z; s[i].w += x[i].w; }
+        if (PAIR) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            s[i].x += two ? y[i].x : 0.f; s[i].y += two ? y[i].y : 0.f; s[i].z += two ? y[i].z : 0.f; s[i].w += two ? y[i].w : 0.f;
+          }
+        }
       };
-      const int cnt = __popcll(members);
       if (cnt <= REPL) {  // uniform
-        for (unsigned long long mm = members; mm; mm &= mm - 1) add(__builtin_amdgcn_readlane(i3, __ffsll(mm) - 1));
+#pragma unroll
+        for (int j = 0; j < WPB; ++j)
+          for (unsigned long long mm = members[j]; mm;) {  // uniform
+            const int m = __builtin_amdgcn_readlane(i3[j], __ffsll(mm) - 1);
+            mm &= mm - 1;
+            if (PAIR && mm) {
+              add(m, __builtin_amdgcn_readlane(i3[j], __ffsll(mm) - 1), true);
+              mm &= mm - 1;
+            } else {
+              add(m, m, false);
+            }
+          }
       } else {
-        if (q == qg) s_i3[wave][__popcll(members & ((1ull << lane) - 1))] = i3;
+        int before = 0;
+#pragma unroll
+        for (int j = 0; j < WPB; ++j) {
+          if (q[j] == qg) s_list[wave][before + __popcll(members[j] & ((1ull << lane) - 1))] = i3[j];
+          before += __popcll(members[j]);
+        }
         tt_wave_lds_order();
-        for (int m = jj0; m < cnt; m += ROWS) add(s_i3[wave][m]);
+        for (int m = jj0; m < cnt; m += PAIR ? 2 * ROWS : ROWS) {
+          const bool two = PAIR && m + ROWS < cnt;
+          add(s_list[wave][m], s_list[wave][two ? m + ROWS : m], two);
+        }
         tt_wave_lds_order();  // the next group overwrites the list
 #pragma unroll
         for (int o = L; o < TT_WAVE; o <<= 1)
@@ -273,8 +334,9 @@ tt_status ttk_forward_sample(const TTBatch &b, hipStream_t s) {
   if (ttk_batch_mfma(b)) {
     const long long bags = tt_batch_max(b, [](const TTDev &d) { return (long long)d.num_bags; });
     if (bags == 0) return TT_OK;
-    // bags of more than one 64-lookup round on average are shared by a workgroup's four wavefronts; its
-    // wavefronts serve a bag each otherwise (the longest bags of the batch's tables decide)
+    // bags of 64 lookups and more on average are shared by a workgroup's four wavefronts (there are few of them, and
+    // a wavefront would serve a long chain alone); its wavefronts serve a bag each otherwise, which leaves
+    // none of them idle.  The table with the longest bags decides for a batch.
     bool long_bags = false;
     for (int t = 0; t < b.T; ++t) long_bags = long_bags || b.host[t].nnz / TT_WAVE >= b.host[t].num_bags;
     const long long grid = long_bags ? bags : (bags + TT_BLOCK / TT_WAVE - 1) / (TT_BLOCK / TT_WAVE);
