@@ -149,10 +149,10 @@ k_bag_chains(TTArg<BATCHED> a, int lds_per_wave) {
 // A round is 64 lookups of a wavefront's own bag (WPB = 1), or 256 lookups of the workgroup's bag, whose groups
 // belong to the wavefront their prefix slot names (slot mod 4: a prefix is read once per 256 lookups, and the
 // hot prefixes, neighbours in slot order, go to different wavefronts); the four results are added in wavefront order.
-// Bound by the reads of the products (R2 = 32: 4 KB per group), out of the infinity cache, and by how many of
-// those chains are in flight.  2000 bags of 100-300 lookups, Zipf exponent 1.2: 101.5 us (one slice
-// in flight instead of two: 105; a round of 64 for each wavefront of a shared bag: 110; one wavefront per bag and
-// products through LDS: 256).
+// Bound by latency: a group is a chain of its product read (R2 = 32: 4 KB, out of the infinity cache) and the
+// gathers of its members, and four or five wavefronts per SIMD are in flight (a quarter fewer product reads gave 4 %).
+// 2000 bags of 100-300 lookups, Zipf exponent 1.2: 101.5 us (one slice in flight instead of two: 105; a round of 64
+// for each wavefront of a shared bag: 110; one wavefront per bag and products through LDS: 256).
 template <bool BATCHED, int R2, int WPB>
 __global__ void __launch_bounds__(TT_BLOCK, 4)
 k_bag_chains_4x8x4(TTArg<BATCHED> a) {
@@ -339,6 +339,7 @@ tt_status ttk_forward_sample(const TTBatch &b, hipStream_t s) {
     // none of them idle.  The table with the longest bags decides for a batch.
     bool long_bags = false;
     for (int t = 0; t < b.T; ++t) long_bags = long_bags || b.host[t].nnz / TT_WAVE >= b.host[t].num_bags;
+    long_bags = long_bags && bags < (1 << 23);  // (a launch has fewer than 2^32 threads)
     const long long grid = long_bags ? bags : (bags + TT_BLOCK / TT_WAVE - 1) / (TT_BLOCK / TT_WAVE);
     TTProfScope prof(&b.host[0].plan, TT_KERNEL_BAG_CHAINS, s);
     if (sh.R2 == 32) {
