@@ -868,52 +868,55 @@ k_bwd_dg2(TTArg<BATCHED> a, int col_tiles, unsigned dmul, unsigned dsh) {
   const int bz = blockIdx.x % r1_tiles, by = (blockIdx.x / r1_tiles) % col_tiles, i2 = blockIdx.x / (r1_tiles * col_tiles);
   const int s0 = i2_seg[i2], nq = i2_seg[i2 + 1] - s0;
   if (fused && nq == 0) return;  // untouched slice: nothing to apply
-  const int K = nq * sh.d1;      // at most n1*d1
   __shared__ __align__(16) float Hs[TT_DG2_K][TT_DG2_C], Gs[TT_DG2_K][TT_DG2_R];
   __shared__ int s_i1[2][TT_DG2_K], s_q[2][TT_DG2_K], s_j1[2][TT_DG2_K];
   const int c = threadIdx.x % TT_DG2_C, rg = threadIdx.x / TT_DG2_C;  // 4 values of r1 per thread
   const int col = by * TT_DG2_C + c, r1b = bz * TT_DG2_R;
   constexpr int HL = TT_DG2_K * TT_DG2_C / TT_BLOCK, GL = TT_DG2_K * TT_DG2_R / TT_BLOCK;
-  auto plan_of = [&](int t) __attribute__((always_inline)) {  // K entries of chunk t -> LDS
-    const int k = t * TT_DG2_K + threadIdx.x;
-    if (threadIdx.x < TT_DG2_K && k < K) {
-      const int s = tt_div(k, dmul, dsh);
+  TTPairWalk<TT_DG2_K> walk(nq, sh.d1, dmul, dsh);
+  auto plan_of = [&](int slot, int n) __attribute__((always_inline)) {  // the walk's chunk (n pairs) -> LDS
+    if ((int)threadIdx.x < n) {
+      int s, j1;
+      walk.pair(threadIdx.x, s, j1);
       const int4 m = pref_meta[s0 + s];
-      s_i1[t & 1][threadIdx.x] = m.x; s_q[t & 1][threadIdx.x] = m.w; s_j1[t & 1][threadIdx.x] = k - s * sh.d1;
+      s_i1[slot][threadIdx.x] = m.x; s_q[slot][threadIdx.x] = m.w; s_j1[slot][threadIdx.x] = j1;
     }
   };
   float h[HL], g[GL];
-  auto fetch = [&](int t) __attribute__((always_inline)) {  // operands of chunk t -> registers (zero past the end)
+  auto fetch = [&](int slot, int n) __attribute__((always_inline)) {  // operands of a chunk -> registers (zero past its end)
 #pragma unroll
     for (int i = 0; i < HL; ++i) {
       const int kk = rg + i * (TT_BLOCK / TT_DG2_C);
-      const bool in = t * TT_DG2_K + kk < K && col < sh.S2;
-      h[i] = in ? hbuf[(size_t)s_q[t & 1][kk] * sh.P + s_j1[t & 1][kk] * sh.S2 + col] : 0.f;
+      const bool in = kk < n && col < sh.S2;
+      h[i] = in ? hbuf[(size_t)s_q[slot][kk] * sh.P + s_j1[slot][kk] * sh.S2 + col] : 0.f;
     }
 #pragma unroll
     for (int i = 0; i < GL; ++i) {
       const int kk = threadIdx.x / TT_DG2_R + i * (TT_BLOCK / TT_DG2_R), r1 = r1b + threadIdx.x % TT_DG2_R;
-      const bool in = t * TT_DG2_K + kk < K && r1 < sh.R1;
-      g[i] = in ? g1[(size_t)s_i1[t & 1][kk] * sh.S1 + s_j1[t & 1][kk] * sh.R1 + r1] : 0.f;
+      const bool in = kk < n && r1 < sh.R1;
+      g[i] = in ? g1[(size_t)s_i1[slot][kk] * sh.S1 + s_j1[slot][kk] * sh.R1 + r1] : 0.f;
     }
   };
   float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  const int chunks = (K + TT_DG2_K - 1) / TT_DG2_K;
-  if (chunks > 0) {  // uniform
-    plan_of(0);
+  int n = walk.count(), next = 0;  // pairs of the chunk that is multiplied and of the one after it (all uniform)
+  if (n > 0) {
+    plan_of(0, n);
     __syncthreads();
-    fetch(0);
-    plan_of(1);
+    fetch(0, n);
+    walk.advance();
+    next = walk.count();
+    plan_of(1, next);
   }
-  for (int t = 0; t < chunks; ++t) {
+  for (int slot = 0; n > 0; slot ^= 1) {
 #pragma unroll
     for (int i = 0; i < HL; ++i) Hs[rg + i * (TT_BLOCK / TT_DG2_C)][c] = h[i];
 #pragma unroll
     for (int i = 0; i < GL; ++i) Gs[threadIdx.x / TT_DG2_R + i * (TT_BLOCK / TT_DG2_R)][threadIdx.x % TT_DG2_R] = g[i];
     __syncthreads();  // the chunk and the next one's plan entries are visible
-    if (t + 1 < chunks) fetch(t + 1);
-    plan_of(t + 2);   // over this chunk's entries, which were last read before the barrier
-    const int n = K - t * TT_DG2_K < TT_DG2_K ? K - t * TT_DG2_K : TT_DG2_K;
+    if (next > 0) fetch(slot ^ 1, next);
+    walk.advance();
+    const int after = walk.count();
+    plan_of(slot, after);  // over this chunk's entries, which were last read before the barrier
 #pragma unroll 4
     for (int kk = 0; kk < n; ++kk) {
       const float x = Hs[kk][c];
@@ -922,6 +925,8 @@ k_bwd_dg2(TTArg<BATCHED> a, int col_tiles, unsigned dmul, unsigned dsh) {
       acc[2] = fmaf(y.z, x, acc[2]); acc[3] = fmaf(y.w, x, acc[3]);
     }
     __syncthreads();  // the next chunk overwrites the tiles
+    n = next;
+    next = after;
   }
   if (col >= sh.S2) return;
 #pragma unroll

@@ -273,9 +273,35 @@ static inline tt_status tt_launch_status() {
 
 // ---- device helpers -----------------------------------------------------------------------
 #ifdef __HIPCC__
-__device__ __forceinline__ int tt_div(int x, unsigned mul, unsigned sh) {
+__host__ __device__ __forceinline__ int tt_div(int x, unsigned mul, unsigned sh) {
   return (int)(((unsigned long long)(unsigned)x * mul) >> (31 + sh));
 }
+// The pairs (prefix s of nq, j < d) of a reduction over K = nq * d, in order, cut into chunks of C: where the current
+// chunk starts, how many pairs it has and which one its k-th pair is.  There can be 2^31 pairs and more (two
+// million prefixes with d1 = 1023 are accepted), so a pair never gets a number of its own; mul, sh: exact division by d.
+template <int C>
+struct TTPairWalk {
+  int nq, d;
+  unsigned mul, sh;
+  int s, j;  // first pair of the chunk; (nq, 0) behind the last one
+  __host__ __device__ __forceinline__ TTPairWalk(int nq_, int d_, unsigned mul_, unsigned sh_)
+      : nq(nq_), d(d_), mul(mul_), sh(sh_), s(0), j(0) {}
+  __host__ __device__ __forceinline__ int count() const {
+    const long long left = (long long)(nq - s) * d - j;
+    return left < 0 ? 0 : (left < C ? (int)left : C);
+  }
+  __host__ __device__ __forceinline__ void pair(int k, int &ps, int &pj) const {  // k < count()
+    const int x = j + k, q = tt_div(x, mul, sh);
+    ps = s + q;
+    pj = x - q * d;
+  }
+  __host__ __device__ __forceinline__ void advance() {
+    int ps = nq, pj = 0;
+    if (count() == C) pair(C, ps, pj);
+    s = ps;
+    j = pj;
+  }
+};
 // Orders the LDS accesses of the lanes of one wavefront (a wavefront executes them in program
 // order; this keeps the compiler from moving them across).
 __device__ __forceinline__ void tt_wave_lds_order() {

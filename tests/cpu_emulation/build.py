@@ -5,6 +5,7 @@ nothing in the product path loads what is built here.
 
   build_shared(out_dir)            -> libtt_emb_emu.so, driven through ctypes by the CPU tests
   build_harness(out_dir, sanitize) -> harness executable under "address" (+UBSan), "memory" or "thread"
+  build_unit(out_dir, name)        -> executable of one unit test over tt_internal.h
 
 Two textual changes are made to the copies that are compiled: `extern __shared__ float x[];`
 becomes a pointer to the emulated dynamic LDS, and the switch that keeps the batched entry points
@@ -90,6 +91,15 @@ def build_harness(out_dir: str, sanitize: str = "address") -> str:
     objs, base = _compile(srcs, flags, out_dir, tag)
     exe = os.path.join(out_dir, "harness_" + sanitize)
     subprocess.run(base + flags + objs + ["-o", exe], check=True)
+    return exe
+
+
+def build_unit(out_dir: str, name: str) -> str:
+    """A small program (`name`.cpp in this folder) over the library's internal header."""
+    os.makedirs(out_dir, exist_ok=True)
+    exe = os.path.join(out_dir, name)
+    subprocess.run([CLANG, "-std=c++17", "-O2", "-D__HIPCC__", "-I" + HERE, "-I" + CSRC, "-I" + os.path.join(ROOT, "include"), "-pthread",
+                    "-Wno-unused-value", os.path.join(HERE, name + ".cpp"), os.path.join(HERE, "emu_runtime.cpp"), "-o", exe], check=True)
     return exe
 
 

@@ -279,3 +279,10 @@ def test_results_do_not_depend_on_workgroup_order(asan_harness):
     # first checksum: the planned arm (no atomics, must not move); second: the naive arm, whose
     # backward adds with float atomics in arrival order and is not expected to be bit-stable
     assert len(sums[0]) == 2 and sums[0][0] == sums[1][0]
+
+
+def test_pair_walk_of_the_core1_reduction():
+    """The chunks of (prefix, j1) pairs that the core-1 gradient of the plain kernels is summed over: the walk names
+    every pair once and in order, also where there are 2^31 pairs and more (two million prefixes, d1 = 1023)."""
+    res = subprocess.run([emu_build.build_unit(BUILD_DIR, "pair_walk")], capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0 and res.stdout.strip() == "ok", res.stdout + res.stderr
