@@ -853,7 +853,7 @@ k_bwd_prefix_wave(TTArg<BATCHED> a) {
 #define TT_DG2_K 64
 template <bool BATCHED>
 __global__ void __launch_bounds__(TT_BLOCK)
-k_bwd_dg2(TTArg<BATCHED> a, int col_tiles, unsigned dmul, unsigned dsh) {
+k_bwd_dg2(TTArg<BATCHED> a, int first_i2, int col_tiles, unsigned dmul, unsigned dsh) {
   const TTDev &d = a.get();
   const TTShape &sh = d.sh;
   const float *__restrict__ g1 = d.g[0], *__restrict__ hbuf = d.plan.hbuf;
@@ -862,10 +862,11 @@ k_bwd_dg2(TTArg<BATCHED> a, int col_tiles, unsigned dmul, unsigned dsh) {
   float *__restrict__ dg2 = d.fused ? const_cast<float *>(d.g[1]) : d.dg[1];
   const int fused = d.fused;
   const float lr = d.lr;
-  // grid.x enumerates (i2, column tile, r1 tile); grid.y is the table in a batched launch
+  // grid.x enumerates (i2 from first_i2 on, column tile, r1 tile); grid.y is the table in a batched launch
   const int r1_tiles = (sh.R1 + TT_DG2_R - 1) / TT_DG2_R;
-  if ((int)blockIdx.x >= sh.n2 * col_tiles * r1_tiles) return;
-  const int bz = blockIdx.x % r1_tiles, by = (blockIdx.x / r1_tiles) % col_tiles, i2 = blockIdx.x / (r1_tiles * col_tiles);
+  const int bz = blockIdx.x % r1_tiles, by = (blockIdx.x / r1_tiles) % col_tiles;
+  const int i2 = first_i2 + blockIdx.x / (r1_tiles * col_tiles);
+  if (i2 >= sh.n2) return;
   const int s0 = i2_seg[i2], nq = i2_seg[i2 + 1] - s0;
   if (fused && nq == 0) return;  // untouched slice: nothing to apply
   __shared__ __align__(16) float Hs[TT_DG2_K][TT_DG2_C], Gs[TT_DG2_K][TT_DG2_R];
@@ -1117,7 +1118,10 @@ tt_status ttk_backward_plan(const TTBatch &b, hipStream_t s) {
     const long long n2max = tt_batch_max(b, [](const TTDev &d) { return (long long)d.sh.n2; });
     unsigned dmul, dsh;
     tt_div_constants(sh.d1, &dmul, &dsh);
-    TT_LAUNCH(k_bwd_dg2, n2max * col_tiles * r1_tiles, TT_BLOCK, 0, s, b, col_tiles, dmul, dsh);
+    // as many i2 a launch as it takes workgroups for: one launch, but for tables of millions of them
+    const long long tiles = (long long)col_tiles * r1_tiles, most = TT_MAX_WORKGROUPS / tiles;
+    for (long long i2 = 0; i2 < n2max; i2 += most)
+      TT_LAUNCH(k_bwd_dg2, (n2max - i2 < most ? n2max - i2 : most) * tiles, TT_BLOCK, 0, s, b, (int)i2, col_tiles, dmul, dsh);
   }
   // 4. core 2: sum the per-row contributions of all rows sharing i3; core 0: sum the per-prefix
   //    contributions of all prefixes sharing i1 (contiguous)

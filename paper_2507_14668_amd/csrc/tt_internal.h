@@ -28,6 +28,7 @@ struct TTShape {
 
 #define TT_WAVE 64
 #define TT_BLOCK 256
+#define TT_MAX_WORKGROUPS ((1ll << 32) / TT_BLOCK - 1)  // of TT_BLOCK threads: a launch has fewer than 2^32 threads
 
 // ---- radix sort geometry ----------------------------------------------------------------
 #define TT_SORT_THREADS 512
