@@ -526,7 +526,7 @@ k_seg_whole(TTArg<BATCHED> arg, int blocks_a) {
 // launch of whole-segment workgroups; otherwise the two-stage sum, sharing its launches when their
 // vectors have the same width (the smaller one would otherwise pay two launches for a few workgroups).
 tt_status seg_sum_dg3_dg1(const TTBatch &b, hipStream_t s) {
-  SegParams p3 = seg_params(b, SEG_DG3, 0), p1 = seg_params(b, SEG_DG1, 0);
+  const SegParams p3 = seg_params(b, SEG_DG3, 0), p1 = seg_params(b, SEG_DG1, 0);
   bool whole = true;
   for (int t = 0; t < b.T && whole; ++t) {
     const TTDev &d = b.host[t];
@@ -536,8 +536,7 @@ tt_status seg_sum_dg3_dg1(const TTBatch &b, hipStream_t s) {
   if (whole) {
     // one launch has one vector width (d3 = 6 beside ranks of four, 12 k lookups: 26 us in the four launches of
     // two separate two-stage sums, 7 us here)
-    if (p3.vec != p1.vec) p3.vec = p1.vec = 1;
-    const int vec = p3.vec, W3 = p3.W;
+    const int vec = p3.vec == p1.vec ? p3.vec : 1, W3 = p3.W;
     const WholeSplit w1 = whole_split(p1.W, vec, TT_SEG_WHOLE_PARTS);
     const long long blocks3 = tt_batch_max(b, [=](const TTDev &d) {
       return (long long)d.sh.n3 * whole_split(W3, vec, whole_want3(d.sh.n3)).parts; });
@@ -549,9 +548,11 @@ tt_status seg_sum_dg3_dg1(const TTBatch &b, hipStream_t s) {
     const long long lds1 = (long long)(TT_BLOCK / w1.lanes) * (p1.W / w1.parts);
     const size_t lds = sizeof(float) * (size_t)(lds3 > lds1 ? lds3 : lds1);
     const long long grid = blocks3 + blocks1;
-    if (vec == 4) TT_LAUNCH_T(k_seg_whole, 4, grid, TT_BLOCK, lds, s, b, (int)blocks3);
-    else TT_LAUNCH_T(k_seg_whole, 1, grid, TT_BLOCK, lds, s, b, (int)blocks3);
-    return tt_launch_status();
+    if (grid <= TT_MAX_WORKGROUPS) {  // (millions of slices: the two-stage sum's workgroups follow the lookups)
+      if (vec == 4) TT_LAUNCH_T(k_seg_whole, 4, grid, TT_BLOCK, lds, s, b, (int)blocks3);
+      else TT_LAUNCH_T(k_seg_whole, 1, grid, TT_BLOCK, lds, s, b, (int)blocks3);
+      return tt_launch_status();
+    }
   }
   if (p3.W == p1.W && p3.vec == p1.vec && p3.lanes == p1.lanes && p3.blocks1 > 0 && p1.blocks1 > 0)
     return seg_launch(b, p3, SEG_DG3, &p1, SEG_DG1, -1, s);

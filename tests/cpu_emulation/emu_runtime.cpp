@@ -272,11 +272,19 @@ void host_only_release(const void *p) {
     if (host_only_regions[i].p == p) { host_only_regions.erase(host_only_regions.begin() + i); return; }
 }
 
+namespace { bool g_error = false; }
+bool take_error() { const bool e = g_error; g_error = false; return e; }
+
 void launch(dim3 grid, dim3 block, size_t lds, const char *name, const std::function<void()> &body) {
   ensure_pool();
   if (block.x > NW * WL || block.y != 1 || block.z != 1 || grid.x == 0 || grid.y == 0) {
     fprintf(stderr, "emu: bad launch %s grid %u,%u block %u\n", name, grid.x, grid.y, block.x);
     abort();
+  }
+  if ((uint64_t)grid.x * block.x >= (uint64_t)1 << 32) {  // the hardware would run the remainder of the division by 2^32
+    fprintf(stderr, "emu: launch %s of 2^32 threads or more (grid %u, block %u)\n", name, grid.x, block.x);
+    g_error = true;
+    return;
   }
   if (getenv("EMU_TRACE")) fprintf(stderr, "emu: launch %s grid (%u,%u) block %u lds %zu\n", name, grid.x, grid.y, block.x, lds);
   g_gridDim = grid; g_blockDim = block;

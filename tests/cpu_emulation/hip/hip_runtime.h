@@ -27,7 +27,7 @@ static inline unsigned __float_as_uint(float f) { unsigned u; memcpy(&u, &f, 4);
 typedef void *hipStream_t;
 typedef void *hipEvent_t;
 typedef int hipError_t;
-enum { hipSuccess = 0 };
+enum { hipSuccess = 0, hipErrorInvalidConfiguration = 9 };
 enum { hipMemcpyDeviceToHost = 2, hipMemcpyHostToDevice = 1 };
 enum { hipFuncAttributeMaxDynamicSharedMemorySize = 8 };
 
@@ -35,6 +35,7 @@ namespace emu {
 extern thread_local dim3 t_threadIdx;
 extern dim3 g_blockIdx, g_blockDim, g_gridDim;
 void launch(dim3 grid, dim3 block, size_t lds, const char *name, const std::function<void()> &body);
+bool take_error();  // a launch since the last call was refused
 void host_only(const void *p, size_t n);   // a region kernels must not touch: poisoned (ASan) while a launch runs
 void host_only_release(const void *p);
 void syncthreads();
@@ -63,7 +64,7 @@ void wave_mfma_16x16x4(float a, float b, float *c4);
 #define hipExtLaunchKernelGGL(kernel, grid, block, lds, stream, start_event, stop_event, flags, ...) \
   emu::launch(grid, block, lds, #kernel, [=]() { kernel(__VA_ARGS__); })
 
-static inline hipError_t hipGetLastError() { return hipSuccess; }
+static inline hipError_t hipGetLastError() { return emu::take_error() ? hipErrorInvalidConfiguration : hipSuccess; }
 static inline hipError_t hipGetDevice(int *dev) { *dev = 0; return hipSuccess; }
 enum { hipDeviceAttributeMultiprocessorCount = 1 };
 static inline hipError_t hipDeviceGetAttribute(int *v, int, int) { *v = 4; return hipSuccess; }  // few "compute units": the work queues are exercised

@@ -286,3 +286,44 @@ def test_pair_walk_of_the_core1_reduction():
     every pair once and in order, also where there are 2^31 pairs and more (two million prefixes, d1 = 1023)."""
     res = subprocess.run([emu_build.build_unit(BUILD_DIR, "pair_walk")], capture_output=True, text=True, timeout=300)
     assert res.returncode == 0 and res.stdout.strip() == "ok", res.stdout + res.stderr
+
+
+def test_launches_of_tables_with_millions_of_slices(emu):
+    """2.2 million i1 and vectors of two widths (d3 = 3 beside ranks of four): one workgroup per slice and column part would
+    be more threads than a launch holds, so the core-2 and core-0 sums take the two-stage route; the fused update of
+    the touched slices against 64 bits, every other slice of core 0 unchanged."""
+    lib, binding = emu
+    n, d, r = (2_200_000, 2, 2), (4, 2, 3), (1, 16, 5, 1)
+    rng = np.random.default_rng(9)
+    idx = np.concatenate([rng.integers(0, 4 * n[0], 20), [0, 4 * n[0] - 1, 3, 3]]).astype(np.int64)
+    u, inv = np.unique(idx, return_inverse=True)
+    off = np.arange(len(idx) + 1, dtype=np.int64)
+    i3, i2, i1 = u % 2, u // 2 % 2, u // 4
+    cores = [np.zeros(n[0] * d[0] * r[1], np.float32)] + [rng.standard_normal(s).astype(np.float32) for s in
+                                                          (r[1] * n[1] * d[1] * r[2], r[2] * n[2] * d[2])]
+    g1 = cores[0].reshape(n[0], d[0], r[1])
+    touched = np.unique(i1)
+    g1[touched] = rng.standard_normal((len(touched), d[0], r[1]))
+    old = [g1[touched].astype(np.float64)] + [c.astype(np.float64) for c in cores[1:]]
+    grad = rng.standard_normal((len(idx), d[0], d[1], d[2])).astype(np.float32)
+    shape = wl.TableShape(4 * n[0], n, d, r)
+    table = _table(binding, shape, cores)
+    ws, plan = _aligned(lib.tt_workspace_bytes(ctypes.byref(table), len(idx), len(idx))), binding.CPlan()
+    assert lib.tt_index_reorder(ctypes.byref(table), _ptr(idx), _ptr(off), len(idx), len(idx), None, _ptr(ws), ws.nbytes,
+                                ctypes.byref(plan), None) == 0
+    assert lib.tt_emb_bag_backward_sgd(ctypes.byref(table), ctypes.byref(plan), _ptr(idx), _ptr(off), len(idx), len(idx),
+                                       _ptr(grad), ctypes.c_float(0.25), None) == 0
+    merged = np.zeros((len(u),) + d)
+    np.add.at(merged, inv, grad.astype(np.float64))
+    a = old[0][np.searchsorted(touched, i1)]
+    b = old[1].reshape(r[1], n[1], d[1], r[2])[:, i2].transpose(1, 0, 2, 3)
+    c = old[2].reshape(r[2], n[2], d[2])[:, i3].transpose(1, 0, 2)
+    h = np.einsum("uabc,usc->uabs", merged, c)
+    new = [old[0].copy(), old[1].reshape(r[1], n[1], d[1], r[2]).copy(), old[2].reshape(r[2], n[2], d[2]).copy()]
+    for k in range(len(u)):
+        new[0][np.searchsorted(touched, i1[k])] -= 0.25 * np.einsum("abs,rbs->ar", h[k], b[k])
+        new[1][:, i2[k]] -= 0.25 * np.einsum("ar,abs->rbs", a[k], h[k])
+        new[2][:, i3[k]] -= 0.25 * np.einsum("ar,rbs,abc->sc", a[k], b[k], merged[k])
+    for got, ref in ((g1[touched], new[0]), (cores[1].reshape(new[1].shape), new[1]), (cores[2].reshape(new[2].shape), new[2])):
+        assert np.abs(got - ref).max() <= 1e-5 * np.abs(ref).max()
+    assert np.count_nonzero(g1.any(axis=(1, 2))) == len(touched)
