@@ -34,7 +34,8 @@ struct TTShape {
 #define TT_SORT_THREADS 512
 #define TT_SORT_ITEMS 2
 #define TT_SORT_TILE (TT_SORT_THREADS * TT_SORT_ITEMS)  // keys per workgroup per pass
-#define TT_SUPER_TILES 32    // tiles whose digit counts are also added up in one row
+#define TT_SCAN_TILES_MAX 64 // sorts of at most this many tiles add up the tiles' digit counts one by one
+#define TT_SUPER_TILES 32    // tiles whose digit counts are also added up in one row, in longer sorts
 #define TT_SUPER_SLOTS 6     // four passes of the main sort, two groupings
 #define TT_SMALL_MAX_LOOKUPS 2048  // batches of at most this many lookups get their plan from one workgroup
 #define TT_SMALL_MAX_BAGS 16384    // ... if they also have at most this many bags (it walks them alone)
@@ -71,7 +72,7 @@ struct TTSortTmp {
   int32_t *bin_total;              // [bins]
   int32_t *tile_sums;              // [2][tiles] head counts per tile of the unique pass
   int32_t *tile_base;              // [2][tiles + 1] first row / prefix slot of each tile
-  int32_t *super;                  // [TT_SUPER_SLOTS][tiles / TT_SUPER_TILES + 1][bins] counts of groups of tiles
+  int32_t *super;                  // [TT_SUPER_SLOTS][tiles / TT_SUPER_TILES + 1][bins] counts of groups of tiles (sorts above TT_SCAN_TILES_MAX tiles)
 };
 TTSortTmp tt_sort_tmp_view(const tt_plan *plan);
 size_t tt_sort_tmp_bytes(int64_t nnz, int64_t max_rows, int64_t max_prefixes);

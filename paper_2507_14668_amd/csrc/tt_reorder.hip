@@ -193,7 +193,9 @@ __device__ __forceinline__ void column_sums(const int32_t *__restrict__ hist, co
   }
   __syncthreads();
 }
+// (nullptr: a table of the batch that is short itself has no group rows, it adds up its few tiles)
 __device__ __forceinline__ int32_t *super_rows(const TTDev &d, int slot) {
+  if (d.sort_tiles <= TT_SCAN_TILES_MAX) return nullptr;
   return d.tmp.super + (size_t)slot * (d.sort_tiles / TT_SUPER_TILES + 1) * ((size_t)1 << TT_SORT_MAX_BITS);
 }
 // A tile's counts h[] -> its row of the [tile][bin] matrix, and into its group's row.
@@ -207,8 +209,7 @@ __device__ __forceinline__ void write_counts(const int *h, int nbins, int32_t *_
 // How a scatter finds its offsets: it adds up the counts of all tiles, of groups of tiles (main sort only:
 // the first kernel clears the group rows), or a launch of its own has scanned every column.
 enum { SCAN_TILES = 0, SCAN_SUPER = 1, SCAN_LAUNCH = 2 };
-#define TT_SCAN_TILES_MAX 64     // tiles
-#define TT_SCAN_SUPER_MAX 1024
+#define TT_SCAN_SUPER_MAX 1024   // tiles
 
 // ------------------------------------------------------------------ kernels of the main sort
 // First kernel of a plan.  Workgroup 0 initialises the counters; every workgroup takes one sort
@@ -236,7 +237,7 @@ k_extract_keys(TTArg<BATCHED> a, int in_a, int bits, int scan) {
   __shared__ int h[1 << TT_SORT_MAX_BITS];
   const int nbins = 1 << bits;
   if (scan == SCAN_SUPER) {  // group rows of every pass and grouping: the tiles add into them
-    const int words = TT_SUPER_SLOTS * (d.sort_tiles / TT_SUPER_TILES + 1) << TT_SORT_MAX_BITS;
+    const int words = d.sort_tiles <= TT_SCAN_TILES_MAX ? 0 : TT_SUPER_SLOTS * (d.sort_tiles / TT_SUPER_TILES + 1) << TT_SORT_MAX_BITS;
     for (int e = blockIdx.x * TT_SORT_THREADS + threadIdx.x; e < words; e += d.sort_tiles * TT_SORT_THREADS) d.tmp.super[e] = 0;
   } else {
     for (int b = threadIdx.x; b < nbins; b += TT_SORT_THREADS) h[b] = 0;
@@ -1138,12 +1139,13 @@ tt_status ttk_sort_slot1(const TTDev &d, int key_bits, hipStream_t s) {
   return radix_sort(b, 1, tt_ceil_div(d.plan.max_rows, TT_SORT_TILE), key_bits, s, 0);
 }
 
+// The scratch is what the arrays with a place of their own take; batches that fit a fixed scratch depend on it.
 size_t tt_sort_tmp_bytes(int64_t nnz, int64_t max_rows, int64_t max_prefixes) {
   const size_t ntiles = (size_t)tt_ceil_div(nnz, TT_SORT_TILE) + 1;
   size_t ints = 3 * (size_t)nnz + 2 * (size_t)max_rows + 3 * (size_t)max_prefixes +
                 TT_SORT_MAX_PASSES * ((size_t)1 << TT_SORT_MAX_BITS) * ntiles + ((size_t)1 << TT_SORT_MAX_BITS) +
-                4 * ntiles + TT_SUPER_SLOTS * ((size_t)1 << TT_SORT_MAX_BITS) * (ntiles / TT_SUPER_TILES + 1);
-  return (ints + 64 * 14) * sizeof(int32_t);
+                2 * ntiles;
+  return (ints + 64 * 12) * sizeof(int32_t);
 }
 
 TTSortTmp tt_sort_tmp_view(const tt_plan *plan) {
@@ -1168,8 +1170,14 @@ TTSortTmp tt_sort_tmp_view(const tt_plan *plan) {
   t.hist = take(TT_SORT_MAX_PASSES * ((size_t)1 << TT_SORT_MAX_BITS) * ntiles);  // one [tile][bin] array per pass
   t.bin_total = take((size_t)1 << TT_SORT_MAX_BITS);
   t.tile_sums = take(2 * ntiles);
-  t.tile_base = take(2 * ntiles);
-  t.super = take(TT_SUPER_SLOTS * ((size_t)1 << TT_SORT_MAX_BITS) * (ntiles / TT_SUPER_TILES + 1));
+  // Two arrays live in space that is free when they are used.  The tiles' first slots (2 * ntiles entries, at least
+  // 64 are there) are written after the sort, whose ping-pong keys are dead by then.  The group rows lie at the
+  // end of the histograms: a sort of three passes or fewer leaves the last pass's array free, one of
+  // four has digits of 8 bits and fills a quarter of it, and from TT_SCAN_TILES_MAX tiles on the rows take less than
+  // a third.
+  t.tile_base = t.keys_alt;
+  const size_t bins = (size_t)1 << TT_SORT_MAX_BITS, tiles = ntiles - 1, groups = tiles / TT_SUPER_TILES + 1;
+  t.super = tiles > TT_SCAN_TILES_MAX ? t.hist + TT_SORT_MAX_PASSES * bins * ntiles - TT_SUPER_SLOTS * bins * groups : nullptr;
   return t;
 }
 

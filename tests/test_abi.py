@@ -137,3 +137,19 @@ def test_fused_table_shape_and_host_validation_without_gpu():
     for p in parts:
         assert sum(members[t][1][0] for t in p) <= 1023
     assert len(binding.fusion_groups(members, groups=5)) == 5
+
+
+def test_workspace_bytes_stay_what_programs_have_laid_out():
+    """Sizes that callers keep (and that decide which batches the static scratch serves): scratch of the reorder that is
+    used at different times shares its space, so new arrays of it do not make the workspace grow."""
+    from paper_2507_14668_amd import binding
+    lib = binding.load_library()
+    for n, d, r, nnz, want in (
+            ((200, 250, 200), (4, 8, 4), (32, 32), 1, 55296), ((200, 250, 200), (4, 8, 4), (32, 32), 1025, 3057664),
+            ((200, 250, 200), (4, 8, 4), (32, 32), 53594, 152898560), ((200, 250, 200), (4, 8, 4), (32, 32), 335000, 642549504),
+            ((342, 342, 342), (4, 8, 4), (64, 64), 65536, 443848192), ((61, 67, 63), (2, 4, 6), (12, 20), 12000, 16023552),
+            ((1290, 1290, 1290), (2, 3, 4), (5, 6), 70000, 43593984), ((10, 10, 10), (2, 2, 4), (4, 4), 2000000, 128292352)):
+        t = binding.CTable()
+        t.num_rows = n[0] * n[1] * n[2]
+        t.n[:], t.d[:], t.r[:] = n, d, (1,) + r + (1,)
+        assert lib.tt_workspace_bytes(ctypes.byref(t), nnz, nnz) == want, (n, nnz)

@@ -39,3 +39,26 @@ def test_static_scratch_forward_equals_workspace_forward(ora):
     with pytest.raises(tt.TTError) as e:
         tt.tt_emb_bag_forward_static(table, g.to_dev(idx, torch.int64), g.to_dev(off, torch.int64), big)
     assert e.value.status == binding.TT_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("nnz,served", [(53_594, True), (53_595, False)])
+def test_largest_batch_of_the_static_scratch(nnz, served):
+    """The scratch serves 53 594 lookups of a table of ten million rows at D = 128, to the bit, and not one more."""
+    import paper_2507_14668_amd as tt
+    from paper_2507_14668_amd import binding
+    print("case static limit nnz=%d" % nnz, flush=True)
+    n, d, r = (200, 250, 200), (4, 8, 4), (1, 32, 32, 1)
+    g = torch.Generator(device="cuda").manual_seed(4)
+    table = tt.Table(10_000_000, n, d, r, [0.1 * torch.randn(r[k] * n[k] * d[k] * r[k + 1], device="cuda", generator=g)
+                                           for k in range(3)])
+    idx = (10_000_000 ** torch.rand(nnz, device="cuda", dtype=torch.float64, generator=g)).long().clamp(max=9_999_999)
+    off = torch.arange(0, nnz + 1, 2 if nnz % 2 == 0 else 5, device="cuda")
+    out = torch.full((off.numel() - 1, 128), float("nan"), device="cuda")
+    if not served:
+        with pytest.raises(tt.TTError) as e:
+            tt.tt_emb_bag_forward_static(table, idx, off, out)
+        assert e.value.status == binding.TT_ERR_WORKSPACE
+        return
+    tt.tt_emb_bag_forward_static(table, idx, off, out)
+    plan = tt.tt_index_reorder(table, idx, off)
+    assert torch.equal(out, tt.tt_emb_bag_forward(table, plan, idx, off))
