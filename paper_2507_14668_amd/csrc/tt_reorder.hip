@@ -26,11 +26,12 @@ __device__ __forceinline__ void check_offsets(const TTDev &d, int l) {
   if (bad) atomicOr(&d.plan.counts[4], 2);
 }
 
-// A batch without lookups: no sort pass runs that could check the offsets, and the groupings are
-// empty (every range of every segment array is [0, 0)).
+// A table without lookups, alone or in a batch: no tile of it checks the offsets or writes the groupings,
+// which are empty (every range of every segment array is [0, 0)).
 template <bool BATCHED>
 __global__ void k_empty_plan(TTArg<BATCHED> a) {
   const TTDev &d = a.get();
+  if (d.nnz != 0) return;  // uniform
   const int u = blockIdx.x * blockDim.x + threadIdx.x;
   check_offsets(d, u);
   if (u <= d.sh.n3) d.plan.i3_seg[u] = 0;
@@ -1209,14 +1210,14 @@ tt_status ttk_reorder(const TTBatch &b, hipStream_t s) {
   // first kernel: counters, keys, bags, histogram of the first digit or cleared group rows
   const int scan = scan_mode(tiles0, true);
   TT_LAUNCH(k_extract_keys, tiles0 > 0 ? tiles0 : 1, TT_SORT_THREADS, 0, s, b, in_a, bits0, scan);
-  if (tiles0 == 0) {
+  if (any_empty) {
     const long long cover = tt_batch_max(b, [](const TTDev &d) {
       long long m = d.sh.n1 > d.sh.n2 ? d.sh.n1 : d.sh.n2;
       m = (m > d.sh.n3 ? m : (long long)d.sh.n3) + 1;
       return m > d.num_bags + 1 ? m : (long long)d.num_bags + 1; });
     TT_LAUNCH(k_empty_plan, tt_ceil_div(cover, TT_BLOCK), TT_BLOCK, 0, s, b);
-    return tt_launch_status();  // no lookups: the first kernel has left an empty plan
   }
+  if (tiles0 == 0) return tt_launch_status();  // no lookups at all: the plan is complete
   // the first scatter pass also checks the bag offsets (one thread per offset)
   tt_status st = radix_sort(b, 0, tiles0, key_bits, s, tt_ceil_div(bags + 1, TT_SORT_TILE));
   if (st != TT_OK) return st;

@@ -3,11 +3,13 @@
 // single-table results.  Built with AddressSanitizer + UBSan (or MemorySanitizer / ThreadSanitizer,
 // see build.py), so every out-of-bounds, misaligned or racing LDS access of a kernel is reported.
 // usage: harness <mfma | plain | unaligned | wide | keys31 | cfg5like> [planned: 1 | 0] [bags for cfg5like]
+//        harness plans [lookups]   plans only, single and batched, against a host construction
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
 #include <stdint.h>
 #include <math.h>
+#include <algorithm>
 #include <vector>
 #include "tt_emb.h"
 
@@ -71,8 +73,121 @@ struct Res { std::vector<float> out, dg[3], core[3]; };
 
 #define CK(x) do { tt_status st_ = (x); if (st_ != TT_OK) { fprintf(stderr, "FAIL %s -> %d (%s)\n", #x, st_, tt_strerror(st_)); exit(1); } } while (0)
 
+// ---- kind "plans": the plan of long batches -- several sort tiles, groups of tiles above 64 of them, two to four
+// radix passes, wide row factors -- and of batched calls that mix them with short, single-lookup and empty tables, against a
+// stable sort on the host; and on malformed offsets, which have to be reported without an access out of bounds.
+static bool same(const char *what, const int32_t *got, const std::vector<int32_t> &want) {
+  if (want.empty() || memcmp(got, want.data(), want.size() * sizeof(int32_t)) == 0) return true;
+  size_t i = 0;
+  while (got[i] == want[i]) ++i;
+  fprintf(stderr, "FAIL plan array %s: entry %zu of %zu is %d, not %d\n", what, i, want.size(), got[i], want[i]);
+  return false;
+}
+static bool plan_is_right(const Tab &B, const tt_plan &p) {
+  const int n1 = B.t.n[0], n2 = B.t.n[1], n3 = B.t.n[2];
+  const int64_t sentinel = (int64_t)n1 * n2 * n3;
+  auto row = [&](int l) { const int64_t r = B.idx[l]; return r >= 0 && r < B.t.num_rows ? r : sentinel; };
+  std::vector<int32_t> perm(B.nnz), sorted_row, bag, slot, l2r(B.nnz, -1), uniq, row_seg, r2p, pref, pref_seg, bag_of(B.nnz);
+  for (int b = 0; b < B.bags; ++b) for (int64_t l = B.off[b]; l < B.off[b + 1]; ++l) bag_of[l] = b;
+  for (int l = 0; l < B.nnz; ++l) perm[l] = l;
+  std::stable_sort(perm.begin(), perm.end(), [&](int a, int b) { return row(a) < row(b); });
+  int valid = 0;
+  for (int s = 0; s < B.nnz; ++s) {
+    const int64_t r = row(perm[s]);
+    sorted_row.push_back((int32_t)r); bag.push_back(bag_of[perm[s]]);
+    if (r == sentinel) { slot.push_back(-1); continue; }
+    ++valid;
+    if (uniq.empty() || uniq.back() != r) {
+      if (pref.empty() || pref.back() != r / n3) { pref_seg.push_back((int32_t)uniq.size()); pref.push_back((int32_t)(r / n3)); }
+      row_seg.push_back(s); uniq.push_back((int32_t)r); r2p.push_back((int32_t)pref.size() - 1);
+    }
+    slot.push_back((int32_t)uniq.size() - 1);
+    l2r[perm[s]] = slot.back();
+  }
+  row_seg.push_back(valid); pref_seg.push_back((int32_t)uniq.size());
+  auto group = [](const std::vector<int32_t> &keys, int nkeys, std::vector<int32_t> &order, std::vector<int32_t> &seg) {
+    for (size_t i = 0; i < keys.size(); ++i) order.push_back((int32_t)i);
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return keys[a] < keys[b]; });
+    seg.assign(nkeys + 1, 0);
+    for (int k : keys) ++seg[k + 1];
+    for (int k = 0; k < nkeys; ++k) seg[k + 1] += seg[k];
+  };
+  std::vector<int32_t> i1, i2, i3, o1, o2, o3, s1, s2, s3, meta, sorted_i3;
+  for (int u : uniq) i3.push_back(u % n3);
+  for (int q : pref) { i1.push_back(q / n2); i2.push_back(q % n2); }
+  group(i1, n1, o1, s1); group(i2, n2, o2, s2); group(i3, n3, o3, s3);
+  for (int u : o3) sorted_i3.push_back(i3[u]);
+  for (int q : o2) for (int v : {i1[q], pref_seg[q], pref_seg[q + 1] - pref_seg[q], q}) meta.push_back(v);
+  const std::vector<int32_t> counts = {(int32_t)uniq.size(), (int32_t)pref.size(), valid, (int32_t)B.nnz, valid < B.nnz ? 1 : 0};
+  return same("counts", p.counts, counts) && same("sorted_row", p.sorted_row, sorted_row) && same("perm", p.perm, perm) &&
+         same("bag_of_sorted", p.bag_of_sorted, bag) && same("slot_of_sorted", p.slot_of_sorted, slot) && same("lookup2row", p.lookup2row, l2r) &&
+         same("uniq_row", p.uniq_row, uniq) && same("row_seg", p.row_seg, row_seg) && same("row2pref", p.row2pref, r2p) &&
+         same("uniq_pref", p.uniq_pref, pref) && same("pref_seg", p.pref_seg, pref_seg) && same("rows_by_i3", p.rows_by_i3, o3) &&
+         same("i3_of_sorted", p.i3_of_sorted, sorted_i3) && same("i3_seg", p.i3_seg, s3) && same("prefs_by_i2", p.prefs_by_i2, o2) &&
+         same("i2_seg", p.i2_seg, s2) && same("i1_seg", p.i1_seg, s1) && same("pref_meta", p.pref_meta, meta);
+}
+
+static int check_plans(int lookups) {
+  const int d[3] = {1, 1, 1};
+  const int ns[6][3] = {{400, 1000, 1000}, {1290, 1290, 1290}, {5, 7, 9}, {61, 67, 63}, {300, 2, 500}, {30, 20, 10}};
+  const int bags[6] = {lookups / 2, lookups / 2, 2600, 1, 40, lookups / 9};  // (about three lookups a bag, see below)
+  std::vector<Tab> tabs;
+  for (int t = 0; t < 6; ++t) {
+    tabs.push_back(make_tab(ns[t], d, 1, 1, bags[t], t == 4 ? 1 : 4, (int64_t)ns[t][0] * ns[t][1] * ns[t][2] - (t & 1)));
+    Tab &B = tabs[t];
+    if (t < 2) for (size_t i = 0; i < B.idx.size(); i += 2) B.idx[i] = (int64_t)(rnd() % (uint32_t)B.t.num_rows);
+    for (size_t i = 5; i < B.idx.size(); i += 97) B.idx[i] = i % 2 ? -1 : B.t.num_rows;  // invalid lookups
+    if (t == 3) { B.idx.assign(1, 1234); B.off = {0, 1}; }                               // one lookup
+    if (t == 4) { B.idx.clear(); B.off.assign(B.bags + 1, 0); }                          // bags, but no lookup
+    B.nnz = (int64_t)B.idx.size();
+    for (int k = 0; k < 3; ++k) B.t.core[k] = B.core[k].data();
+    fprintf(stderr, "plan table %d: %lld lookups, %lld bags\n", t, (long long)B.nnz, (long long)B.bags);
+  }
+  for (size_t t = 0; t < tabs.size(); ++t) {
+    Tab &B = tabs[t];
+    const size_t wb = tt_workspace_bytes(&B.t, B.nnz, B.bags);
+    void *ws = amalloc(wb);
+    tt_plan plan; memset(&plan, 0, sizeof(plan));
+    CK(tt_index_reorder(&B.t, B.idx.data(), B.off.data(), B.nnz, B.bags, nullptr, ws, wb, &plan, nullptr));
+    if (!plan_is_right(B, plan)) { fprintf(stderr, "FAIL single plan of table %zu\n", t); return 9; }
+    if (B.bags > 3) {
+      std::vector<int64_t> bad = B.off;
+      for (size_t i = 1; i < bad.size(); i += 7) bad[i] = (i % 3 == 0) ? -5 : ((i % 3 == 1) ? B.nnz + 9 : bad[i - 1] - 2);
+      CK(tt_index_reorder(&B.t, B.idx.data(), bad.data(), B.nnz, B.bags, nullptr, ws, wb, &plan, nullptr));
+      if (!(plan.counts[4] & 2)) { fprintf(stderr, "FAIL malformed offsets of table %zu not reported\n", t); return 7; }
+    }
+    free(ws);
+  }
+  // groups of tables in one batched call each: with and without a table above 64 tiles or of wide factors
+  const std::vector<std::vector<int>> groups = {{0, 2, 3, 4, 5}, {1, 4, 2}, {2, 3, 4}, {3, 4}, {4}, {3, 3}};
+  for (const auto &grp : groups) {
+    const int T = (int)grp.size();
+    std::vector<tt_batch_item> items(T);
+    std::vector<tt_plan> plans(T);
+    const size_t db = tt_batch_desc_bytes(T);
+    void *desc = amalloc(db);
+    for (int i = 0; i < T; ++i) {
+      Tab &B = tabs[grp[i]];
+      memset(&items[i], 0, sizeof(tt_batch_item)); memset(&plans[i], 0, sizeof(tt_plan));
+      items[i].table = &B.t; items[i].plan = &plans[i]; items[i].indices = B.idx.data(); items[i].offsets = B.off.data();
+      items[i].nnz = B.nnz; items[i].num_bags = B.bags;
+      items[i].workspace_bytes = tt_workspace_bytes(&B.t, B.nnz, B.bags);
+      items[i].workspace = amalloc(items[i].workspace_bytes);
+    }
+    CK(tt_index_reorder_batched(T, items.data(), desc, db, nullptr));
+    for (int i = 0; i < T; ++i) {
+      if (!plan_is_right(tabs[grp[i]], plans[i])) { fprintf(stderr, "FAIL batched plan of table %d in a call of %d tables\n", grp[i], T); return 9; }
+      free(items[i].workspace);
+    }
+    free(desc);
+  }
+  fprintf(stderr, "plans: all right\n");
+  return 0;
+}
+
 int main(int argc, char **argv) {
   const char *kind = argc > 1 ? argv[1] : "mfma";
+  if (!strcmp(kind, "plans")) return check_plans(argc > 2 ? atoi(argv[2]) : 70000);
   const int planned_only = argc > 2 ? atoi(argv[2]) : -1;
   std::vector<Tab> tabs;
   if (!strcmp(kind, "unaligned")) { g_off = 1; kind = "mfma"; }

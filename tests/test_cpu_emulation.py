@@ -327,3 +327,17 @@ def test_launches_of_tables_with_millions_of_slices(emu):
     for got, ref in ((g1[touched], new[0]), (cores[1].reshape(new[1].shape), new[1]), (cores[2].reshape(new[2].shape), new[2])):
         assert np.abs(got - ref).max() <= 1e-5 * np.abs(ref).max()
     assert np.count_nonzero(g1.any(axis=(1, 2))) == len(touched)
+
+
+@pytest.mark.parametrize("lookups,shuffle", [(9000, None), (9000, "21"), (70000, None)])
+def test_sanitized_plans_of_long_batches(asan_harness, lookups, shuffle):
+    """The plan built by several launches, under AddressSanitizer + UBSan and against a host construction, bit for bit: ten
+    sort tiles and (70 000 lookups) more than 64, where groups of tiles are counted; two to four radix passes; row factors
+    above 1023; malformed offsets; and batched calls that mix such tables with short ones, one lookup and no lookups."""
+    env = dict(os.environ, ASAN_OPTIONS="detect_stack_use_after_return=0:detect_leaks=0", UBSAN_OPTIONS="halt_on_error=1")
+    if shuffle:
+        env["EMU_SHUFFLE"] = shuffle
+    res = subprocess.run([asan_harness, "plans", str(lookups)], capture_output=True, text=True, env=env, timeout=600)
+    text = res.stdout + res.stderr
+    assert res.returncode == 0 and "plans: all right" in text, text[-4000:]
+    assert "ERROR" not in text and "runtime error" not in text, text[-4000:]
