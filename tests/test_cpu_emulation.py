@@ -341,3 +341,27 @@ def test_sanitized_plans_of_long_batches(asan_harness, lookups, shuffle):
     text = res.stdout + res.stderr
     assert res.returncode == 0 and "plans: all right" in text, text[-4000:]
     assert "ERROR" not in text and "runtime error" not in text, text[-4000:]
+
+
+@pytest.mark.parametrize("nnz,bags,n,threads", [
+    (20, 1, (200, 250, 200), 64), (32, 64, (256, 256, 256), 64), (33, 64, (256, 256, 256), 256), (32, 65, (256, 256, 256), 256),
+    (32, 64, (257, 3, 4), 256), (32, 64, (3, 257, 4), 256), (32, 64, (3, 4, 257), 256), (60, 1000, (16000, 3, 2), 256),
+    (256, 300, (7, 9, 11), 256), (257, 300, (7, 9, 11), 512)])
+def test_who_builds_a_short_plan(emu, ora, capfd, monkeypatch, nnz, bags, n, threads):
+    """Only the shortest batches of small tables get their plan from a single wavefront, which walks the bags and the
+    segment starts alone; the plan is the oracle's on both sides of every limit."""
+    rng = np.random.default_rng(nnz + bags)
+    shape, cores, _, _, _ = wl.small_random_problem(3, n=n, d=(1, 2, 2), r=(1, 1, 2, 1))
+    off = np.concatenate([[0], np.sort(rng.integers(0, nnz + 1, bags - 1)), [nnz]]).astype(np.int64)
+    idx = rng.integers(0, shape.num_rows, nnz).astype(np.int64)
+    monkeypatch.setenv("EMU_TRACE", "1")
+    res = _run(emu, shape, cores, idx, off, rng.standard_normal(bags * 4), 0.05)["plan_arrays"]
+    launches = [ln for ln in capfd.readouterr().err.splitlines() if "k_plan_small" in ln]
+    assert len(launches) == 1 and " block %d " % threads in launches[0], launches
+    ref = ora.reorder_plan(shape, idx, off)
+    for key in ("uniq_row", "row_seg", "uniq_pref", "pref_seg", "lookup2row"):
+        assert np.array_equal(res[key], ref[key]), key
+    i3, i2 = np.sort(ref["uniq_row"] % n[2]), np.sort(ref["uniq_pref"] % n[1])
+    assert np.array_equal(res["i3_seg"], np.searchsorted(i3, np.arange(n[2] + 1)))
+    assert np.array_equal(res["i2_seg"], np.searchsorted(i2, np.arange(n[1] + 1)))
+    assert np.array_equal(res["i1_seg"], np.searchsorted(ref["uniq_pref"] // n[1], np.arange(n[0] + 1)))
