@@ -494,8 +494,12 @@ k_seg_whole(TTArg<BATCHED> arg, int blocks_a) {
       Vec<VEC> x[TT_SEG_WHOLE_UNROLL];
 #pragma unroll
       for (int k = 0; k < TT_SEG_WHOLE_UNROLL; ++k) load_pos(pos + k * groups, e, x[k]);
+      // in pairs, then into the running sum: a chain of a quarter of the additions, and of their rounding errors
 #pragma unroll
-      for (int k = 0; k < TT_SEG_WHOLE_UNROLL; ++k) acc.add(x[k]);
+      for (int w = 1; w < TT_SEG_WHOLE_UNROLL; w <<= 1)
+#pragma unroll
+        for (int k = 0; k < TT_SEG_WHOLE_UNROLL; k += 2 * w) x[k].add(x[k + w]);
+      acc.add(x[0]);
     }
     for (; pos < b; pos += groups) {
       Vec<VEC> x;
@@ -507,11 +511,16 @@ k_seg_whole(TTArg<BATCHED> arg, int blocks_a) {
   __syncthreads();
   if (g == 0)
     for (int e = lane * VEC; e < Wp; e += lanes * VEC) {
-      Vec<VEC> acc, x;
-      acc.load(red + e);
-      for (int k = 1; k < groups; ++k) {
-        x.load(red + (size_t)k * Wp + e);
-        acc.add(x);
+      // the groups (a power of two of them, four or more), four in pairs and then into the running sum
+      Vec<VEC> acc, x[4];
+      acc.zero();
+      for (int k = 0; k < groups; k += 4) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[j].load(red + (size_t)(k + j) * Wp + e);
+        x[0].add(x[1]);
+        x[2].add(x[3]);
+        x[0].add(x[2]);
+        acc.add(x[0]);
       }
       float *dst = out + seg_out_index(s, e0 + e, out_inner, nseg);
       if (sv.fused) acc.store_sgd(dst, sv.lr); else acc.store(dst);
@@ -692,13 +701,30 @@ k_bwd_prefix_wave(TTArg<BATCHED> a) {
     for (int o0 = tid / TT_WAVE * width; o0 < sh.S1; o0 += threads / parts) {  // uniform per wavefront
       const int o = o0 + (lane & (width - 1)), oc = o < sh.S1 ? o : 0, j1 = oc / sh.R1, r1 = oc - j1 * sh.R1;
       const float *hp = h + j1 * sh.S2, *gp = g2s + r1 * S2p;
-      float acc[4] = {0.f, 0.f, 0.f, 0.f};
-      int c = c0;
-      for (; c + 8 <= c1; c += 8)
+      // chains of four products, added in pairs and in blocks of 64: no more rounding than one product per lane and
+      // a sum over the lanes
+      float sum = 0.f;
+      for (int cb = c0; cb < c1; cb += 64) {
+        const int end = cb + 64 < c1 ? cb + 64 : c1;
+        float block = 0.f;
+        int c = cb;
+        for (; c + 16 <= end; c += 16) {
+          float acc[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int k = 0; k < 8; ++k) acc[k & 3] = fmaf(hp[c + k], gp[c + k], acc[k & 3]);
-      for (; c < c1; ++c) acc[0] = fmaf(hp[c], gp[c], acc[0]);
-      float sum = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+          for (int k = 0; k < 16; ++k) acc[k >> 2] = fmaf(hp[c + k], gp[c + k], acc[k >> 2]);
+          block += (acc[0] + acc[1]) + (acc[2] + acc[3]);
+        }
+        if (c + 8 <= end) {
+          float acc[2] = {0.f, 0.f};
+#pragma unroll
+          for (int k = 0; k < 8; ++k) acc[k >> 2] = fmaf(hp[c + k], gp[c + k], acc[k >> 2]);
+          block += acc[0] + acc[1];
+          c += 8;
+        }
+        float tail = 0.f;
+        for (; c < end; ++c) tail = fmaf(hp[c], gp[c], tail);
+        sum += block + tail;
+      }
       for (int w = width; w < TT_WAVE; w <<= 1) sum += __shfl_xor(sum, w, TT_WAVE);
       if (part == 0 && o < sh.S1) t1buf[(size_t)q * sh.S1 + o] = sum;
     }

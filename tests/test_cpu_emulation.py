@@ -365,3 +365,50 @@ def test_who_builds_a_short_plan(emu, ora, capfd, monkeypatch, nnz, bags, n, thr
     assert np.array_equal(res["i3_seg"], np.searchsorted(i3, np.arange(n[2] + 1)))
     assert np.array_equal(res["i2_seg"], np.searchsorted(i2, np.arange(n[1] + 1)))
     assert np.array_equal(res["i1_seg"], np.searchsorted(ref["uniq_pref"] // n[1], np.arange(n[0] + 1)))
+
+
+def _exact_grads(shape, cores, idx, off, grad):
+    """Core gradients of the batch in 64 bits, in the layout of the cores."""
+    n, d, (_, r1, r2, _) = shape.n, shape.d, shape.r
+    a, b, c = (x.astype(np.float64) for x in cores)
+    a, b, c = a.reshape(n[0], d[0], r1), b.reshape(r1, n[1], d[1], r2), c.reshape(r2, n[2], d[2])
+    u, inv = np.unique(idx, return_inverse=True)
+    g = np.zeros((len(u),) + tuple(d))
+    np.add.at(g, inv, grad.astype(np.float64).reshape((-1,) + tuple(d))[np.repeat(np.arange(len(off) - 1), np.diff(off))])
+    i1, i2, i3 = u // n[2] // n[1], u // n[2] % n[1], u % n[2]
+    au, bu, cu = a[i1], b[:, i2].transpose(1, 0, 2, 3), c[:, i3].transpose(1, 0, 2)
+    p12 = np.einsum("uar,urbs->uabs", au, bu, optimize=True)
+    h = np.einsum("uabc,usc->uabs", g, cu, optimize=True)
+    dg = [np.zeros_like(a), np.zeros((n[1], r1, d[1], r2)), np.zeros((n[2], r2, d[2]))]
+    np.add.at(dg[0], i1, np.einsum("uabs,urbs->uar", h, bu, optimize=True))
+    np.add.at(dg[1], i2, np.einsum("uar,uabs->urbs", au, h, optimize=True))
+    np.add.at(dg[2], i3, np.einsum("uabs,uabc->usc", p12, g, optimize=True))
+    return dg[0].ravel(), dg[1].transpose(1, 0, 2, 3).ravel(), dg[2].transpose(1, 0, 2).ravel()
+
+
+# largest geometric mean over eight batches of the relative error (2-norm) of the three core gradients: what the kernels
+# with a workgroup per prefix and two-stage sums show on the same batches (emulated sums are the same on every machine)
+@pytest.mark.parametrize("n,d,r,bags,limits", [
+    ((20, 21, 20), (2, 4, 6), (1, 12, 20, 1), 700, (1.127e-7, 1.315e-7, 1.163e-7)),  # one sum's vectors are fours, the other's are not
+    ((20, 20, 20), (2, 4, 6), (1, 8, 8, 1), 700, (1.157e-7, 1.308e-7, 1.100e-7)),
+    ((30, 30, 30), (4, 4, 4), (1, 16, 16, 1), 700, (1.295e-7, 1.909e-7, 1.534e-7)),
+    ((10, 10, 10), (2, 2, 4), (1, 4, 4, 1), 400, (1.152e-7, 1.069e-7, 1.543e-7)),
+])
+def test_order_of_additions_costs_no_precision(emu, n, d, r, bags, limits):
+    """Core gradients of the plain kernels against 64 bits: the order in which products, rows and slices are added may
+    change, their error may not grow."""
+    lib, binding = emu
+    logs = np.zeros(3)
+    for seed in range(8):
+        shape, cores, idx, off, grad = wl.small_random_problem(900 + seed, n=n, d=d, r=r, num_bags=bags, max_len=5, sigma=0.3)
+        table = _table(binding, shape, cores)
+        ws, plan = _aligned(lib.tt_workspace_bytes(ctypes.byref(table), len(idx), bags)), binding.CPlan()
+        assert lib.tt_index_reorder(ctypes.byref(table), _ptr(idx), _ptr(off), len(idx), bags, None, _ptr(ws), ws.nbytes,
+                                    ctypes.byref(plan), None) == 0
+        dg = [_aligned(c.nbytes).view(np.float32) for c in cores]
+        arr = (ctypes.c_void_p * 3)(*[g.ctypes.data for g in dg])
+        grad = np.ascontiguousarray(grad, np.float32)
+        assert lib.tt_emb_bag_backward(ctypes.byref(table), ctypes.byref(plan), _ptr(idx), _ptr(off), len(idx), bags, _ptr(grad), arr, None) == 0
+        logs += [np.log(np.linalg.norm(got - ref) / np.linalg.norm(ref)) for got, ref in zip(dg, _exact_grads(shape, cores, idx, off, grad))]
+    errors = np.exp(logs / 8)
+    assert np.all(errors <= np.array(limits)), (errors, limits)
