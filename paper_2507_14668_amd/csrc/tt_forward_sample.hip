@@ -11,6 +11,8 @@
 //                separate bag-sum launch; the price is one read of a whole prefix product per
 //                (bag, prefix) group instead of one read of a finished row per lookup.
 //   k_bag_chains_4x8x4  the same for the matrix-core shapes, products in registers, several wavefronts per long bag
+#include <type_traits>
+
 #include "tt_internal.h"
 
 namespace {
@@ -180,6 +182,10 @@ k_bag_chains_4x8x4(TTArg<BATCHED> a) {
   const long long o0 = offsets[b], o1 = offsets[b + 1], nnz = d.nnz;
   const long long lo = o0 < 0 ? 0 : (o0 > nnz ? nnz : o0), hi = o1 < lo ? lo : (o1 > nnz ? nnz : o1);
   const size_t rstep = (size_t)sh.n3;  // float4 between consecutive r2 of core 2
+  if (WPB == 1 && lo == hi) {  // uniform: an empty bag has no sums to form
+    for (int o = lane; o < D; o += TT_WAVE) d.out[(size_t)b * D + o] = 0.f;
+    return;
+  }
   for (long long base = lo; base < hi; base += WPB * TT_WAVE) {  // uniform
     // prefix slot and i3 of the round's lookups, lane + 64*j (an invalid lookup has no row slot and takes no part)
     int q[WPB], i3[WPB];
@@ -289,15 +295,32 @@ k_bag_chains_4x8x4(TTArg<BATCHED> a) {
       }
     }
   }
-  // over r2: the L lanes of a row; one of them leaves the row's four columns
+  // Over r2, the L lanes of a row: in every step a lane hands on the half of its values that the other lane keeps
+  // (14 or 30 exchanges; every value at every lane would be 48 or 128), and ends with two columns of the row.
+  float v[4 * NK];
 #pragma unroll
   for (int k = 0; k < NK; ++k)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < 4; ++j) v[4 * k + j] = acc[k][j];
+  int first = 0;
+  auto halve = [&](auto lanes_apart, auto values) __attribute__((always_inline)) {
+    constexpr int o = decltype(lanes_apart)::value, half = decltype(values)::value / 2;
+    const bool up = (r4 & o) != 0;
 #pragma unroll
-      for (int o = 1; o < L; o <<= 1) acc[k][j] += __shfl_xor(acc[k][j], o, TT_WAVE);
-      if (r4 == (k & (L - 1))) s_out[wave][4 * (jj0 + ROWS * k) + j] = acc[k][j];
+    for (int i = 0; i < half; ++i) {
+      const float give = up ? v[i] : v[i + half], keep = up ? v[i + half] : v[i];
+      v[i] = keep + __shfl_xor(give, o, TT_WAVE);
     }
+    first += up ? half : 0;
+  };
+  halve(std::integral_constant<int, 1>{}, std::integral_constant<int, 4 * NK>{});
+  halve(std::integral_constant<int, 2>{}, std::integral_constant<int, 2 * NK>{});
+  halve(std::integral_constant<int, 4>{}, std::integral_constant<int, NK>{});
+  if constexpr (L == 16) halve(std::integral_constant<int, 8>{}, std::integral_constant<int, NK / 2>{});
+  static_assert(4 * NK / L == 2, "two columns per lane");
+  float *mine = s_out[wave] + 4 * (jj0 + ROWS * (first >> 2)) + (first & 3);
+  mine[0] = v[0];
+  mine[1] = v[1];
   if constexpr (WPB == 1) {
     tt_wave_lds_order();
     for (int o = lane; o < D; o += TT_WAVE) d.out[(size_t)b * D + o] = s_out[wave][o];

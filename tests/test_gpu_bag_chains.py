@@ -32,3 +32,11 @@ def test_bag_and_group_edges(ora, rank, lens):
         ref = ora.forward(shape, cores, np.where(idx < 0, shape.num_rows, idx), off)
         g.assert_close_rows(out.cpu().numpy(), ref, g.FWD_RTOL, shape.dim, "forward(sample)")
         assert torch.equal(tt.tt_emb_bag_forward_sample(table, plan, d_off), out)
+
+
+@pytest.mark.parametrize("rank", [32, 64])
+@pytest.mark.parametrize("lens", [(1,) * 37, (0,) * 9, (0, 1, 0, 0, 2, 0, 1), (0, 0, 63, 0, 1, 0), (0, 500, 0)])
+def test_short_and_empty_bags(ora, rank, lens):
+    """One-lookup bags, and empty ones, which leave before the sums over the lanes are formed: alone in the batch, between
+    others in a workgroup, and as a bag of a workgroup's own."""
+    test_bag_and_group_edges(ora, rank, lens)
