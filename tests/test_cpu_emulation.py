@@ -412,3 +412,32 @@ def test_order_of_additions_costs_no_precision(emu, n, d, r, bags, limits):
         logs += [np.log(np.linalg.norm(got - ref) / np.linalg.norm(ref)) for got, ref in zip(dg, _exact_grads(shape, cores, idx, off, grad))]
     errors = np.exp(logs / 8)
     assert np.all(errors <= np.array(limits)), (errors, limits)
+
+
+@pytest.mark.parametrize("case", ["one_hot", "zero_or_one", "empty_runs", "one_bag"])
+def test_emulated_bag_search_of_long_batches(emu, ora, case):
+    """The bag of every lookup in batches of several sort tiles: one lookup per bag (no search), bags of zero or one, runs
+    of thousands of empty bags (beyond the window of offsets that a tile stages), one bag over all tiles."""
+    lib, binding = emu
+    rng = np.random.default_rng(6)
+    lens = {"one_hot": np.ones(2500, np.int64), "zero_or_one": rng.integers(0, 2, 5200), "empty_runs": np.zeros(9000, np.int64),
+            "one_bag": np.array([0, 3100, 0])}[case]
+    if case == "empty_runs":
+        lens[[0, 3000, 3001, 8999]] = (700, 900, 500, 1300)
+    shape, cores, _, _, _ = wl.small_random_problem(42, n=(5, 4, 6), d=(1, 1, 2), r=(1, 1, 1, 1))
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    idx = rng.integers(-1, shape.num_rows + 1, int(off[-1])).astype(np.int64)
+    table, plan = _table(binding, shape, cores), binding.CPlan()
+    ws = _aligned(lib.tt_workspace_bytes(ctypes.byref(table), len(idx), len(lens)))
+    assert len(idx) > 2048
+    assert lib.tt_index_reorder(ctypes.byref(table), _ptr(idx), _ptr(off), len(idx), len(lens), None, _ptr(ws), ws.nbytes,
+                                ctypes.byref(plan), None) == 0
+    ref = ora.reorder_plan(shape, idx, off)
+
+    def ints(name, count):
+        o = getattr(plan, name) - ws.ctypes.data
+        return ws[o:o + 4 * count].view(np.int32)
+    assert int(ints("counts", 5)[4]) == 1  # lookups outside the table, valid offsets
+    for key in ("bag_of_sorted", "perm", "sorted_row"):
+        assert np.array_equal(ints(key, ref["num_valid"]), ref[key]), key
+    assert np.array_equal(ints("lookup2row", len(idx)), ref["lookup2row"])

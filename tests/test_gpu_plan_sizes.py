@@ -32,3 +32,55 @@ def test_plan_at_tile_edges(ora, nnz):
     none = np.full(nnz, -1, np.int64)  # not one valid lookup
     plan = tt.tt_index_reorder(g.gpu_table(shape, cores), torch.from_numpy(none).cuda(), torch.from_numpy(off).cuda())
     g.assert_plan_equals_oracle(ora, shape, plan, none, off)
+
+
+@pytest.mark.parametrize("nnz,n", [
+    (1, (1, 1, 500)), (32, (256, 256, 256)), (33, (256, 256, 256)), (32, (257, 9, 11)), (2048, (1, 1, 500)), (2049, (1, 1, 500)),
+    (2048, (1023, 1023, 1023)), (2049, (1023, 1023, 1023)),                 # 30 bits: three passes, the largest narrow factors
+    (2048, (7, 1024, 11)), (2048, (7, 9, 1024)), (5000, (20000, 9, 11)),    # a factor above 1023: separate grouping sorts
+    (64 * 1024, (400, 1000, 1000)), (64 * 1024 + 1, (400, 1000, 1000)), (64 * 1024 + 1, (400, 1500, 700)),
+    (64 * 1024 + 1, (1290, 1290, 1290)),                                    # four passes with groups of tiles
+    (1024 * 1024, (400, 1000, 1000)), (1024 * 1024 + 1, (400, 1000, 1000)), (1024 * 1024, (700, 30, 1500))])
+def test_plan_of_wide_keys_at_tile_edges(ora, nnz, n):
+    """The limits again with tables of up to 31 key bits (two to four radix passes, so every row of the counts is used)
+    and with row factors on both sides of one digit."""
+    import gpu_util as g
+    import paper_2507_14668_amd as tt
+    print("case plan nnz=%d n=%s" % (nnz, n), flush=True)
+    rng = np.random.default_rng(nnz + n[0])
+    rows = n[0] * n[1] * n[2]
+    shape = wl.TableShape(rows - nnz % 2, n, (1, 1, 1), (1, 1, 1, 1))
+    table = g.gpu_table(shape, [np.zeros(shape.core_size(k), np.float32) for k in range(3)])
+    idx = np.where(rng.random(nnz) < 0.5, rng.integers(0, shape.num_rows, nnz),
+                   np.minimum((shape.num_rows ** rng.random(nnz)).astype(np.int64) - 1, shape.num_rows - 1))
+    idx[rng.random(nnz) < 0.01] = -1
+    off = np.concatenate([[0], np.sort(rng.integers(0, nnz + 1, max(1, nnz // 3) - 1)), [nnz]]).astype(np.int64)
+    plan = tt.tt_index_reorder(table, torch.from_numpy(idx).cuda(), torch.from_numpy(off).cuda())
+    g.assert_plan_equals_oracle(ora, shape, plan, idx, off)
+
+
+@pytest.mark.parametrize("bags", [60, 1500, 60_000])
+def test_malformed_offsets_are_reported_at_every_length(bags):
+    """Negative, decreasing and too large bag offsets in a plan of one workgroup, of a few sort tiles and of more than 64:
+    reported by the plan, and neither the plan nor its readers leave the buffers (the next valid batch is right)."""
+    import gpu_util as g
+    import paper_2507_14668_amd as tt
+    print("case malformed offsets bags=%d" % bags, flush=True)
+    rng = np.random.default_rng(bags)
+    shape, cores, idx, off, grad = wl.small_random_problem(77, n=(7, 9, 11), d=(2, 2, 2), r=(1, 2, 2, 1), num_bags=bags, max_len=4)
+    bad = off.copy()
+    bad[1:-1:7] = -5
+    bad[3:-1:7] = len(idx) + 9
+    bad[5:-1:7] = bad[4:-2:7] - 2
+    table = g.gpu_table(shape, cores)
+    d_idx, d_off, d_bad, d_grad = (torch.from_numpy(x).cuda() for x in (idx, off, bad, grad))
+    good = tt.tt_index_reorder(table, d_idx, d_off)
+    want = tt.tt_emb_bag_forward(table, good, d_idx, d_off)
+    plan = tt.tt_index_reorder(table, d_idx, d_bad)
+    assert tt.tt_plan_status(plan) == tt.binding.TT_ERR_INDEX_RANGE and tt.tt_plan_status(good) == 0
+    tt.tt_emb_bag_forward(table, plan, d_idx, d_bad)
+    tt.tt_emb_bag_forward_sample(table, plan, d_bad)
+    tt.tt_emb_bag_backward(table, plan, d_idx, d_bad, d_grad)
+    again = tt.tt_index_reorder(table, d_idx, d_off, workspace=plan.workspace)
+    assert tt.tt_plan_status(again) == 0
+    assert torch.equal(tt.tt_emb_bag_forward(table, again, d_idx, d_off), want)
