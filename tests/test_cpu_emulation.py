@@ -441,3 +441,34 @@ def test_emulated_bag_search_of_long_batches(emu, ora, case):
     for key in ("bag_of_sorted", "perm", "sorted_row"):
         assert np.array_equal(ints(key, ref["num_valid"]), ref[key]), key
     assert np.array_equal(ints("lookup2row", len(idx)), ref["lookup2row"])
+
+
+def _backward_with_trace(emu, capfd, monkeypatch, n, d, r, nnz, seed=5):
+    """(launch lines, gradients, exact gradients) of one planned backward of `nnz` one-lookup bags."""
+    lib, binding = emu
+    rng = np.random.default_rng(seed)
+    shape, cores, _, _, _ = wl.small_random_problem(seed, n=n, d=d, r=r, num_bags=1, max_len=1, sigma=0.3)
+    idx, off = rng.integers(0, shape.num_rows, nnz).astype(np.int64), np.arange(nnz + 1, dtype=np.int64)
+    grad = rng.standard_normal(nnz * shape.dim).astype(np.float32)
+    table, plan = _table(binding, shape, cores), binding.CPlan()
+    ws = _aligned(lib.tt_workspace_bytes(ctypes.byref(table), nnz, nnz))
+    assert lib.tt_index_reorder(ctypes.byref(table), _ptr(idx), _ptr(off), nnz, nnz, None, _ptr(ws), ws.nbytes, ctypes.byref(plan), None) == 0
+    dg = [_aligned(c.nbytes).view(np.float32) for c in cores]
+    arr = (ctypes.c_void_p * 3)(*[x.ctypes.data for x in dg])
+    monkeypatch.setenv("EMU_TRACE", "1")
+    capfd.readouterr()
+    assert lib.tt_emb_bag_backward(ctypes.byref(table), ctypes.byref(plan), _ptr(idx), _ptr(off), nnz, nnz, _ptr(grad), arr, None) == 0
+    return capfd.readouterr().err.splitlines(), dg, _exact_grads(shape, cores, idx, off, grad)
+
+
+@pytest.mark.parametrize("n,d,r,nnz,whole", [
+    ((50, 50, 2), (2, 2, 3), (1, 16, 5, 1), 1025, True), ((50, 50, 2), (2, 2, 3), (1, 16, 5, 1), 1026, False),  # rows per i3
+    ((1, 2500, 9), (2, 2, 3), (1, 16, 5, 1), 2048, True), ((1, 2500, 9), (2, 2, 3), (1, 16, 5, 1), 2049, False),  # prefixes per i1
+    ((50, 50, 2), (2, 2, 4), (1, 16, 5, 1), 1026, True),  # vectors of one width
+])
+def test_who_sums_the_core2_and_core0_gradients(emu, capfd, monkeypatch, n, d, r, nnz, whole):
+    """Long segments of sums of mixed vector width take the two-stage sums; gradients against 64 bits on both sides."""
+    launches, dg, ref = _backward_with_trace(emu, capfd, monkeypatch, n, d, r, nnz)
+    assert any("k_seg_whole" in ln for ln in launches) == whole, launches
+    for a, b in zip(dg, ref):  # sums of up to 2049 terms in 32 bits
+        assert np.linalg.norm(a - b) <= 2e-6 * np.linalg.norm(b)
