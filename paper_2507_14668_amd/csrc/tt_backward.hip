@@ -530,11 +530,12 @@ k_seg_whole(TTArg<BATCHED> arg, int blocks_a) {
 #ifndef TT_SEG_WHOLE_MAX_AVG
 #define TT_SEG_WHOLE_MAX_AVG 4096  // positions per segment (capacity / segments) up to which whole segments are used
 #endif
-// ... where the two sums' vectors differ in width: a whole segment then goes four bytes a lane, and long ones cost more
-// than the four launches they save.  Whole backward calls, whole segments / two-stage sums, d = 2x4x6, ranks 12, 20: rows
-// per i3 500: 43.0 / 50.8 us, 1000: 61.6 / 56.1, 4000: 171 / 108; prefixes per i1 1000: 49.1 / 57.0, 2000: 78.1 / 78.4,
-// 3000: 98.8 / 90.0.
-#define TT_SEG_MIXED_MAX_ROWS 512    // rows per i3
+// ... where the two sums' vectors differ in width: both then go four bytes a lane, and long segments cost more than the
+// launches they save.  Whole backward calls, whole segments / two-stage sums, d = 2x4x6, ranks 12, 20, rows per i3: 4 i3,
+// 500 43.0 / 50.8 us, 1000 61.6 / 56.1, 4000 171 / 108; ratios at 700 rows 0.95 (4 i3), 0.92 (30, 60), 1.00 (100), 1.14 (200
+// i3: at 500 1.04, at 300 0.98); three other shapes cross between 700 and 1100 rows.  Prefixes per i1: 1000 49.1 / 57.0,
+// 2000 78.1 / 78.4, 3000 98.8 / 90.0.
+static long long seg_mixed_max_rows(long long max_rows) { return max_rows <= 65536 ? 768 : 512; }  // rows per i3
 #define TT_SEG_MIXED_MAX_PREFS 2048  // prefixes per i1
 
 // The core-2 and core-0 reductions are independent.  With segments of moderate length they take one
@@ -543,16 +544,16 @@ k_seg_whole(TTArg<BATCHED> arg, int blocks_a) {
 tt_status seg_sum_dg3_dg1(const TTBatch &b, hipStream_t s) {
   const SegParams p3 = seg_params(b, SEG_DG3, 0), p1 = seg_params(b, SEG_DG1, 0);
   bool whole = true;
-  const long long most3 = p3.vec == p1.vec ? TT_SEG_WHOLE_MAX_AVG : TT_SEG_MIXED_MAX_ROWS;
-  const long long most1 = p3.vec == p1.vec ? TT_SEG_WHOLE_MAX_AVG : TT_SEG_MIXED_MAX_PREFS;
+  const bool mixed = p3.vec != p1.vec;
   for (int t = 0; t < b.T && whole; ++t) {
     const TTDev &d = b.host[t];
-    whole = d.plan.max_rows / d.sh.n3 <= most3 && d.plan.max_prefixes * d.strips / d.sh.n1 <= most1;
+    whole = d.plan.max_rows / d.sh.n3 <= (mixed ? seg_mixed_max_rows(d.plan.max_rows) : TT_SEG_WHOLE_MAX_AVG) &&
+            d.plan.max_prefixes * d.strips / d.sh.n1 <= (mixed ? TT_SEG_MIXED_MAX_PREFS : TT_SEG_WHOLE_MAX_AVG);
   }
   if (whole) {
     // one launch has one vector width (d3 = 6 beside ranks of four, 12 k lookups: 26 us in the four launches of
     // two separate two-stage sums, 7 us here)
-    const int vec = p3.vec == p1.vec ? p3.vec : 1, W3 = p3.W;
+    const int vec = mixed ? 1 : p3.vec, W3 = p3.W;
     const WholeSplit w1 = whole_split(p1.W, vec, TT_SEG_WHOLE_PARTS);
     const long long blocks3 = tt_batch_max(b, [=](const TTDev &d) {
       return (long long)d.sh.n3 * whole_split(W3, vec, whole_want3(d.sh.n3)).parts; });
