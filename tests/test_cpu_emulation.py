@@ -454,11 +454,18 @@ def _backward_with_trace(emu, capfd, monkeypatch, n, d, r, nnz, seed=5):
     ws = _aligned(lib.tt_workspace_bytes(ctypes.byref(table), nnz, nnz))
     assert lib.tt_index_reorder(ctypes.byref(table), _ptr(idx), _ptr(off), nnz, nnz, None, _ptr(ws), ws.nbytes, ctypes.byref(plan), None) == 0
     dg = [_aligned(c.nbytes).view(np.float32) for c in cores]
+    for x in dg:
+        x.fill(np.nan)
     arr = (ctypes.c_void_p * 3)(*[x.ctypes.data for x in dg])
     monkeypatch.setenv("EMU_TRACE", "1")
     capfd.readouterr()
     assert lib.tt_emb_bag_backward(ctypes.byref(table), ctypes.byref(plan), _ptr(idx), _ptr(off), nnz, nnz, _ptr(grad), arr, None) == 0
-    return capfd.readouterr().err.splitlines(), dg, _exact_grads(shape, cores, idx, off, grad)
+    launches, ref, old = capfd.readouterr().err.splitlines(), _exact_grads(shape, cores, idx, off, grad), [c.copy() for c in cores]
+    assert lib.tt_emb_bag_backward_sgd(ctypes.byref(table), ctypes.byref(plan), _ptr(idx), _ptr(off), nnz, nnz, _ptr(grad),
+                                       ctypes.c_float(0.5), None) == 0
+    for new, before, x in zip(cores, old, dg):  # the fused update takes the same routes
+        assert np.array_equal(new, (before - 0.5 * x.astype(np.float64)).astype(np.float32))
+    return launches, dg, ref
 
 
 @pytest.mark.parametrize("n,d,r,nnz,whole", [
@@ -486,3 +493,21 @@ def test_who_works_on_a_prefix(emu, capfd, monkeypatch, n, d, r, nnz, wave):
     assert any("k_bwd_prefix_wave" in ln for ln in launches) == wave and any("k_bwd_prefix" in ln for ln in launches), launches
     for a, b in zip(dg, ref):
         assert np.linalg.norm(a - b) <= 2e-6 * np.linalg.norm(b)
+
+
+@pytest.mark.parametrize("n,d,r,nnz,workgroups", [
+    ((2, 20000, 2), (1, 2, 1), (1, 3, 3, 1), 60, 60 + 59),        # 341 slices cleared by a workgroup, then one per prefix
+    ((3, 2000, 2), (2, 11, 2), (1, 17, 24, 1), 30, 30 * 10 + 286),  # five column tiles, two of r1; seven slices at a time
+    ((2, 16446, 2), (1, 2, 1), (1, 3, 3, 1), 62, 62 + 49), ((2, 16445, 2), (1, 2, 1), (1, 3, 3, 1), 62, 16445),  # the rule's edge
+    ((3, 2000, 2), (2, 11, 2), (1, 17, 24, 1), 0, 286),           # no lookup at all
+])
+def test_core1_gradient_of_mostly_untouched_slices(emu, capfd, monkeypatch, n, d, r, nnz, workgroups):
+    """Tables with thousands of i2 that no lookup touched: their slices are cleared by workgroups that take many at a time,
+    and only the prefixes' i2 get workgroups of their own; the gradient is written whole and right, also in the
+    fused update, which leaves the untouched slices as they are."""
+    launches, dg, ref = _backward_with_trace(emu, capfd, monkeypatch, n, d, r, nnz)
+    grids = [int(ln.split("grid (")[1].split(",")[0]) for ln in launches if "k_bwd_dg2" in ln]
+    assert grids == [workgroups], launches
+    for a, b in zip(dg, ref):  # (uninitialised memory went in: every element is written)
+        assert np.all(np.isfinite(a)) and np.linalg.norm(a - b) <= 2e-6 * np.linalg.norm(b)
+        assert np.array_equal(a == 0, b == 0)
