@@ -325,7 +325,7 @@ k_extract_keys(TTArg<BATCHED> a, int in_a, int bits, int scan) {
 #pragma unroll
     for (int i = 0; i < TT_SORT_ITEMS; ++i) searching |= hi[i] - lo[i] > 1;
   }
-  while (searching) {  // one halving step for all four per round
+  while (searching) {  // one halving step for each of the thread's lookups per round
     searching = false;
 #pragma unroll
     for (int i = 0; i < TT_SORT_ITEMS; ++i) {
