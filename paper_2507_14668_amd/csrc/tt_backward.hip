@@ -681,17 +681,14 @@ struct PrefixWaveLds {
     floats = (g2s + sh.R1 * (sh.S2 | 1) + 3) & ~3;
   }
 };
-// The rule: four wavefronts' operands fit the 64 KB of LDS a launch gets without asking (larger shapes have enough work
-// per prefix for a workgroup), and there are enough chains to fill the chip, or rows to share, or T1 -- d1*R1 sums over a
-// whole wavefront in the workgroup's kernel -- is much of a prefix's work.  A single small prefix is done sooner by a
-// workgroup.  Whole backward calls with one row a prefix, wavefront / workgroup: d1*R1 = 24 (ranks 12, 20) 64 prefixes
-// 25.0 / 22.0 us, 512 26.5 / 25.0, 1536 30.3 / 29.7, 2048 33.1 / 37.6; d1*R1 = 8 (rank 4) 64 24.0 / 21.3, 2048 29.6 / 31.7;
-// d1*R1 = 32 (4x4x4, rank 8) 64 22.1 / 21.7, 256 23.4 / 24.3, 2048 29.9 / 37.8; d1*R1 = 64 (rank 16) 64 23.6 / 25.6, 2048
-// 33.0 / 46.6.  With two rows a prefix the wavefront is ahead of or beside the workgroup (rank 4, 400 prefixes: 0.92 of the
-// time, with six rows 0.84).
-static inline bool prefix_wave_serves(const TTShape &sh, long long max_prefixes, long long max_rows) {
-  if (PW_WAVES * (PrefixWaveLds(sh).floats + 1) * (long long)sizeof(float) > 65536) return false;
-  return sh.S1 >= 32 || max_prefixes >= 2048 || max_rows >= 2 * max_prefixes;
+// The rule: four wavefronts' operands fit the 64 KB of LDS a launch gets without asking.  Larger shapes have
+// enough work per prefix for a workgroup.  Not how many prefixes there are: a few hundred of one row each are done sooner
+// by a workgroup each (whole backward calls, wavefront / workgroup, ranks 12, 20: 64 prefixes 25.0 / 22.0 us, 1536 30.3 / 29.7,
+// 2048 33.1 / 37.6; rank 4: 64 24.0 / 21.3, 2048 29.6 / 31.7), but skewed batches have few prefixes with many rows, which a
+// workgroup takes one after the other, and the host knows lookups only (Zipf exponent 1.1, passes with reorder, forward and
+// update: 363 lookups at rank 8, d = 2x2x4 65.9 / 82.3; 2736, d = 3x5x4 110.7 / 133.1).
+static inline bool prefix_wave_fits(const TTShape &sh) {
+  return PW_WAVES * (PrefixWaveLds(sh).floats + 1) * (long long)sizeof(float) <= 65536;
 }
 
 template <bool BATCHED>
@@ -1173,7 +1170,7 @@ tt_status ttk_backward_plan(const TTBatch &b, hipStream_t s) {
   const long long max_pref = tt_batch_max(b, [](const TTDev &d) { return (long long)d.plan.max_prefixes; });
   if (mfma) {
     if ((st = ttk_backward_mfma(b, s)) != TT_OK) return st;
-  } else if (max_pref > 0 && prefix_wave_serves(sh, max_pref, tt_batch_max(b, [](const TTDev &d) { return (long long)d.plan.max_rows; }))) {
+  } else if (max_pref > 0 && prefix_wave_fits(sh)) {
     const long long wgs = (max_pref + PW_WAVES - 1) / PW_WAVES, blocks = wgs < 4096 ? wgs : 4096;
     TTProfScope prof(&b.host[0].plan, TT_KERNEL_BWD_CONTRACT, s);
     TT_LAUNCH(k_bwd_prefix_wave, blocks, TT_WAVE * PW_WAVES, sizeof(float) * PW_WAVES * PrefixWaveLds(sh).floats, s, b);

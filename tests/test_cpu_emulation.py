@@ -482,20 +482,6 @@ def test_who_sums_the_core2_and_core0_gradients(emu, capfd, monkeypatch, n, d, r
         assert np.linalg.norm(a - b) <= 2e-6 * np.linalg.norm(b)
 
 
-@pytest.mark.parametrize("n,d,r,nnz,wave", [
-    ((64, 64, 8), (2, 2, 2), (1, 4, 4, 1), 2047, False), ((64, 64, 8), (2, 2, 2), (1, 4, 4, 1), 2048, True),  # d1*R1 = 8
-    ((10, 10, 4), (2, 2, 2), (1, 4, 4, 1), 199, False), ((10, 10, 4), (2, 2, 2), (1, 4, 4, 1), 200, True),    # two rows a prefix
-    ((30, 30, 3), (1, 2, 2), (1, 31, 4, 1), 50, False), ((30, 30, 3), (4, 2, 2), (1, 8, 4, 1), 50, True),     # d1*R1 = 31, 32
-    ((30, 30, 3), (4, 4, 4), (1, 32, 32, 1), 300, False),                                                     # too large for a wavefront
-])
-def test_who_works_on_a_prefix(emu, capfd, monkeypatch, n, d, r, nnz, wave):
-    """A wavefront per prefix where there are enough of them, or rows to share; gradients against 64 bits on both sides."""
-    launches, dg, ref = _backward_with_trace(emu, capfd, monkeypatch, n, d, r, nnz)
-    assert any("k_bwd_prefix_wave" in ln for ln in launches) == wave and any("k_bwd_prefix" in ln for ln in launches), launches
-    for a, b in zip(dg, ref):
-        assert np.linalg.norm(a - b) <= 2e-6 * np.linalg.norm(b)
-
-
 @pytest.mark.parametrize("n,d,r,nnz,workgroups", [
     ((2, 20000, 2), (1, 2, 1), (1, 3, 3, 1), 60, 60 + 59),        # 341 slices cleared by a workgroup, then one per prefix
     ((3, 2000, 2), (2, 11, 2), (1, 17, 24, 1), 30, 30 * 10 + 286),  # five column tiles, two of r1; seven slices at a time
