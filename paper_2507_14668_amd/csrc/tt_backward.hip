@@ -531,12 +531,12 @@ k_seg_whole(TTArg<BATCHED> arg, int blocks_a) {
 #define TT_SEG_WHOLE_MAX_AVG 4096  // positions per segment (capacity / segments) up to which whole segments are used
 #endif
 // ... where the two sums' vectors differ in width: both then go four bytes a lane, and long segments cost more than the
-// launches they save.  Whole backward calls, whole segments / two-stage sums, d = 2x4x6, ranks 12, 20, rows per i3: 4 i3,
-// 500 43.0 / 50.8 us, 1000 61.6 / 56.1, 4000 171 / 108; ratios at 700 rows 0.95 (4 i3), 0.92 (30, 60), 1.00 (100), 1.14 (200
-// i3: at 500 1.04, at 300 0.98), at 1000 rows 1.10 (4 i3), 0.99 (30), 0.95 (60); three other shapes: 0.97 to 1.02 at 700 rows
-// of 4 to 16 i3, 0.94 to 1.04 at 1000 rows of 60 i3.  Prefixes per i1: 1000 49.1 / 57.0,
-// 2000 78.1 / 78.4, 3000 98.8 / 90.0.
-static long long seg_mixed_max_rows(long long max_rows, int n3) { return max_rows > 65536 ? 512 : (n3 < 48 ? 768 : 1024); }  // rows per i3
+// launches they save.  Whole backward calls, whole segments / two-stage sums, d = 2x4x6, ranks 12, 20.  Every lookup a row of
+// its own: 4 i3, rows per i3 500 43.0 / 50.8 us, 1000 61.6 / 56.1, 4000 171 / 108; 30 i3, 1000 0.99 of the two-stage time, 2500
+// 1.14; prefixes per i1 1000 49.1 / 57.0, 2000 78.1 / 78.4, 3000 98.8 / 90.0.  Skewed lookups (Zipf exponents 1.05 and 1.2, near-
+// cubic tables of 8 k to 1 M rows) have two to five times fewer rows than the capacity that the rule knows: 938 to 2500 per i3
+// by capacity are 210 to 620, 50.5 / 62.5 to 119 / 129 us.
+static long long seg_mixed_max_rows(int n3) { return n3 < 16 ? 1024 : 3072; }  // rows per i3
 #define TT_SEG_MIXED_MAX_PREFS 2048  // prefixes per i1
 // ... and where the slices are many: empty ones cost a workgroup per column part (four bytes a lane make many parts).  500
 // lookups, d = 4x2x3, ranks 16, 5: 1000 i1 (8000 workgroups) 44.4 / 46.2, 1500 50.9 / 46.8, 100000 1200 / 102; d = 2x4x6,
@@ -552,7 +552,7 @@ tt_status seg_sum_dg3_dg1(const TTBatch &b, hipStream_t s) {
   const bool mixed = p3.vec != p1.vec;
   for (int t = 0; t < b.T && whole; ++t) {
     const TTDev &d = b.host[t];
-    whole = d.plan.max_rows / d.sh.n3 <= (mixed ? seg_mixed_max_rows(d.plan.max_rows, d.sh.n3) : TT_SEG_WHOLE_MAX_AVG) &&
+    whole = d.plan.max_rows / d.sh.n3 <= (mixed ? seg_mixed_max_rows(d.sh.n3) : TT_SEG_WHOLE_MAX_AVG) &&
             d.plan.max_prefixes * d.strips / d.sh.n1 <= (mixed ? TT_SEG_MIXED_MAX_PREFS : TT_SEG_WHOLE_MAX_AVG);
   }
   if (whole) {

@@ -469,10 +469,11 @@ def _backward_with_trace(emu, capfd, monkeypatch, n, d, r, nnz, seed=5):
 
 
 @pytest.mark.parametrize("n,d,r,nnz,whole", [
-    ((50, 50, 2), (2, 2, 3), (1, 16, 5, 1), 1537, True), ((50, 50, 2), (2, 2, 3), (1, 16, 5, 1), 1538, False),  # rows per i3
+    ((50, 50, 2), (2, 2, 3), (1, 16, 5, 1), 2049, True), ((50, 50, 2), (2, 2, 3), (1, 16, 5, 1), 2050, False),  # rows per i3
+    ((34, 33, 16), (2, 2, 3), (1, 16, 5, 1), 16416, True),
     ((1, 2500, 9), (2, 2, 3), (1, 16, 5, 1), 2048, True), ((1, 2500, 9), (2, 2, 3), (1, 16, 5, 1), 2049, False),  # prefixes per i1
     ((2047, 2, 2), (2, 2, 3), (1, 16, 5, 1), 60, True), ((2048, 2, 2), (2, 2, 3), (1, 16, 5, 1), 60, False),  # slices
-    ((50, 50, 2), (2, 2, 4), (1, 16, 5, 1), 1538, True), ((2048, 2, 2), (2, 2, 4), (1, 16, 5, 1), 60, True),  # vectors of one width
+    ((50, 50, 2), (2, 2, 4), (1, 16, 5, 1), 2050, True), ((2048, 2, 2), (2, 2, 4), (1, 16, 5, 1), 60, True),  # vectors of one width
 ])
 def test_who_sums_the_core2_and_core0_gradients(emu, capfd, monkeypatch, n, d, r, nnz, whole):
     """Long segments of sums of mixed vector width take the two-stage sums; gradients against 64 bits on both sides."""
