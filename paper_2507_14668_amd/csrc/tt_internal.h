@@ -28,7 +28,9 @@ struct TTShape {
 
 #define TT_WAVE 64
 #define TT_BLOCK 256
+#ifndef TT_MAX_WORKGROUPS
 #define TT_MAX_WORKGROUPS ((1ll << 32) / TT_BLOCK - 1)  // of TT_BLOCK threads: a launch has fewer than 2^32 threads
+#endif
 
 // ---- radix sort geometry ----------------------------------------------------------------
 #define TT_SORT_THREADS 512

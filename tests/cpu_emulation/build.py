@@ -66,11 +66,12 @@ def _compile(sources, flags, out_dir, tag):
         return list(pool.map(one, sources)), base
 
 
-def build_shared(out_dir: str) -> str:
+def build_shared(out_dir: str, tag: str = "so", defines=()) -> str:
+    """The library; with `defines` ("-DNAME=value") and a tag of its own, a variant of it."""
     os.makedirs(out_dir, exist_ok=True)
-    srcs = _generate(os.path.join(out_dir, "gen_so")) + [os.path.join(HERE, "emu_runtime.cpp")]
-    objs, base = _compile(srcs, ["-O2", "-fPIC"], out_dir, "so")
-    lib = os.path.join(out_dir, "libtt_emb_emu.so")
+    srcs = _generate(os.path.join(out_dir, "gen_" + tag)) + [os.path.join(HERE, "emu_runtime.cpp")]
+    objs, base = _compile(srcs, ["-O2", "-fPIC"] + list(defines), out_dir, tag)
+    lib = os.path.join(out_dir, "libtt_emb_emu%s.so" % ("" if tag == "so" else "_" + tag))
     subprocess.run(base + ["-O2", "-fPIC", "-shared"] + objs + ["-o", lib], check=True)
     return lib
 

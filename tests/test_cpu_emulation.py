@@ -27,8 +27,12 @@ pytestmark = pytest.mark.skipif(not emu_build.available(), reason="host clang++ 
 
 @pytest.fixture(scope="module")
 def emu():
+    return _load(emu_build.build_shared(BUILD_DIR))
+
+
+def _load(path):
     from paper_2507_14668_amd import binding
-    lib = ctypes.CDLL(emu_build.build_shared(BUILD_DIR))
+    lib = ctypes.CDLL(path)
     vp, i64, f32 = ctypes.c_void_p, ctypes.c_int64, ctypes.c_float
     lib.tt_workspace_bytes.restype = ctypes.c_size_t
     lib.tt_workspace_bytes.argtypes = [vp, i64, i64]
@@ -499,3 +503,15 @@ def test_core1_gradient_of_mostly_untouched_slices(emu, capfd, monkeypatch, n, d
     for a, b in zip(dg, ref):  # (uninitialised memory went in: every element is written)
         assert np.all(np.isfinite(a)) and np.linalg.norm(a - b) <= 2e-6 * np.linalg.norm(b)
         assert np.array_equal(a == 0, b == 0)
+
+
+@pytest.mark.parametrize("nnz,grids", [(62, [11808, 4637]), (100, [100 + 49])])
+def test_core1_gradient_in_several_launches(capfd, monkeypatch, nnz, grids):
+    """More i2 than a launch takes workgroups for, in a build whose launches take 20000: the first launch ends at its limit
+    and the second goes on there; with a few lookups more untouched slices the other route takes one."""
+    small = _load(emu_build.build_shared(BUILD_DIR, "few_wgs", ["-DTT_MAX_WORKGROUPS=20000"]))
+    n = (2, 16445 if nnz == 62 else 16484, 2)
+    launches, dg, ref = _backward_with_trace(small, capfd, monkeypatch, n, (1, 2, 1), (1, 3, 3, 1), nnz)
+    assert [int(ln.split("grid (")[1].split(",")[0]) for ln in launches if "k_bwd_dg2" in ln] == grids
+    for a, b in zip(dg, ref):
+        assert np.all(np.isfinite(a)) and np.linalg.norm(a - b) <= 2e-6 * np.linalg.norm(b)

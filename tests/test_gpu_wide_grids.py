@@ -8,7 +8,7 @@ pytestmark = pytest.mark.gpu
 
 
 def test_core1_gradient_of_many_slices():
-    """8.4 million i2 with two column tiles each: 16.8 million workgroups of the core-1 reduction."""
+    """8.4 million i2 with two column tiles each: a workgroup for each of them would be 16.8 million."""
     import gpu_util as g
     import paper_2507_14668_amd as tt
     n, d, r = (1, 8_400_000, 1), (2, 5, 2), (1, 1, 13, 1)
