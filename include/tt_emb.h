@@ -256,7 +256,7 @@ tt_status tt_emb_bag_forward_bf16(const tt_table *table, const void *bf16_cores,
  * Forward for callers that cannot allocate device memory or hand over a workspace: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  One call = index reorder +
  * planned forward (the result is bitwise that of tt_index_reorder followed by tt_emb_bag_forward
- * with the plan), with the plan's workspace in a static device array of TT_STATIC_SCRATCH_BYTES
+ * with the plan; short batches get it without a plan), with the plan's workspace in a static device array of TT_STATIC_SCRATCH_BYTES
  * that the library's code object holds on every GPU it runs on until the process ends.  The call
  * allocates and frees nothing.
  *   indices, offsets, out  DEVICE, as in tt_emb_bag_forward; no remap.

@@ -482,6 +482,7 @@ tt_status tt_emb_bag_forward_static(const tt_table *table, const int64_t *indice
   TTDev d;
   fill_dev(&d, sh, table, &plan, indices, offsets, nnz, num_bags, nullptr, out, nullptr, nullptr, 0.f, false);
   const TTBatch b = {1, &d, nullptr};
+  if (ttk_forward_direct_serves(d)) return ttk_forward_direct(b, (hipStream_t)stream);
   const tt_status st = ttk_reorder(b, (hipStream_t)stream);
   return st != TT_OK ? st : ttk_forward_plan(b, (hipStream_t)stream);
 }

@@ -236,6 +236,123 @@ k_fwd_naive(TTArg<BATCHED> a) {
   }
 }
 
+// Few lookups of a matrix-core shape (d = 4x8x4, ranks R, R), without a plan.  A lane has one column (j2, r2) of the core-1 slices
+// and forms P12[j1][j2][r2] = sum_r1 G1[i1][j1][r1] G2[r1][i2][j2][r2]; the wavefront then forms the lookup's 16 columns
+// (j1, j3) of each of its j2.  Every sum runs in the order of the planned kernels (the matrix cores add one product after the
+// other) and the rows are added as k_bag_sum adds them, so the result is theirs to the bit.
+// BAGS: a workgroup has a bag and 64 columns, its wavefronts take the bag's lookups in turn and the sum is formed here: one
+// launch.  Otherwise a wavefront has one lookup and 64 columns, the row goes to rowbuf and k_bag_sum follows.
+// Latency bound: offsets, index, slices are three dependent round trips; a wavefront requests the next lookup's slices
+// before it multiplies the current one's.  A repeated prefix is multiplied again, which limits the number of lookups.
+constexpr int DIRECT_WAVES = 8;
+template <bool BATCHED, int R, bool BAGS>
+__global__ void __launch_bounds__(TT_WAVE * DIRECT_WAVES)
+k_fwd_direct(TTArg<BATCHED> a) {
+  const TTDev &d = a.get();
+  const TTShape &sh = d.sh;
+  constexpr int S2 = 8 * R, GROUPS = S2 / TT_WAVE, JW = TT_WAVE / R, NV = 16 * JW;  // NV: columns (j2, j1, j3) of a row here
+  static_assert(TT_WAVE % R == 0, "a wavefront holds whole j2");
+  const float *__restrict__ g1 = d.g[0], *__restrict__ g2 = d.g[1], *__restrict__ g3 = d.g[2];
+  const int64_t *__restrict__ indices = d.indices, *__restrict__ offsets = d.offsets;
+  __shared__ __align__(16) float s_p[DIRECT_WAVES][4][TT_WAVE], s_w[DIRECT_WAVES][4][R];  // products [j1][column], core-2 slice [j3][r2]
+  __shared__ float s_row[BAGS ? TT_DIRECT_BAG_LOOKUPS : 1][NV];
+  const int b = (int)blockIdx.x / GROUPS, grp = (int)blockIdx.x - b * GROUPS;  // bag, or eight lookups
+  const int lane = threadIdx.x & (TT_WAVE - 1), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / TT_WAVE);
+  const int c = grp * TT_WAVE + lane, r2 = lane & (R - 1);
+  int l0 = b * DIRECT_WAVES, l1 = l0 + DIRECT_WAVES < d.nnz ? l0 + DIRECT_WAVES : d.nnz;
+  if constexpr (BAGS) {
+    // offsets are clamped to [0, nnz] so that a malformed CSR array cannot index out of bounds (nnz <= TT_DIRECT_BAG_LOOKUPS)
+    const long long o0 = offsets[b], o1 = offsets[b + 1], nnz = d.nnz;
+    l0 = o0 < 0 ? 0 : (o0 > nnz ? (int)nnz : (int)o0);
+    l1 = o1 < l0 ? l0 : (o1 > nnz ? (int)nnz : (int)o1);
+  }
+  const size_t step = (size_t)sh.n2 * S2;
+  // the wavefront's lookups, one per lane: l0 + wave, l0 + wave + 8, ... (at most 64 of them)
+  const int mine = l0 + wave + DIRECT_WAVES * lane;
+  const long long at = mine < l1 ? indices[mine] : -1;
+  const int row = at >= 0 && at < sh.num_rows ? (int)at : -1;
+  unsigned long long left = __ballot(mine < l1);
+  struct Slices { float v[R]; float4 w; int i1, k; };  // this lane's column of core 1, its row of core 2
+  auto load = [&](Slices &x) __attribute__((always_inline)) {  // the next lookup (k: of the wavefront)
+    x.k = __ffsll(left) - 1;
+    left &= left - 1;
+    const int r = __builtin_amdgcn_readlane(row, x.k), rc = r < 0 ? 0 : r;  // an invalid lookup reads row 0
+    const int p = tt_div(rc, sh.mul3, sh.sh3), i1 = tt_div(p, sh.mul2, sh.sh2), i2 = p - i1 * sh.n2, i3 = rc - p * sh.n3;
+    const float *col = g2 + (size_t)i2 * S2 + c;
+#pragma unroll
+    for (int r1 = 0; r1 < R; ++r1) x.v[r1] = col[(size_t)r1 * step];
+    x.w = *reinterpret_cast<const float4 *>(g3 + ((size_t)r2 * sh.n3 + i3) * 4);
+    x.i1 = r < 0 ? -1 : i1;
+  };
+  auto finish = [&](const Slices &x) __attribute__((always_inline)) {
+    const float *__restrict__ u = g1 + (size_t)(x.i1 < 0 ? 0 : x.i1) * (4 * R);
+    float p[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int r1 = 0; r1 < R; ++r1)
+#pragma unroll
+      for (int j1 = 0; j1 < 4; ++j1) p[j1] = fmaf(u[j1 * R + r1], x.v[r1], p[j1]);
+#pragma unroll
+    for (int j1 = 0; j1 < 4; ++j1) s_p[wave][j1][lane] = p[j1];
+    if (lane < R) { s_w[wave][0][lane] = x.w.x; s_w[wave][1][lane] = x.w.y; s_w[wave][2][lane] = x.w.z; s_w[wave][3][lane] = x.w.w; }
+    tt_wave_lds_order();
+    if (lane < NV) {
+      const float4 *pp = reinterpret_cast<const float4 *>(&s_p[wave][(lane >> 2) & 3][(lane >> 4) * R]),
+                   *ww = reinterpret_cast<const float4 *>(s_w[wave][lane & 3]);
+      float acc = 0.f;
+#pragma unroll
+      for (int q = 0; q < R / 4; ++q) {
+        const float4 y = pp[q], z = ww[q];
+        acc = fmaf(z.x, y.x, acc); acc = fmaf(z.y, y.y, acc); acc = fmaf(z.z, y.z, acc); acc = fmaf(z.w, y.w, acc);
+      }
+      if constexpr (BAGS) {
+        s_row[wave + DIRECT_WAVES * x.k][lane] = x.i1 < 0 ? 0.f : acc;  // an invalid lookup adds zeros
+      } else if (x.i1 >= 0) {
+        const int j2 = grp * JW + (lane >> 4), j1 = (lane >> 2) & 3, j3 = lane & 3;
+        d.plan.rowbuf[(size_t)(l0 + wave) * sh.D + (j1 * 8 + j2) * 4 + j3] = acc;
+      }
+    }
+    tt_wave_lds_order();  // the next lookup overwrites s_p and s_w
+  };
+  if constexpr (!BAGS) {
+    if (left == 0) return;  // uniform per wavefront
+    Slices x;
+    load(x);
+    if (grp == 0 && lane == 0) d.plan.lookup2row[l0 + wave] = x.i1 < 0 ? -1 : l0 + wave;
+    finish(x);
+    return;
+  }
+  if (left != 0) {  // uniform per wavefront
+    Slices xa, xb;
+    load(xa);
+    while (true) {  // written out twice so that both sets of slices stay in registers
+      bool more = left != 0;
+      if (more) load(xb);
+      finish(xa);
+      if (!more) break;
+      more = left != 0;
+      if (more) load(xa);
+      finish(xb);
+      if (!more) break;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < NV) {
+    float tot = 0.f;
+    const int len = l1 - l0;
+    for (int base = 0; base < len; base += TT_BAG_BLOCK) {
+      const int stop = base + TT_BAG_BLOCK < len ? base + TT_BAG_BLOCK : len;
+      float sum = 0.f;
+      int l = base;
+      for (; l + 4 <= stop; l += 4)
+        sum += (s_row[l][threadIdx.x] + s_row[l + 1][threadIdx.x]) + (s_row[l + 2][threadIdx.x] + s_row[l + 3][threadIdx.x]);
+      for (; l < stop; ++l) sum += s_row[l][threadIdx.x];
+      tot += sum;
+    }
+    const int j2 = grp * JW + (int)threadIdx.x / 16, j1 = (threadIdx.x >> 2) & 3, j3 = threadIdx.x & 3;
+    d.out[(size_t)b * sh.D + (j1 * 8 + j2) * 4 + j3] = tot;
+  }
+}
+
 size_t fwd_lds_bytes(const TTShape &sh, int rows_per_iter) {
   return sizeof(float) * ((size_t)sh.S1 + (size_t)sh.d1 * sh.d2 * sh.R2p +
                           (size_t)rows_per_iter * sh.S3);
@@ -288,4 +405,33 @@ tt_status ttk_forward_naive(const TTBatch &b, hipStream_t s) {
   const long long blocks = max_bags < 65536 ? max_bags : 65536;
   TT_LAUNCH(k_fwd_naive, blocks, TT_BLOCK, fwd_lds_bytes(b.host[0].sh, 1), s, b);
   return tt_launch_status();
+}
+
+// A plan is a chain of launches (one of 8 to 20 us up to TT_SMALL_MAX_LOOKUPS, nine of 40 us and more above), and what it saves, the
+// repeated rows and prefixes, is less than that in a short batch.  Whole calls, reorder + forward / this, in us; rows
+// spread over the table / log-uniform / all the same:
+//   ranks 32   20 lookups in one bag 18.4 / 5.5     2048 37.5 / 10.7, 35.5 / 10.4, 28.3 / 10.3     16384 75 / 43, 68 / 42, 55 / 38
+//   ranks 64   20 lookups in one bag 26.4 / 8.6     2048 50.6 / 26.8, 45.2 / 25.7, 33.1 / 20.2     8192 102 / 86, 80 / 77, 64 / 58
+//   (ranks 64, 12000: 118 / 120, 83 / 108, 65 / 83, hence the limits)
+// One launch up to TT_DIRECT_BAG_LOOKUPS: 64 lookups in one bag take it 13.2 (ranks 32) and 22.4, the two launches 13.2 and 14.3;
+// in 64 bags 4.9 and 6.8, 7.4 and 8.2.
+bool ttk_forward_direct_serves(const TTDev &d) {
+  // (rowbuf has a row per lookup unless the table itself has fewer)
+  return d.mfma && d.nnz <= (d.sh.R1 == 32 ? TT_DIRECT_MAX_LOOKUPS_32 : TT_DIRECT_MAX_LOOKUPS_64) && d.num_bags <= TT_SMALL_MAX_BAGS &&
+         (d.nnz <= TT_DIRECT_BAG_LOOKUPS || d.plan.max_rows == d.nnz);
+}
+
+tt_status ttk_forward_direct(const TTBatch &b, hipStream_t s) {
+  const TTDev &d = b.host[0];
+  if (d.num_bags == 0) return TT_OK;
+  const int groups = d.sh.S2 / TT_WAVE, nt = TT_WAVE * DIRECT_WAVES;
+  if (d.nnz <= TT_DIRECT_BAG_LOOKUPS) {
+    if (d.sh.R1 == 32) TT_LAUNCH_T2(k_fwd_direct, 32, true, d.num_bags * groups, nt, 0, s, b);
+    else TT_LAUNCH_T2(k_fwd_direct, 64, true, d.num_bags * groups, nt, 0, s, b);
+    return tt_launch_status();
+  }
+  const int wgs = tt_ceil_div(d.nnz, DIRECT_WAVES) * groups;
+  if (d.sh.R1 == 32) TT_LAUNCH_T2(k_fwd_direct, 32, false, wgs, nt, 0, s, b);
+  else TT_LAUNCH_T2(k_fwd_direct, 64, false, wgs, nt, 0, s, b);
+  return ttk_bag_sum(b, s);
 }

@@ -192,6 +192,12 @@ tt_status ttk_index_graph_edges(const int64_t *indices, const int64_t *offsets, 
                                 void *workspace, long long max_pairs, int32_t *eu, int32_t *ev, int32_t *ew,
                                 int32_t *counts_out, hipStream_t s);
 tt_status ttk_forward_plan(const TTBatch &b, hipStream_t s);
+// The bag sums of a short batch without a plan, for calls that hand out none (rowbuf and lookup2row of the scratch are used).
+#define TT_DIRECT_BAG_LOOKUPS 32       // up to this many lookups in one launch, a workgroup per bag
+#define TT_DIRECT_MAX_LOOKUPS_32 16384 // ... and up to this many in two, a wavefront per lookup and 64 columns (ranks 32)
+#define TT_DIRECT_MAX_LOOKUPS_64 8192  // (ranks 64)
+bool ttk_forward_direct_serves(const TTDev &d);
+tt_status ttk_forward_direct(const TTBatch &b, hipStream_t s);
 bool ttk_forward_mfma_supported(const TTShape &sh);
 tt_status ttk_forward_mfma(const TTBatch &b, hipStream_t s);
 // number of strips (16 values of r2, all j2) a core-1 slice is cut into by the backward matrix-core

@@ -1,0 +1,51 @@
+"""The plan-free forward of short batches (emulated kernels) against the oracle and against reorder + planned forward: one and two
+launches, empty bags, invalid lookups, offsets that are no CSR array, a table with fewer rows than the batch has lookups."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import tt_workloads as wl
+from test_cpu_emulation import BUILD_DIR, _aligned, _load, _ptr, _table, emu_build
+
+pytestmark = pytest.mark.skipif(not emu_build.available(), reason="host clang++ of the ROCm toolchain not found")
+
+
+@pytest.fixture(scope="module")
+def emu():
+    lib, binding = _load(emu_build.build_shared(BUILD_DIR))
+    vp, i64 = ctypes.c_void_p, ctypes.c_int64
+    lib.tt_emb_bag_forward_static.argtypes = [vp, vp, vp, i64, i64, vp, vp]
+    return lib, binding
+
+
+@pytest.mark.parametrize("r,n,lens,spoil", [
+    (32, (5, 3, 7), (20,), ""), (64, (5, 3, 7), (0, 7, 0, 13), ""), (32, (5, 3, 7), (9, 0, 30, 8), ""),
+    (64, (5, 3, 7), (3, 31), "indices"), (32, (5, 3, 7), (4, 20, 3), "indices"), (32, (5, 3, 7), (6, 10, 6, 4), "offsets"),
+    (32, (5, 3, 7), (16, 10, 16, 14), "offsets"), (64, (2, 3, 2), (25, 15), "")])
+def test_direct_forward_matches_oracle_and_plan(emu, ora, r, n, lens, spoil):
+    import gpu_util as g
+    lib, binding = emu
+    shape, cores, _, _, _ = wl.small_random_problem(7, n=n, d=(4, 8, 4), r=(1, r, r, 1), sigma=0.2)
+    rng = np.random.default_rng(len(lens) + r)
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    nnz, nb = int(off[-1]), len(lens)
+    idx = rng.integers(0, shape.num_rows, nnz).astype(np.int64)
+    if spoil == "indices":
+        idx[[1, 5, nnz - 1]] = (-1, shape.num_rows, 2 ** 40)
+    if spoil == "offsets":
+        off[1], off[3] = nnz + 5, -2
+    cores = [np.ascontiguousarray(_aligned(c.nbytes).view(np.float32)) for c in cores]
+    for c in cores:
+        c[:] = 0.3 * rng.standard_normal(c.size)
+    table = _table(binding, shape, cores)
+    out = np.full((nb, shape.dim), np.nan, np.float32)
+    assert lib.tt_emb_bag_forward_static(ctypes.byref(table), _ptr(idx), _ptr(off), nnz, nb, _ptr(out), None) == 0
+    ws, plan = _aligned(lib.tt_workspace_bytes(ctypes.byref(table), nnz, nb)), binding.CPlan()
+    assert lib.tt_index_reorder(ctypes.byref(table), _ptr(idx), _ptr(off), nnz, nb, None, _ptr(ws), ws.nbytes, ctypes.byref(plan), None) == 0
+    ref = np.full_like(out, np.nan)
+    assert lib.tt_emb_bag_forward(ctypes.byref(table), ctypes.byref(plan), _ptr(idx), _ptr(off), nnz, nb, _ptr(ref), None) == 0
+    # (the host compiler may contract the emulated products and sums differently in the two kernels: bits are compared on the GPU)
+    np.testing.assert_allclose(out, ref, rtol=0, atol=2e-6 * np.abs(ref).max())
+    if not spoil:
+        g.assert_close_rows(out, ora.forward(shape, cores, idx, off), g.FWD_RTOL, shape.dim, "direct forward")

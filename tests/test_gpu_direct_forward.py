@@ -1,0 +1,75 @@
+"""Short batches of the allocation-free forward are summed without a plan (one launch up to 32 lookups, two up to 16384 or
+8192): bit for bit the result of tt_index_reorder + tt_emb_bag_forward, on both sides of every limit, with invalid lookups, empty
+and malformed bags, repeated rows, and replayed from a graph."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _table(tt, r, rows=None, n=(60, 50, 40)):
+    g = torch.Generator(device="cuda").manual_seed(r)
+    d, rr = (4, 8, 4), (1, r, r, 1)
+    cores = [0.2 * torch.randn(rr[k] * n[k] * d[k] * rr[k + 1], device="cuda", generator=g) for k in range(3)]
+    return tt.Table(rows or n[0] * n[1] * n[2] - 7, n, d, rr, cores)
+
+
+def _batch(rows, nnz, bags, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    idx = (rows ** torch.rand(nnz, device="cuda", dtype=torch.float64, generator=g)).long().clamp(max=rows - 1)
+    if nnz > 8:  # invalid lookups among the others
+        idx[nnz // 3], idx[nnz // 2], idx[-1] = -1, rows, 2 ** 40
+    cut = torch.sort(torch.randint(0, nnz + 1, (bags - 1,), device="cuda", generator=g)).values
+    ends = torch.tensor([nnz], device="cuda")
+    return idx, torch.cat([torch.zeros_like(ends), cut, ends])
+
+
+@pytest.mark.parametrize("r,nnz,bags", [
+    (r, nnz, bags) for r, top in ((32, 16384), (64, 8192))
+    for nnz, bags in ((0, 3), (1, 1), (9, 9), (31, 2), (32, 1), (32, 90), (33, 1), (33, 5), (64, 1), (257, 100), (2049, 300),
+                      (top, 2000), (top + 1, 2000))])
+def test_same_bits_as_with_a_plan(r, nnz, bags):
+    import paper_2507_14668_amd as tt
+    print("case direct r=%d nnz=%d bags=%d" % (r, nnz, bags), flush=True)
+    table = _table(tt, r)
+    idx, off = _batch(table.num_rows, nnz, bags, nnz + bags)
+    out = torch.full((bags, 128), float("nan"), device="cuda")
+    tt.tt_emb_bag_forward_static(table, idx, off, out)
+    plan = tt.tt_index_reorder(table, idx, off)
+    assert torch.equal(out, tt.tt_emb_bag_forward(table, plan, idx, off))
+
+
+@pytest.mark.parametrize("nnz", [20, 200])
+def test_malformed_offsets_and_a_table_smaller_than_the_batch(nnz):
+    import paper_2507_14668_amd as tt
+    print("case direct malformed nnz=%d" % nnz, flush=True)
+    table = _table(tt, 32)
+    idx, off = _batch(table.num_rows, nnz, 6, 5)
+    off[2], off[4] = nnz + 9, -3  # not monotone, outside of the batch
+    small = _table(tt, 64, rows=17, n=(2, 3, 3))
+    sidx = torch.randint(0, 17, (nnz,), device="cuda")
+    for t, i, o in ((table, idx, off), (small, sidx, torch.tensor([0, 5, nnz], device="cuda"))):
+        out = torch.full((o.numel() - 1, 128), float("nan"), device="cuda")
+        tt.tt_emb_bag_forward_static(t, i, o, out)
+        plan = tt.tt_index_reorder(t, i, o)
+        assert torch.equal(out, tt.tt_emb_bag_forward(t, plan, i, o))
+
+
+def test_replayed_from_a_graph():
+    import paper_2507_14668_amd as tt
+    print("case direct graph", flush=True)
+    table = _table(tt, 32)
+    for nnz, bags in ((20, 2), (700, 90)):
+        idx, off = _batch(table.num_rows, nnz, bags, 1)
+        out = torch.zeros(bags, 128, device="cuda")
+        tt.tt_emb_bag_forward_static(table, idx, off, out)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            tt.tt_emb_bag_forward_static(table, idx, off, out, stream=torch.cuda.current_stream())
+        for turn in range(3):
+            idx.copy_(_batch(table.num_rows, nnz, bags, turn)[0])
+            out.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            plan = tt.tt_index_reorder(table, idx, off)
+            assert torch.equal(out, tt.tt_emb_bag_forward(table, plan, idx, off))
