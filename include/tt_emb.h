@@ -253,6 +253,19 @@ tt_status tt_emb_bag_forward_bf16(const tt_table *table, const void *bf16_cores,
                                   void *stream);
 
 /*
+ * The same bag sums without a plan, in one launch and without scratch: every lookup multiplies its own
+ * chain, so repeated rows and prefixes are computed again.  Same shapes, same alignment of bf16_cores and
+ * same tolerance as tt_emb_bag_forward_bf16; invalid indices are skipped and malformed offsets clamped, and
+ * there is no plan that would report them.  tt_forward_bf16_direct_pays says (1 / 0, from the
+ * sizes alone) whether this is the faster way for a batch whose plan serves nothing else; 0 on invalid
+ * arguments.
+ */
+int tt_forward_bf16_direct_pays(const tt_table *table, int64_t nnz, int64_t num_bags);
+tt_status tt_emb_bag_forward_bf16_direct(const tt_table *table, const void *bf16_cores, const int64_t *indices,
+                                         const int64_t *offsets, int64_t nnz, int64_t num_bags, float *out,
+                                         void *stream);
+
+/*
  * Forward for callers that cannot allocate device memory or hand over a workspace: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  One call = index reorder +
  * planned forward (the result is bitwise that of tt_index_reorder followed by tt_emb_bag_forward

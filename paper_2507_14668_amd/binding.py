@@ -26,6 +26,7 @@ TT_ERR_UNAVAILABLE = -6
 EXPORTS = ("tt_workspace_bytes", "tt_index_reorder", "tt_emb_bag_forward", "tt_emb_bag_backward",
            "tt_core_sgd_update", "tt_emb_bag_backward_sgd", "tt_emb_bag_forward_static", "tt_reuse_buffer_bytes", "tt_emb_bag_forward_sample",
            "tt_bf16_cores_bytes", "tt_cores_to_bf16", "tt_emb_bag_forward_bf16",
+           "tt_forward_bf16_direct_pays", "tt_emb_bag_forward_bf16_direct",
            "tt_index_graph_workspace_bytes", "tt_index_graph_edges", "tt_fuse_shape", "tt_fuse_lookups", "tt_fuse_lookups_starts", "tt_plan_status", "tt_strerror", "tt_prof_create", "tt_prof_destroy",
            "tt_prof_collect", "tt_kernel_name", "tt_batch_desc_bytes", "tt_index_reorder_batched",
            "tt_emb_bag_forward_batched", "tt_emb_bag_backward_batched", "tt_core_sgd_update_batched")
@@ -111,6 +112,10 @@ def load_library():
         lib.tt_bf16_cores_bytes.argtypes = [vp]
         lib.tt_cores_to_bf16.restype = ctypes.c_int
         lib.tt_cores_to_bf16.argtypes = [vp, vp, ctypes.c_size_t, vp]
+        lib.tt_forward_bf16_direct_pays.restype = ctypes.c_int
+        lib.tt_forward_bf16_direct_pays.argtypes = [vp, i64, i64]
+        lib.tt_emb_bag_forward_bf16_direct.restype = ctypes.c_int
+        lib.tt_emb_bag_forward_bf16_direct.argtypes = [vp, vp, vp, vp, i64, i64, vp, vp]
         lib.tt_emb_bag_forward_bf16.restype = ctypes.c_int
         lib.tt_emb_bag_forward_bf16.argtypes = [vp, vp, vp, vp, i64, i64, vp, vp]
         lib.tt_index_graph_workspace_bytes.restype = ctypes.c_size_t
@@ -372,6 +377,23 @@ def tt_emb_bag_forward_bf16(table: Table, bf16_cores, plan, offsets, out=None, s
                                                 _ptr(offsets), nnz, nb, _ptr(out), _stream(stream))
     _check(st, "tt_emb_bag_forward_bf16")
     return out
+
+
+def tt_emb_bag_forward_bf16_direct(table: Table, bf16_cores, indices, offsets, out=None, stream=None):
+    """`tt_emb_bag_forward_bf16` without a plan: one launch, every lookup its own chain."""
+    indices, offsets = _dev_i64(indices, "indices"), _dev_i64(offsets, "offsets")
+    nnz, nb = indices.numel(), offsets.numel() - 1
+    if out is None:
+        out = torch.empty((nb, table.dim), dtype=torch.float32, device=offsets.device)
+    _dev_f32(out, "out")
+    st = load_library().tt_emb_bag_forward_bf16_direct(ctypes.byref(table.c), _ptr(bf16_cores), _ptr(indices), _ptr(offsets),
+                                                       nnz, nb, _ptr(out), _stream(stream))
+    _check(st, "tt_emb_bag_forward_bf16_direct")
+    return out
+
+
+def tt_forward_bf16_direct_pays(table: Table, nnz: int, num_bags: int) -> bool:
+    return bool(load_library().tt_forward_bf16_direct_pays(ctypes.byref(table.c), int(nnz), int(num_bags)))
 
 
 def tt_emb_bag_forward_static(table: Table, indices, offsets, out, stream=None):

@@ -417,6 +417,29 @@ tt_status tt_emb_bag_forward_bf16(const tt_table *table, const void *bf16_cores,
   return ttk_bag_sum(b, (hipStream_t)stream);
 }
 
+int tt_forward_bf16_direct_pays(const tt_table *table, int64_t nnz, int64_t num_bags) {
+  TTShape sh;
+  if (!table || !derive_shape(table, &sh) || !ttk_forward_mfma_supported(sh) || !batch_ok(nnz, num_bags)) return 0;
+  return ttk_bag_direct_bf16_pays(sh, nnz, num_bags) ? 1 : 0;
+}
+
+tt_status tt_emb_bag_forward_bf16_direct(const tt_table *table, const void *bf16_cores, const int64_t *indices,
+                                         const int64_t *offsets, int64_t nnz, int64_t num_bags, float *out, void *stream) {
+  TTShape sh;
+  if (!table || !bf16_cores || !offsets || (nnz > 0 && !indices) || (num_bags > 0 && !out)) return TT_ERR_INVALID_ARG;
+  if (!derive_shape(table, &sh) || !ttk_forward_mfma_supported(sh)) return TT_ERR_SHAPE;
+  if (!batch_ok(nnz, num_bags)) return TT_ERR_INVALID_ARG;
+  if (((uintptr_t)bf16_cores & 255) != 0) return TT_ERR_WORKSPACE;
+  size_t off[3], total;
+  ttk_bf16_layout(sh, off, &total);
+  tt_table view = *table;  // the kernel's core pointers: the bf16 copies
+  for (int k = 0; k < 3; ++k) view.core[k] = (float *)((char *)const_cast<void *>(bf16_cores) + off[k]);
+  TTDev d;
+  fill_dev(&d, sh, &view, nullptr, indices, offsets, nnz, num_bags, nullptr, out, nullptr, nullptr, 0.f, false);
+  const TTBatch b = {1, &d, nullptr};
+  return ttk_bag_direct_bf16(b, (hipStream_t)stream);
+}
+
 tt_status tt_fuse_shape(const tt_fuse_members *members, tt_table *fused) {
   long long N[3];
   if (!fused) return TT_ERR_INVALID_ARG;

@@ -353,6 +353,108 @@ k_fwd_direct(TTArg<BATCHED> a) {
   }
 }
 
+// The bag sums from bf16 copies of the cores (layouts of k_cores_to_bf16) without a plan.  A workgroup has a bag and 64 columns
+// (j2, r2) of core 1, its wavefronts take the bag's lookups in turn.  The product of a lookup is R / 4 MFMAs of sixteen 4x4x4
+// blocks (A[m = j1][k = r1], B[k = r1][n = column]: the four r1 of a column are 8 contiguous bytes of the copy), after which a lane
+// holds P12[j1 = 0..3] of its column and adds P12[j1] G3[r2][i3][j3] to 16 sums that stay in registers over the bag; the
+// sums over r2, across lanes, and over the wavefronts are formed once per bag.  All sums are fp32.
+// Bound by the slices a lookup reads, repeated or not (64 KB at ranks 64, out of L1 as fast as out of L2); two columns a lane
+// halve the rest (one: 29.8 us for 5161 lookups at ranks 64, two: 23.3; with reorder and planned forward 62).  Errors against 64 bits
+// are two thirds of the planned forward's (500 bags of 1 to 20 lookups, ranks 64: 9.7e-8 / 1.59e-7, 2-norm).
+typedef short bf16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int BAGB_WAVES = 4, BAGB_COLS = 2, BAGB_BLOCK = 8;  // wavefronts per workgroup, columns per lane, lookups per partial sum
+template <bool BATCHED, int R>
+__global__ void __launch_bounds__(TT_WAVE * BAGB_WAVES, 4)
+k_bag_direct_bf16(TTArg<BATCHED> a) {
+  const TTDev &d = a.get();
+  const TTShape &sh = d.sh;
+  constexpr int CPL = BAGB_COLS, COLS = TT_WAVE * CPL, S2 = 8 * R, GROUPS = S2 / COLS, JW = COLS / R, JL = R / CPL, NV = 16;
+  static_assert(COLS % R == 0 && JL >= NV, "a wavefront holds whole j2; NV: sums (j1, j3) of a lane, JL: lanes of a j2");
+  const unsigned short *__restrict__ g1 = reinterpret_cast<const unsigned short *>(d.g[0]),
+                       *__restrict__ g2 = reinterpret_cast<const unsigned short *>(d.g[1]),
+                       *__restrict__ g3 = reinterpret_cast<const unsigned short *>(d.g[2]);
+  const int64_t *__restrict__ indices = d.indices, *__restrict__ offsets = d.offsets;
+  __shared__ float s_sum[BAGB_WAVES][JW * NV];
+  const int b = (int)blockIdx.x / GROUPS, grp = (int)blockIdx.x - b * GROUPS;
+  const int lane = threadIdx.x & (TT_WAVE - 1), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / TT_WAVE);
+  const int c = grp * COLS + lane * CPL, r2 = (lane * CPL) & (R - 1);
+  // offsets are clamped to [0, nnz] so that a malformed CSR array cannot index out of bounds
+  const long long o0 = offsets[b], o1 = offsets[b + 1], nnz = d.nnz;
+  const int l0 = o0 < 0 ? 0 : (o0 > nnz ? (int)nnz : (int)o0), l1 = o1 < l0 ? l0 : (o1 > nnz ? (int)nnz : (int)o1);
+  float acc[NV], tot[NV];  // the running block of BAGB_BLOCK lookups, and the blocks before it: rounding grows with the blocks
+#pragma unroll
+  for (int k = 0; k < NV; ++k) acc[k] = tot[k] = 0.f;
+  int in_block = 0;
+  for (int base = l0 + wave; base < l1; base += BAGB_WAVES * TT_WAVE) {  // uniform per wavefront
+    const int mine = base + BAGB_WAVES * lane;  // the wavefront's next 64 lookups, one per lane
+    const long long at = mine < l1 ? indices[mine] : -1;
+    const int row = at >= 0 && at < sh.num_rows ? (int)at : -1;  // an invalid lookup adds nothing
+    for (unsigned long long left = __ballot(row >= 0); left != 0; left &= left - 1) {
+      const int x = __builtin_amdgcn_readlane(row, __ffsll(left) - 1);
+      const int p = tt_div(x, sh.mul3, sh.sh3), i1 = tt_div(p, sh.mul2, sh.sh2), i2 = p - i1 * sh.n2, i3 = x - p * sh.n3;
+      struct __align__(8 * CPL) Cols { uint2 c[CPL]; };  // four r1 of this lane's columns
+      const Cols *col = reinterpret_cast<const Cols *>(g2 + (((size_t)i2 * (R / 4)) * S2 + c) * 4);
+      // block q of the A register holds r1 = 4q .. 4q + 3; step q broadcasts it to all blocks
+      const uint2 av = *reinterpret_cast<const uint2 *>(g1 + (size_t)i1 * (4 * R) + (lane & 3) * R + 4 * ((lane >> 2) & (R / 4 - 1)));
+      const bf16x4 am = *reinterpret_cast<const bf16x4 *>(&av);
+      Cols bv[R / 4];
+      uint2 w2[CPL];
+#pragma unroll
+      for (int q = 0; q < R / 4; ++q) bv[q] = col[(size_t)q * (S2 / CPL)];
+#pragma unroll
+      for (int e = 0; e < CPL; ++e) w2[e] = *reinterpret_cast<const uint2 *>(g3 + ((size_t)(r2 + e) * sh.n3 + i3) * 4);
+      __builtin_amdgcn_sched_barrier(0);  // every load is requested before the first product waits
+      f32x4 pr[CPL][2];  // per column two chains
+#pragma unroll
+      for (int e = 0; e < CPL; ++e) pr[e][0] = pr[e][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+      tt_static_for<0, R / 4>([&](auto k) __attribute__((always_inline)) {
+        constexpr int q = decltype(k)::value;
+#pragma unroll
+        for (int e = 0; e < CPL; ++e)
+          pr[e][q & 1] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(am, *reinterpret_cast<const bf16x4 *>(&bv[q].c[e]), pr[e][q & 1], 4, q, 0);
+      });
+#pragma unroll
+      for (int e = 0; e < CPL; ++e) {
+        const float w[4] = {__uint_as_float(w2[e].x << 16), __uint_as_float(w2[e].x & 0xffff0000u), __uint_as_float(w2[e].y << 16),
+                            __uint_as_float(w2[e].y & 0xffff0000u)};
+#pragma unroll
+        for (int j1 = 0; j1 < 4; ++j1)
+#pragma unroll
+          for (int j3 = 0; j3 < 4; ++j3) acc[4 * j1 + j3] = fmaf(pr[e][0][j1] + pr[e][1][j1], w[j3], acc[4 * j1 + j3]);
+      }
+      if (++in_block == BAGB_BLOCK) {  // uniform
+        in_block = 0;
+#pragma unroll
+        for (int k = 0; k < NV; ++k) { tot[k] += acc[k]; acc[k] = 0.f; }
+      }
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < NV; ++k) acc[k] += tot[k];
+  // Over r2, the JL lanes of a j2: a lane hands on the half of its sums that the other one keeps, and ends with one of the 16.
+  int idx = 0;
+#pragma unroll
+  for (int o = 1, half = NV / 2; o < NV; o <<= 1, half >>= 1) {
+    const bool up = (lane & o) != 0;
+#pragma unroll
+    for (int i = 0; i < half; ++i) {
+      const float x = acc[i], y = acc[i + half];  // (by value: a choice between elements becomes an index, and a chain of selects)
+      acc[i] = (up ? y : x) + __shfl_xor(up ? x : y, o, TT_WAVE);
+    }
+    idx += up ? half : 0;
+  }
+#pragma unroll
+  for (int o = NV; o < JL; o <<= 1) acc[0] += __shfl_xor(acc[0], o, TT_WAVE);
+  if ((lane & (JL - 1)) < NV) s_sum[wave][(lane / JL) * NV + idx] = acc[0];
+  __syncthreads();
+  if (threadIdx.x < JW * NV) {
+    const float sum = (s_sum[0][threadIdx.x] + s_sum[1][threadIdx.x]) + (s_sum[2][threadIdx.x] + s_sum[3][threadIdx.x]);
+    const int j2 = grp * JW + (int)threadIdx.x / NV, j1 = (threadIdx.x >> 2) & 3, j3 = threadIdx.x & 3;
+    d.out[(size_t)b * sh.D + (j1 * 8 + j2) * 4 + j3] = sum;
+  }
+}
+
 size_t fwd_lds_bytes(const TTShape &sh, int rows_per_iter) {
   return sizeof(float) * ((size_t)sh.S1 + (size_t)sh.d1 * sh.d2 * sh.R2p +
                           (size_t)rows_per_iter * sh.S3);
@@ -434,4 +536,28 @@ tt_status ttk_forward_direct(const TTBatch &b, hipStream_t s) {
   if (d.sh.R1 == 32) TT_LAUNCH_T2(k_fwd_direct, 32, false, wgs, nt, 0, s, b);
   else TT_LAUNCH_T2(k_fwd_direct, 64, false, wgs, nt, 0, s, b);
   return ttk_bag_sum(b, s);
+}
+
+// Nanoseconds per lookup and per bag that this costs (fitted to batches of 100 to 40000 lookups in 500 to 20000 bags), against
+// what a plan and the planned forward take at least, with every lookup the same row: 18 us and more up to
+// TT_SMALL_MAX_LOOKUPS, 51 us and more above.  Reorder + forward / this, bags of ten, rows spread / log-uniform / all the same:
+//   ranks 32   2048 lookups 35 / 5.5, 34 / 5.6, 27 / 5.6   5161 59 / 10.2, 61 / 10.0, 53 / 10.0   40000 87 / 47, 78 / 49, 59 / 46
+//   ranks 64   2048 39 / 10.3, 35 / 10.7, 27 / 9.5         5161 67 / 22.6, 63 / 23.3, 52 / 19.5   10000 79 / 37, 67 / 41, 54 / 31
+//              20000 97 / 71, 77 / 75, 54 / 59
+// One-lookup bags, ranks 64: 5000 62 / 40, 15000 70 / 117; 20000 bags with ten lookups in all: 49 / 86 (ranks 32 50 / 33).
+// A bag that holds thousands of lookups takes the planned bag sum and this about the same time (ranks 64, 5000 in one bag 679 / 782,
+// in 100 bags 88 / 59).
+bool ttk_bag_direct_bf16_pays(const TTShape &sh, long long nnz, long long bags) {
+  const long long ns = sh.R1 == 32 ? (19 * nnz + 28 * bags) / 20 : (31 * nnz + 43 * bags) / 10;
+  return ns <= (nnz <= TT_SMALL_MAX_LOOKUPS ? 13000 : 45000);
+}
+
+tt_status ttk_bag_direct_bf16(const TTBatch &b, hipStream_t s) {
+  const TTDev &d = b.host[0];
+  if (d.num_bags == 0) return TT_OK;
+  const long long wgs = (long long)d.num_bags * (d.sh.S2 / (TT_WAVE * BAGB_COLS));
+  if (wgs > TT_MAX_WORKGROUPS) return TT_ERR_INVALID_ARG;
+  if (d.sh.R1 == 32) TT_LAUNCH_T(k_bag_direct_bf16, 32, wgs, TT_WAVE * BAGB_WAVES, 0, s, b);
+  else TT_LAUNCH_T(k_bag_direct_bf16, 64, wgs, TT_WAVE * BAGB_WAVES, 0, s, b);
+  return tt_launch_status();
 }

@@ -6,6 +6,8 @@
 #include <hip/hip_ext.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "tt_emb.h"
 
 // Derived shape of one table, passed by value to kernels.
@@ -198,6 +200,9 @@ tt_status ttk_forward_plan(const TTBatch &b, hipStream_t s);
 #define TT_DIRECT_MAX_LOOKUPS_64 8192  // (ranks 64)
 bool ttk_forward_direct_serves(const TTDev &d);
 tt_status ttk_forward_direct(const TTBatch &b, hipStream_t s);
+// the same from bf16 copies of the cores, one launch and no scratch at all
+tt_status ttk_bag_direct_bf16(const TTBatch &b, hipStream_t s);
+bool ttk_bag_direct_bf16_pays(const TTShape &sh, long long nnz, long long bags);
 bool ttk_forward_mfma_supported(const TTShape &sh);
 tt_status ttk_forward_mfma(const TTBatch &b, hipStream_t s);
 // number of strips (16 values of r2, all j2) a core-1 slice is cut into by the backward matrix-core
@@ -283,6 +288,14 @@ static inline tt_status tt_launch_status() {
 
 // ---- device helpers -----------------------------------------------------------------------
 #ifdef __HIPCC__
+// f(integral constant I) for I = A .. B - 1: loops whose counter has to be a constant (operand modifiers of an instruction)
+template <int A, int B, class F>
+__device__ __forceinline__ void tt_static_for(F f) {
+  if constexpr (A < B) {
+    f(std::integral_constant<int, A>{});
+    tt_static_for<A + 1, B>(f);
+  }
+}
 __host__ __device__ __forceinline__ int tt_div(int x, unsigned mul, unsigned sh) {
   return (int)(((unsigned long long)(unsigned)x * mul) >> (31 + sh));
 }

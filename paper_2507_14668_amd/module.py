@@ -149,6 +149,9 @@ class TTEmbeddingBag(torch.nn.Module):
             input = input.to(torch.int64)
         indices, offsets = self._bag_offsets(input, offsets)
         table = self._table(self.cores())
+        # the plan would serve this call only: short batches are faster without one
+        if binding.tt_forward_bf16_direct_pays(table, indices.numel(), offsets.numel() - 1):
+            return binding.tt_emb_bag_forward_bf16_direct(table, self._bf16_cores, indices, offsets)
         plan = binding.tt_index_reorder(table, indices, offsets)
         return binding.tt_emb_bag_forward_bf16(table, self._bf16_cores, plan, offsets)
 

@@ -370,4 +370,13 @@ void wave_mfma_16x16x4(float a, float b, float *c4) {
   }
   yield(AT_WAVE);
 }
+void wave_mfma_4x4x1(float a, float b, float *c4, int cbsz, int abid) {
+  Wave *w = t_wave;
+  const int lane = w->cur;
+  w->mfa[lane] = a; w->mfb[lane] = b;
+  yield(AT_WAVE);
+  const int block = ((lane >> 2) & ~((1 << cbsz) - 1)) + abid;
+  for (int v = 0; v < 4; ++v) c4[v] = fmaf(w->mfa[4 * block + v], b, c4[v]);
+  yield(AT_WAVE);
+}
 }  // namespace emu

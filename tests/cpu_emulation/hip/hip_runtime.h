@@ -43,6 +43,7 @@ void *dyn_lds();
 uint64_t wave_exchange(uint64_t v, int src_lane);          // value of lane src_lane (own lane if out of range)
 uint64_t wave_ballot(bool pred);
 void wave_mfma_16x16x4(float a, float b, float *c4);
+void wave_mfma_4x4x1(float a, float b, float *c4, int cbsz, int abid);
 }  // namespace emu
 
 #define threadIdx emu::t_threadIdx
@@ -101,6 +102,7 @@ static inline int __builtin_amdgcn_readlane(int v, int lane) { return (int)(uint
 // accesses inside a wavefront has to be one
 static inline void __builtin_amdgcn_wave_barrier() { emu::wave_exchange(0, -1); }
 #define __builtin_amdgcn_fence(order, scope) ((void)0)
+#define __builtin_amdgcn_sched_barrier(mask) ((void)0)
 static inline long long clock64() { return 0; }
 
 static inline int atomicAdd(int *p, int v) { return __atomic_fetch_add(p, v, __ATOMIC_RELAXED); }
@@ -135,3 +137,19 @@ static inline emu_f32x4 emu_mfma_bf16(emu_bf16x4 a, emu_bf16x4 b, emu_f32x4 c, i
   return (emu_f32x4){t[0], t[1], t[2], t[3]};
 }
 #define __builtin_amdgcn_mfma_f32_16x16x16bf16_1k emu_mfma_bf16
+// sixteen blocks of 4x4x1 (4x4x4 for bf16): lane l supplies A[m = l%4] and B[n = l%4] of block l/4 and holds its C[m = v][n = l%4];
+// every block of a group of 2^cbsz takes A from the group's block abid
+static inline emu_f32x4 emu_mfma_4x4(float a, float b, emu_f32x4 c, int cbsz, int abid, int) {
+  float t[4] = {c[0], c[1], c[2], c[3]};
+  emu::wave_mfma_4x4x1(a, b, t, cbsz, abid);
+  return (emu_f32x4){t[0], t[1], t[2], t[3]};
+}
+#define __builtin_amdgcn_mfma_f32_4x4x1f32 emu_mfma_4x4
+static inline emu_f32x4 emu_mfma_4x4_bf16(emu_bf16x4 a, emu_bf16x4 b, emu_f32x4 c, int cbsz, int abid, int) {
+  float t[4] = {c[0], c[1], c[2], c[3]};
+  for (int i = 0; i < 4; ++i)
+    emu::wave_mfma_4x4x1(__uint_as_float((unsigned)(unsigned short)a[i] << 16), __uint_as_float((unsigned)(unsigned short)b[i] << 16), t,
+                         cbsz, abid);
+  return (emu_f32x4){t[0], t[1], t[2], t[3]};
+}
+#define __builtin_amdgcn_mfma_f32_4x4x4bf16_1k emu_mfma_4x4_bf16

@@ -49,3 +49,49 @@ def test_direct_forward_matches_oracle_and_plan(emu, ora, r, n, lens, spoil):
     np.testing.assert_allclose(out, ref, rtol=0, atol=2e-6 * np.abs(ref).max())
     if not spoil:
         g.assert_close_rows(out, ora.forward(shape, cores, idx, off), g.FWD_RTOL, shape.dim, "direct forward")
+
+
+@pytest.mark.parametrize("r,n,lens,spoil", [
+    (32, (5, 3, 7), (20,), ""), (64, (5, 3, 7), (0, 7, 0, 13), ""), (32, (5, 3, 7), (300, 1, 40), ""), (64, (5, 3, 7), (3, 70), "indices"),
+    (32, (5, 3, 7), (6, 10, 6, 4), "offsets"), (64, (2, 3, 2), (25, 15), ""), (32, (5, 3, 7), (), "")])
+def test_direct_bf16_forward_matches_oracle_and_plan(emu, ora, r, n, lens, spoil):
+    import gpu_util as g
+    from test_gpu_parity_small import round_to_bf16
+    lib, binding = emu
+    vp, i64 = ctypes.c_void_p, ctypes.c_int64
+    lib.tt_cores_to_bf16.argtypes = [vp, vp, ctypes.c_size_t, vp]
+    lib.tt_bf16_cores_bytes.restype, lib.tt_bf16_cores_bytes.argtypes = ctypes.c_size_t, [vp]
+    lib.tt_emb_bag_forward_bf16.argtypes = [vp, vp, vp, vp, i64, i64, vp, vp]
+    lib.tt_emb_bag_forward_bf16_direct.argtypes = [vp, vp, vp, vp, i64, i64, vp, vp]
+    lib.tt_forward_bf16_direct_pays.argtypes = [vp, i64, i64]
+    shape, cores, _, _, _ = wl.small_random_problem(9, n=n, d=(4, 8, 4), r=(1, r, r, 1), sigma=0.2)
+    rng = np.random.default_rng(len(lens) + r)
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    nnz, nb = int(off[-1]), len(lens)
+    idx = rng.integers(0, shape.num_rows, nnz).astype(np.int64)
+    if spoil == "indices":
+        idx[[1, 5, nnz - 1]] = (-1, shape.num_rows, 2 ** 40)
+    if spoil == "offsets":
+        off[1], off[3] = nnz + 5, -2
+    raw = cores
+    cores = [_aligned(np.asarray(c).size * 4).view(np.float32) for c in raw]
+    for c, x in zip(cores, raw):
+        c[:] = np.asarray(x, np.float32).reshape(-1)
+    table = _table(binding, shape, cores)
+    bf = _aligned(lib.tt_bf16_cores_bytes(ctypes.byref(table)))
+    assert lib.tt_cores_to_bf16(ctypes.byref(table), _ptr(bf), bf.nbytes, None) == 0
+    out = np.full((nb, shape.dim), np.nan, np.float32)
+    assert lib.tt_emb_bag_forward_bf16_direct(ctypes.byref(table), _ptr(bf), _ptr(idx), _ptr(off), nnz, nb, _ptr(out), None) == 0
+    assert lib.tt_forward_bf16_direct_pays(ctypes.byref(table), nnz, nb) == 1
+    assert lib.tt_forward_bf16_direct_pays(ctypes.byref(table), nnz, -1) == 0
+    assert lib.tt_forward_bf16_direct_pays(ctypes.byref(table), 10 ** 6, 1000) == 0
+    ws, plan = _aligned(lib.tt_workspace_bytes(ctypes.byref(table), nnz, nb)), binding.CPlan()
+    assert lib.tt_index_reorder(ctypes.byref(table), _ptr(idx), _ptr(off), nnz, nb, None, _ptr(ws), ws.nbytes, ctypes.byref(plan), None) == 0
+    ref = np.full_like(out, np.nan)
+    assert lib.tt_emb_bag_forward_bf16(ctypes.byref(table), _ptr(bf), ctypes.byref(plan), _ptr(off), nnz, nb, _ptr(ref), None) == 0
+    if nb == 0:
+        return
+    # both are fp32 sums of the same products, over chains of at most 300 lookups in another order
+    np.testing.assert_allclose(out, ref, rtol=0, atol=5e-6 * np.abs(ref).max())
+    if not spoil:
+        g.assert_close_rows(out, ora.forward(shape, [round_to_bf16(c) for c in raw], idx, off), g.FWD_RTOL, shape.dim, "direct bf16 forward")

@@ -1,6 +1,6 @@
 """Short batches of the allocation-free forward are summed without a plan (one launch up to 32 lookups, two up to 16384 or
 8192): bit for bit the result of tt_index_reorder + tt_emb_bag_forward, on both sides of every limit, with invalid lookups, empty
-and malformed bags, repeated rows, and replayed from a graph."""
+and malformed bags, repeated rows, and replayed from a graph.  The bf16 inference forward without a plan against the planned one."""
 import pytest
 import torch
 
@@ -73,3 +73,26 @@ def test_replayed_from_a_graph():
             torch.cuda.synchronize()
             plan = tt.tt_index_reorder(table, idx, off)
             assert torch.equal(out, tt.tt_emb_bag_forward(table, plan, idx, off))
+
+
+@pytest.mark.parametrize("r,nnz,bags", [
+    (r, nnz, bags) for r, top in ((32, 40000), (64, 12000))
+    for nnz, bags in ((1, 1), (20, 1), (65, 3), (300, 1), (700, 90), (2048, 300), (2049, 300), (top, top // 10), (2 * top, top // 10), (50, 30000))])
+def test_bf16_inference_without_a_plan(r, nnz, bags):
+    """On both sides of the rule the module gives what the planned call gives, to the fp32 rounding of sums over the bag's
+    lookups (chains of R products and of the lookups, added in another order: a few 1e-7 of the largest output)."""
+    import paper_2507_14668_amd as tt
+    from paper_2507_14668_amd import binding
+    print("case direct bf16 r=%d nnz=%d bags=%d" % (r, nnz, bags), flush=True)
+    n, d = (60, 50, 40), (4, 8, 4)
+    bag = tt.TTEmbeddingBag(n[0] * n[1] * n[2] - 7, 128, n=n, d=d, ranks=(r, r), include_last_offset=True,
+                            generator=torch.Generator(device="cuda").manual_seed(r)).bf16_inference()
+    table = bag._table(bag.cores())
+    idx, off = _batch(table.num_rows, nnz, bags, nnz + bags)
+    plan = tt.tt_index_reorder(table, idx, off)
+    ref = tt.tt_emb_bag_forward_bf16(table, bag._bf16_cores, plan, off)
+    direct = binding.tt_emb_bag_forward_bf16_direct(table, bag._bf16_cores, idx, off)
+    for out in (bag.forward_bf16(idx, off), direct):
+        assert (out - ref).abs().max() <= 3e-6 * ref.abs().max() and (out - ref).norm() <= 1e-6 * ref.norm()
+    if not binding.tt_forward_bf16_direct_pays(table, nnz, bags):
+        assert torch.equal(bag.forward_bf16(idx, off), ref)
