@@ -122,12 +122,13 @@ __device__ __forceinline__ SegView seg_view(const TTDev &d, int kind) {
 struct SegLaunch {
   int kind, chunk, blocks;
   int kind_b, chunk_b;  // kind_b < 0: a single sum
+  int spread, spread_b; // stage 2 takes a chunk per lane group instead of one per workgroup
 };
-struct SegPick { int kind, chunk, bid, nblk; size_t poff; };
+struct SegPick { int kind, chunk, bid, nblk, spread; size_t poff; };
 __device__ __forceinline__ SegPick seg_pick(const SegLaunch &L, const TTDev &d) {
-  SegPick p = {L.kind, L.chunk, (int)blockIdx.x, L.kind_b < 0 ? (int)gridDim.x : L.blocks, 0};
+  SegPick p = {L.kind, L.chunk, (int)blockIdx.x, L.kind_b < 0 ? (int)gridDim.x : L.blocks, L.spread, 0};
   if (L.kind_b >= 0 && (int)blockIdx.x >= L.blocks) {
-    p.kind = L.kind_b; p.chunk = L.chunk_b; p.bid = (int)blockIdx.x - L.blocks;
+    p.kind = L.kind_b; p.chunk = L.chunk_b; p.spread = L.spread_b; p.bid = (int)blockIdx.x - L.blocks;
     p.nblk = (int)gridDim.x - L.blocks;
     // the first kind's share of this table's partial buffer: two slots per chunk it can have
     const long long cap = L.kind == SEG_GAGG ? d.plan.nnz : (L.kind == SEG_DG3 ? d.plan.max_rows : d.plan.max_prefixes);
@@ -272,10 +273,21 @@ k_seg_stage1(TTArg<BATCHED> arg, SegLaunch L, int lanes) {
 #ifndef TT_SEG2_UNROLL
 #define TT_SEG2_UNROLL 8  // partials a lane group of stage 2 keeps in flight
 #endif
-// Stage 2: workgroup per chunk.  The chunk in which a multi-chunk segment begins owns it and adds
-// its own slot-1 partial and the slot-0 partials of the following chunks, in chunk order.
-// With `dense`, workgroup c also zero-fills segment c if it is empty.
+// Stage 2.  The chunk in which a multi-chunk segment begins owns it and adds its own slot-1 partial and the
+// slot-0 partials of the following chunks, in chunk order.  What a workgroup costs is its chain of dependent loads
+// (segment id, segment range, partials), whatever it adds.
+//   Workgroup per chunk: the shortest chain, as long as the chip holds them in about two rounds.
+//   Lane group per chunk (`spread`): most owners add two vectors, which a lane group does by itself, so that
+// many chunks are through in one round.  Segments of many partials are left to all lane groups of the workgroup; those
+// are the hot rows, neighbours in sorted order where ids are not permuted, so the chunks of a workgroup lie a grid
+// apart and no workgroup gets many of them.
+// Stage 2 of the gradient merge at D = 128, per chunk / spread: 1125 chunks 5.0 / 6.6 us, 4600 8.3 / 9.8, 8192 10.1 / 8.4,
+// 10500 13.1 / 11.1, 12800 15.3 / 11.0; the sums are the same bit for bit.
+// With `dense`, workgroup (lane group) c also zero-fills segment c if it is empty.
 // LDS: red[groups][W]
+#ifndef TT_SEG2_SPREAD_CHUNKS
+#define TT_SEG2_SPREAD_CHUNKS 6144  // chunks above which a lane group takes one
+#endif
 template <bool BATCHED, int VEC>
 __global__ void __launch_bounds__(TT_BLOCK)
 k_seg_stage2(TTArg<BATCHED> arg, SegLaunch L, int lanes) {
@@ -289,66 +301,113 @@ k_seg_stage2(TTArg<BATCHED> arg, SegLaunch L, int lanes) {
   extern __shared__ float red[];
   const int M = *sv.count_ptr;
   const int nchunks = (M + chunk - 1) / chunk;
-  const int c = pk.bid;
   const int groups = blockDim.x / lanes, g = threadIdx.x / lanes, lane = threadIdx.x - g * lanes;
-  if (dense && c < nseg && seg_off[c] == seg_off[c + 1] && g == 0) {
+  const int gc = groups * chunk;
+  // Partials to add for the segment that chunk c owns: slot 0 of the chunks c+1 .. c1, except that stage 1
+  // has left ONE partial (in the first chunk) for every run of `groups` chunks handled by one workgroup
+  // that lies strictly inside the segment: the runs B0 .. B1.  Units in order: single chunks before the
+  // runs, one per run, single chunks after.
+  struct Units {
+    int seg, c, B0, B1, nh, nm, n;  // n = 0: no segment starts in the chunk and runs past it
+    __device__ __forceinline__ int chunk_of(int u, int groups) const {
+      return u < nh ? c + 1 + u : (u < nh + nm ? (B0 + (u - nh)) * groups : (B1 + 1) * groups + (u - nh - nm));
+    }
+  };
+  __shared__ int s_long;
+  __shared__ Units s_list[TT_BLOCK];  // spread: segments left to the whole workgroup
+  auto units_of = [&](int c) {
+    Units k;
+    const int lo = c * chunk, hi = lo + chunk, end = hi < M ? hi : M;
+    k.c = c;
+    k.seg = seg_src[end - 1] / seg_div;
+    const int a = seg_off[k.seg], b = seg_off[k.seg + 1], c1 = (b - 1) / chunk;
+    k.B0 = a / gc + 1; k.B1 = (b + gc - 1) / gc - 2;
+    k.nh = c1 - c; k.nm = 0;
+    int nt = 0;
+    if (k.B0 <= k.B1) {
+      k.nh = k.B0 * groups - (c + 1);
+      k.nm = k.B1 - k.B0 + 1;
+      nt = c1 - (k.B1 + 1) * groups + 1;
+    }
+    k.n = a >= lo && b > hi ? k.nh + k.nm + nt : 0;
+    return k;
+  };
+  auto finish = [&](const Vec<VEC> &acc, int s, int e) {
+    float *dst = out + seg_out_index(s, e, out_inner, nseg);
+    if (sv.fused) acc.store_sgd(dst, sv.lr); else acc.store(dst);
+  };
+  // One segment by all lane groups: they take the units round-robin, their sums are added in group order.
+  auto fold = [&](const Units &k) {
+    for (int e = lane * VEC; e < W; e += lanes * VEC) {
+      Vec<VEC> acc;
+      acc.zero();
+      int u = g;
+      for (; u + (TT_SEG2_UNROLL - 1) * groups < k.n; u += TT_SEG2_UNROLL * groups) {
+        Vec<VEC> x[TT_SEG2_UNROLL];  // independent loads in flight, added in unit order
+#pragma unroll
+        for (int j = 0; j < TT_SEG2_UNROLL; ++j) x[j].load(partial + ((size_t)k.chunk_of(u + j * groups, groups) * 2) * W + e);
+#pragma unroll
+        for (int j = 0; j < TT_SEG2_UNROLL; ++j) acc.add(x[j]);
+      }
+      for (; u < k.n; u += groups) {
+        Vec<VEC> x;
+        x.load(partial + ((size_t)k.chunk_of(u, groups) * 2) * W + e);
+        acc.add(x);
+      }
+      acc.store(red + (size_t)g * W + e);
+    }
+    __syncthreads();
+    if (g == 0) {
+      for (int e = lane * VEC; e < W; e += lanes * VEC) {
+        Vec<VEC> acc, x;
+        acc.load(partial + ((size_t)k.c * 2 + 1) * W + e);
+        for (int j = 0; j < groups; ++j) {
+          x.load(red + (size_t)j * W + e);
+          acc.add(x);
+        }
+        finish(acc, k.seg, e);
+      }
+    }
+  };
+  const int mine = pk.bid + (pk.spread ? g * pk.nblk : 0);
+  if (dense && (pk.spread || g == 0) && mine < nseg && seg_off[mine] == seg_off[mine + 1]) {
     Vec<VEC> z;
     z.zero();
     for (int e = lane * VEC; e < W; e += lanes * VEC)
-      z.store(out + seg_out_index(c, e, out_inner, nseg));
+      z.store(out + seg_out_index(mine, e, out_inner, nseg));
   }
-  if (c >= nchunks) return;  // uniform
-  const int lo = c * chunk, hi = lo + chunk, end = hi < M ? hi : M;
-  const int s = seg_src[end - 1] / seg_div;
-  const int a = seg_off[s], b = seg_off[s + 1];
-  if (!(a >= lo && b > hi)) return;  // uniform: no segment starts here and runs past the chunk
-  const int c1 = (b - 1) / chunk;
-  // Partials to add: slot 0 of the chunks c+1 .. c1, except that stage 1 has left ONE partial (in
-  // the first chunk) for every run of `groups` chunks handled by one workgroup that lies strictly
-  // inside the segment: the runs B0 .. B1.  Units in order: single chunks before the runs, one per
-  // run, single chunks after.
-  const int gc = groups * chunk;
-  int B0 = a / gc + 1, B1 = (b + gc - 1) / gc - 2;
-  int nh = c1 - c, nm = 0, nt = 0;
-  if (B0 <= B1) {
-    nh = B0 * groups - (c + 1);
-    nm = B1 - B0 + 1;
-    nt = c1 - (B1 + 1) * groups + 1;
+  if (!pk.spread) {  // uniform
+    if (mine >= nchunks) return;
+    const Units k = units_of(mine);
+    if (k.n > 0) fold(k);
+    return;
   }
-  const int units = nh + nm + nt;
-  auto unit_chunk = [&](int u) {
-    return u < nh ? c + 1 + u : (u < nh + nm ? (B0 + (u - nh)) * groups : (B1 + 1) * groups + (u - nh - nm));
-  };
-  for (int e = lane * VEC; e < W; e += lanes * VEC) {
-    Vec<VEC> acc;
-    acc.zero();
-    int u = g;
-    for (; u + (TT_SEG2_UNROLL - 1) * groups < units; u += TT_SEG2_UNROLL * groups) {
-      Vec<VEC> x[TT_SEG2_UNROLL];  // independent loads in flight, added in unit order
+  if (threadIdx.x == 0) s_long = 0;
+  __syncthreads();
+  if (mine < nchunks) {
+    const Units k = units_of(mine);
+    if (k.n > TT_SEG2_UNROLL || k.n > groups) {
+      if (lane == 0) s_list[atomicAdd(&s_long, 1)] = k;  // (segments are independent: their order does not matter)
+    } else if (k.n > 0) {
+      for (int e = lane * VEC; e < W; e += lanes * VEC) {
+        Vec<VEC> acc, x[TT_SEG2_UNROLL];
+        acc.load(partial + ((size_t)mine * 2 + 1) * W + e);
 #pragma unroll
-      for (int k = 0; k < TT_SEG2_UNROLL; ++k) x[k].load(partial + ((size_t)unit_chunk(u + k * groups) * 2) * W + e);
+        for (int u = 0; u < TT_SEG2_UNROLL; ++u)
+          if (u < k.n) x[u].load(partial + ((size_t)k.chunk_of(u, groups) * 2) * W + e);
 #pragma unroll
-      for (int k = 0; k < TT_SEG2_UNROLL; ++k) acc.add(x[k]);
+        for (int u = 0; u < TT_SEG2_UNROLL; ++u)
+          if (u < k.n) acc.add(x[u]);
+        finish(acc, k.seg, e);
+      }
     }
-    for (; u < units; u += groups) {
-      Vec<VEC> x;
-      x.load(partial + ((size_t)unit_chunk(u) * 2) * W + e);
-      acc.add(x);
-    }
-    acc.store(red + (size_t)g * W + e);
   }
   __syncthreads();
-  if (g == 0) {
-    for (int e = lane * VEC; e < W; e += lanes * VEC) {
-      Vec<VEC> acc, x;
-      acc.load(partial + ((size_t)c * 2 + 1) * W + e);
-      for (int k = 0; k < groups; ++k) {
-        x.load(red + (size_t)k * W + e);
-        acc.add(x);
-      }
-      float *dst = out + seg_out_index(s, e, out_inner, nseg);
-      if (sv.fused) acc.store_sgd(dst, sv.lr); else acc.store(dst);
-    }
+  const int nlong = s_long;
+  for (int i = 0; i < nlong; ++i) {  // uniform
+    const Units k = s_list[i];
+    fold(k);
+    __syncthreads();
   }
 }
 
@@ -362,7 +421,7 @@ static int seg_chunk_for(long long count) {
 }
 
 // Launch shape of one segmented sum over every table of the batch (chunk <= 0: chosen from the count).
-struct SegParams { int W, vec, lanes, groups, chunk, nchunks, blocks1; long long blocks2; };
+struct SegParams { int W, vec, lanes, groups, chunk, nchunks, blocks1, spread; long long blocks2; };
 static SegParams seg_params(const TTBatch &b, int kind, int chunk) {
   const TTShape &sh = b.host[0].sh;
   SegParams p;
@@ -391,6 +450,8 @@ static SegParams seg_params(const TTBatch &b, int kind, int chunk) {
   p.blocks1 = tt_ceil_div(p.nchunks, p.groups);
   if (p.blocks1 > 8192) p.blocks1 = 8192;
   p.blocks2 = p.nchunks > max_seg ? p.nchunks : max_seg;  // dense kinds also zero-fill empty segments
+  p.spread = p.nchunks > TT_SEG2_SPREAD_CHUNKS;
+  if (p.spread) p.blocks2 = tt_ceil_div(p.blocks2, p.groups);
   return p;
 }
 
@@ -399,7 +460,7 @@ static tt_status seg_launch(const TTBatch &b, const SegParams &pa, int kind, con
                             int prof_kernel, hipStream_t s) {
   TTProfScope prof(&b.host[0].plan, prof_kernel, s);  // both stages
   const size_t lds = sizeof(float) * (size_t)pa.groups * pa.W;
-  SegLaunch L1 = {kind, pa.chunk, pa.blocks1, pb ? kind_b : -1, pb ? pb->chunk : 0};
+  SegLaunch L1 = {kind, pa.chunk, pa.blocks1, pb ? kind_b : -1, pb ? pb->chunk : 0, pa.spread, pb ? pb->spread : 0};
   const long long g1 = pa.blocks1 + (pb ? pb->blocks1 : 0);
   if (g1 > 0) {
     if (pa.vec == 4) TT_LAUNCH_T(k_seg_stage1, 4, g1, TT_BLOCK, lds, s, b, L1, pa.lanes);
