@@ -298,7 +298,7 @@ k_seg_stage2(TTArg<BATCHED> arg, SegLaunch L, int lanes) {
   const int32_t *__restrict__ seg_src = sv.seg_src, *__restrict__ seg_off = sv.seg_off;
   float *__restrict__ out = sv.out;
   const float *__restrict__ partial = sv.partial + pk.poff;
-  extern __shared__ float red[];
+  extern __shared__ __align__(16) float red[];  // (16: it lies behind the static arrays)
   const int M = *sv.count_ptr;
   const int nchunks = (M + chunk - 1) / chunk;
   const int groups = blockDim.x / lanes, g = threadIdx.x / lanes, lane = threadIdx.x - g * lanes;

@@ -38,7 +38,7 @@ def _generate(gen: str) -> list:
     out = []
     for u in UNITS:
         text = open(os.path.join(CSRC, u + ".hip")).read()
-        text = re.sub(r"extern __shared__ float (\w+)\[\];", r"float *\1 = (float *)emu::dyn_lds();", text)
+        text = re.sub(r"extern __shared__ (?:__align__\(16\) )?float (\w+)\[\];", r"float *\1 = (float *)emu::dyn_lds();", text)
         text = text.replace("kBatchedCallsEnabled = false", "kBatchedCallsEnabled = true")
         # the host copies of the table descriptors are for the host only: kernels get the uploaded array
         text = text.replace("  if (!host) return TT_ERR_INVALID_ARG;\n",
