@@ -18,6 +18,12 @@
 // (i2, strip) to several workgroups (each loads the strip; the outputs are per row, so nothing has
 // to be combined).
 //
+// Longer batches split F1's operands into three bf16 parts each (FWD_SPLIT): six 16x16x32 bf16 MFMAs of 8.2 ns take the place of
+// eight 16x16x4 fp32 ones of 14.4.  The strip is split once per workgroup and the core-0 tile when it is staged, so the loop has
+// no conversions.  One table with 65 k one-hot lookups at ranks 64: 53.9 -> 42.0 us a launch, nine tables fused at batch 4096: 49 ->
+// 42.3; multi-hot at ranks 32 29.0 -> 26.0, the prefix products alone 18.7 -> 16.5.  The operand tile has to lie on 16 bytes:
+// with the dynamic LDS at any float's address the 16-byte reads made it 68 us.
+//
 // Operand layout of __builtin_amdgcn_mfma_f32_16x16x4f32 (D = A[16x4] * B[4x16] + C):
 //   lane l supplies A[m = l%16][k = l/16] and B[k = l/16][n = l%16];
 //   lane l holds C[m = 4*(l/16) + v][n = l%16] in component v of its float4.
@@ -41,6 +47,8 @@ constexpr int FTHR = 512;   // threads per workgroup
 constexpr int FMETA = 64;   // prefixes whose plan entries are fetched into LDS in one go (8 chunks)
 constexpr int FWD_I3_STAGE = FTHR / TT_MP;  // i3 of the first 64 distinct rows of each prefix is staged in LDS
 
+enum { FWD_FP32 = 0, FWD_SPLIT = 1, FWD_BF16 = 2 };  // how F1 multiplies
+
 template <int R1, int R2, int D2>
 struct FwdGeom {
   static constexpr int JW = 256 / R2;      // j2 values covered by one 256-column strip
@@ -55,10 +63,12 @@ struct FwdGeom {
   static constexpr int KS1 = R1 / 4, KS2 = R2 / 4;
   static constexpr int NT2 = CC / 16;
   static constexpr int D = 4 * D2 * 4, S1 = 4 * R1;
-  static constexpr int OFF_P12 = 32 * RS;
-  static constexpr size_t LDS_FLOATS = (size_t)OFF_P12 + TT_MP * PS;
+  static constexpr int PLANE = 32 * R1;    // split: bf16 values of one of the tile's three parts
+  static constexpr int off_p12(int mode) { return mode == FWD_SPLIT ? 3 * PLANE / 2 : 32 * RS; }
+  static constexpr size_t lds_floats(int mode) { return (size_t)off_p12(mode) + TT_MP * PS; }
+  static constexpr int KB = R1 / 32;       // split: k steps of F1 on 16x16x32
   static constexpr int GPT = (32 * R1) / FTHR;  // core-0 tile elements per thread
-  static_assert(256 % R2 == 0 && D2 % JW == 0 && R1 % 16 == 0 && CC % 16 == 0 && TT_MP == 8, "unsupported shape");
+  static_assert(256 % R2 == 0 && D2 % JW == 0 && R1 % 32 == 0 && 8 * R1 <= FTHR && CC % 16 == 0 && TT_MP == 8, "unsupported shape");
 };
 
 // P12OUT: the kernel stops after F1 and stores the prefix products to the reuse buffer
@@ -69,27 +79,32 @@ struct FwdGeom {
 // and B[k = 4*(l/16) + i][n = l%16], i = 0..3; C as for 16x16x4) with fp32 accumulators, the products
 // stay fp32 in LDS, and F2 is the fp32 MFMA with core-2 values widened exactly: the only difference
 // from the fp32 path is the rounding of the stored cores.
-template <bool BATCHED, int R1, int R2, int D2, bool P12OUT, bool BF16>
+template <bool BATCHED, int R1, int R2, int D2, bool P12OUT, int MODE>
 __global__ void __launch_bounds__(FTHR, 4)  // four wavefronts per SIMD: two workgroups per compute unit
 k_fwd_mfma(TTArg<BATCHED> a, int split) {
   const TTDev &d = a.get();
   const TTShape &sh = d.sh;
+  constexpr bool BF16 = MODE == FWD_BF16, SPLIT = MODE == FWD_SPLIT;
+  if (BATCHED && !BF16 && ttk_forward_splits(d) != SPLIT) return;  // uniform: the other launch serves this table
   const float *__restrict__ g1 = d.g[0], *__restrict__ g2 = d.g[1], *__restrict__ g3 = d.g[2];
   const int32_t *__restrict__ uniq_row = d.plan.uniq_row, *__restrict__ i2_seg = d.plan.i2_seg;
   const int4 *__restrict__ pref_meta = reinterpret_cast<const int4 *>(d.plan.pref_meta);
   float *__restrict__ rowbuf = d.plan.rowbuf, *__restrict__ p12buf = d.p12buf;
   using G = FwdGeom<R1, R2, D2>;
-  extern __shared__ float lds[];
+  extern __shared__ __align__(16) float lds[];  // (16: behind the static arrays it would start at any float)
   float *As = lds;                  // [32][RS]  core-0 slices of the chunk
-  unsigned short *Asb = reinterpret_cast<unsigned short *>(lds);  // BF16: the same tile as [32][R1 + 4] bf16
+  // bf16 cores: the same tile as [32][RSB] bf16.  Split: its three parts of tt_split_bf16, each as F1 reads it, [row tile]
+  // [k step][lane][8], so that a wavefront's operand is 1024 consecutive bytes.
+  unsigned short *Asb = reinterpret_cast<unsigned short *>(lds);
   constexpr int RSB = R1 + 4;
   const unsigned short *__restrict__ g1b = reinterpret_cast<const unsigned short *>(d.g[0]),
                        *__restrict__ g2b = reinterpret_cast<const unsigned short *>(d.g[1]),
                        *__restrict__ g3b = reinterpret_cast<const unsigned short *>(d.g[2]);
-  float *P12s = lds + G::OFF_P12;   // [8][PS]   prefix products of the chunk
+  float *P12s = lds + G::off_p12(MODE);   // [8][PS]   prefix products of the chunk
   __shared__ int s_i1[FMETA], s_u0[FMETA], s_nr[FMETA], s_slot[FMETA];
   __shared__ int s_item_off[2][TT_MP + 1];
   __shared__ int s_i3[2][TT_MP][FWD_I3_STAGE];
+  __shared__ int s_not_finite;  // split: a product was not finite
 
   // Workgroup index = ((i2 / 8) * (strips * split) + (strip, part)) * 8 + i2 % 8: workgroups are
   // dealt to the 8 XCDs round-robin, so all strips and parts of one i2 run on XCD i2 % 8, close in
@@ -105,7 +120,7 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
   // This wavefront's 32 columns of the strip of G2[:, i2], all r1 (B operand of F1), as one float2
   // per row and lane: lane lm holds columns 2*lm, 2*lm + 1, and MFMA tile nt takes component nt, i.e.
   // tile column lm stands for strip column 32*wave + 2*lm + nt.  Requested before the plan is looked at.
-  float2 bq[BF16 ? 1 : G::KS1];
+  float2 bq[BF16 ? 1 : G::KS1];  // (split: row 32*kb + 8*lq + i in bq[8*kb + i])
   uint4 bqb[BF16 ? R1 / 16 : 1];  // BF16: per 16 values of r1, columns 2*lm and 2*lm + 1 with four r1 each
   if constexpr (BF16) {
 #pragma unroll
@@ -114,9 +129,10 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
                                                         32 * wave + 2 * lm) * 4);
   } else {
 #pragma unroll
-    for (int ks = 0; ks < G::KS1; ++ks)
-      bq[ks] = *reinterpret_cast<const float2 *>(g2 + ((size_t)(4 * ks + lq) * sh.n2 + i2) * G::S2 + strip * 256 +
-                                                 32 * wave + 2 * lm);
+    for (int ks = 0; ks < G::KS1; ++ks) {
+      const int r1 = SPLIT ? 32 * (ks >> 3) + 8 * lq + (ks & 7) : 4 * ks + lq;
+      bq[ks] = *reinterpret_cast<const float2 *>(g2 + ((size_t)r1 * sh.n2 + i2) * G::S2 + strip * 256 + 32 * wave + 2 * lm);
+    }
   }
 
   int seg0 = i2_seg[i2], seg1 = i2_seg[i2 + 1];
@@ -131,7 +147,7 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
 
   // Global-memory operands of the NEXT chunk (core-0 rows, row ids of its first rows) are fetched
   // into registers while the current chunk computes.
-  float g1n[G::GPT];
+  float g1n[SPLIT ? 4 : G::GPT];
   int rown = 0;
   auto fetch_meta = [&](int base) __attribute__((always_inline)) {  // plan entries of prefixes base .. base+63 -> LDS
     if (threadIdx.x < FMETA) {
@@ -143,26 +159,48 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
       s_i1[threadIdx.x] = i1; s_u0[threadIdx.x] = u0; s_nr[threadIdx.x] = nr; s_slot[threadIdx.x] = slot;
     }
   };
+  // (split: a thread holds four consecutive r1 of a row; at R1 = 32 two threads hold the same four, since a load under
+  // a branch would have to wait for the stores in front of it)
+  const int arow = (threadIdx.x & 15) + 16 * ((threadIdx.x / (4 * R1)) & 1), ar1 = 4 * ((threadIdx.x >> 4) & (R1 / 4 - 1));
   auto fetch_chunk = [&](int mo) __attribute__((always_inline)) {  // mo = offset of the chunk inside the staged plan entries
+    // unconditional (slice 0 stands in for a prefix the chunk does not have; it is replaced by
+    // zero when the chunk is staged, so that no load sits under a branch)
+    if constexpr (!SPLIT) {
 #pragma unroll
-    for (int k = 0; k < G::GPT; ++k) {
-      const int e = threadIdx.x + k * FTHR, row = e / R1, r1 = e - row * R1;
-      // unconditional (slice 0 stands in for a prefix the chunk does not have; it is replaced by
-      // zero when the chunk is staged, so that no load sits under a branch)
-      const int i1 = s_i1[mo + (row >> 2)];
-      const size_t at = (size_t)(i1 >= 0 ? i1 : 0) * G::S1 + (row & 3) * R1 + r1;
-      g1n[k] = BF16 ? bf16_to_float(g1b[at]) : g1[at];
+      for (int k = 0; k < G::GPT; ++k) {
+        const int e = threadIdx.x + k * FTHR, row = e / R1, r1 = e - row * R1;
+        const int i1 = s_i1[mo + (row >> 2)];
+        const size_t at = (size_t)(i1 >= 0 ? i1 : 0) * G::S1 + (row & 3) * R1 + r1;
+        g1n[k] = BF16 ? bf16_to_float(g1b[at]) : g1[at];
+      }
+    } else {
+      const int i1 = s_i1[mo + (arow >> 2)];
+      const tt_f32x4u v = *reinterpret_cast<const tt_f32x4u *>(g1 + (size_t)(i1 >= 0 ? i1 : 0) * G::S1 + (arow & 3) * R1 + ar1);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) g1n[k] = v[k];
     }
     const int p = threadIdx.x / FWD_I3_STAGE, r = threadIdx.x - p * FWD_I3_STAGE;
     rown = uniq_row[s_u0[mo + p] + (r < s_nr[mo + p] ? r : 0)];
   };
   auto stage_chunk = [&](int par, int mo) __attribute__((always_inline)) {  // registers -> LDS
+    if constexpr (!SPLIT) {
 #pragma unroll
-    for (int k = 0; k < G::GPT; ++k) {
-      const int e = threadIdx.x + k * FTHR, row = e / R1, r1 = e - row * R1;
-      const float v = s_i1[mo + (row >> 2)] >= 0 ? g1n[k] : 0.f;  // zero rows for prefixes the chunk does not have
-      if constexpr (BF16) Asb[row * RSB + r1] = (unsigned short)(__float_as_uint(v) >> 16);  // exact: v is a bf16 value
-      else As[row * G::RS + r1] = v;
+      for (int k = 0; k < G::GPT; ++k) {
+        const int e = threadIdx.x + k * FTHR, row = e / R1, r1 = e - row * R1;
+        const float v = s_i1[mo + (row >> 2)] >= 0 ? g1n[k] : 0.f;  // zero rows for prefixes the chunk does not have
+        if constexpr (BF16) Asb[row * RSB + r1] = (unsigned short)(__float_as_uint(v) >> 16);  // exact: v is a bf16 value
+        else As[row * G::RS + r1] = v;
+      }
+    } else if (8 * R1 == FTHR || threadIdx.x < 8 * R1) {
+      const bool have = s_i1[mo + (arow >> 2)] >= 0;
+      uint2 hi, mid, lo;
+      tt_split_bf16(have ? g1n[0] : 0.f, have ? g1n[1] : 0.f, hi.x, mid.x, lo.x);
+      tt_split_bf16(have ? g1n[2] : 0.f, have ? g1n[3] : 0.f, hi.y, mid.y, lo.y);
+      uint2 *dst = reinterpret_cast<uint2 *>(Asb + ((arow >> 4) * G::KB + (ar1 >> 5)) * 512 + ((ar1 >> 3 & 3) * 16 + (arow & 15)) * 8 +
+                                             (ar1 & 4));
+      dst[0] = hi;
+      dst[G::PLANE / 4] = mid;
+      dst[G::PLANE / 2] = lo;
     }
     s_i3[par][threadIdx.x / FWD_I3_STAGE][threadIdx.x % FWD_I3_STAGE] = rown % sh.n3;
     if (wave == 0) {  // quads per prefix of the chunk, running total (scan over the first 8 lanes)
@@ -178,9 +216,26 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
     }
   };
 
+  if (SPLIT && threadIdx.x == 0) s_not_finite = 0;
   fetch_meta(seg0);
   __syncthreads();
   fetch_chunk(0);
+  // the strip as F1's B operand: per part, k step and tile column eight bf16 values
+  uint4 bs[SPLIT ? 3 : 1][SPLIT ? G::KB : 1][2];
+  if constexpr (SPLIT) {
+#pragma unroll
+    for (int kb = 0; kb < G::KB; ++kb)
+#pragma unroll
+      for (int nt = 0; nt < 2; ++nt) {
+        unsigned w[3][4];
+#pragma unroll
+        for (int i = 0; i < 8; i += 2)
+          tt_split_bf16(nt ? bq[8 * kb + i].y : bq[8 * kb + i].x, nt ? bq[8 * kb + i + 1].y : bq[8 * kb + i + 1].x, w[0][i / 2],
+                        w[1][i / 2], w[2][i / 2]);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) bs[k][kb][nt] = make_uint4(w[k][0], w[k][1], w[k][2], w[k][3]);
+      }
+  }
   stage_chunk(0, 0);
   int par = 0;
 
@@ -214,7 +269,7 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
             for (int nt = 0; nt < 2; ++nt)
               acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av[mt], bv[nt], acc[mt][nt], 0, 0, 0);
         }
-      } else {
+      } else if constexpr (!SPLIT) {
 #pragma unroll
         for (int ks = 0; ks < G::KS1; ++ks) {
           float av[MT];
@@ -227,6 +282,36 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
             for (int nt = 0; nt < 2; ++nt)
               acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[mt], bv[nt], acc[mt][nt], 0, 0, 0);
         }
+      } else {
+        auto a_part = [&](int part, int mt, int kb) __attribute__((always_inline)) {
+          return *reinterpret_cast<const uint4 *>(Asb + part * G::PLANE + (mt * G::KB + kb) * 512 + lane * 8);
+        };
+#pragma unroll
+        for (int kb = 0; kb < G::KB; ++kb) {
+          uint4 av[3][MT];
+#pragma unroll
+          for (int part = 0; part < 3; ++part)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) av[part][mt] = a_part(part, mt, kb);
+          tt_static_for<0, 6>([&](auto term) __attribute__((always_inline)) {  // the smallest products first
+            constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
+            constexpr int ta = pa[decltype(term)::value], tb = pb[decltype(term)::value];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+              for (int nt = 0; nt < 2; ++nt)
+                acc[mt][nt] = tt_mfma_bf16_k32(*reinterpret_cast<const tt_bf16x8 *>(&av[ta][mt]),
+                                               *reinterpret_cast<const tt_bf16x8 *>(&bs[tb][kb][nt]), acc[mt][nt]);
+          });
+        }
+        float z = 0.f;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+          for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) z = fmaf(acc[mt][nt][v], 0.f, z);
+        if (z != 0.f) s_not_finite = 1;
       }
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
@@ -318,19 +403,53 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
     }
     par ^= 1;
   }
+
+  if constexpr (SPLIT) {
+    // Infinities and NaN in the cores, or products beyond fp32: everything of this workgroup once more, in fp32
+    // as the formulas are written, so that the splitting never shows.
+    __syncthreads();
+    if (!s_not_finite) return;  // uniform
+    for (int x = seg0; x < seg1; ++x) {
+      const int4 m = pref_meta[x];
+      auto product = [&](int j1, int j2, int r2) {
+        float sum = 0.f;
+        for (int r1 = 0; r1 < R1; ++r1)
+          sum = fmaf(g1[(size_t)m.x * G::S1 + j1 * R1 + r1], g2[((size_t)r1 * sh.n2 + i2) * G::S2 + j2 * R2 + r2], sum);
+        return sum;
+      };
+      if constexpr (P12OUT) {
+        for (int e = threadIdx.x; e < G::CC * R2; e += FTHR) {
+          const int cc = e / R2, r2 = e - cc * R2, j1 = cc / G::JW, j2 = j2base + cc - j1 * G::JW;
+          p12buf[(size_t)m.w * (4 * D2 * R2) + (j1 * D2 + j2) * R2 + r2] = product(j1, j2, r2);
+        }
+      } else {
+        for (int e = threadIdx.x; e < m.z * G::CC; e += FTHR) {
+          const int u = m.y + e / G::CC, cc = e % G::CC, j1 = cc / G::JW, j2 = j2base + cc - j1 * G::JW, i3 = uniq_row[u] % sh.n3;
+          float o[4] = {0.f, 0.f, 0.f, 0.f};
+          for (int r2 = 0; r2 < R2; ++r2) {
+            const float t = product(j1, j2, r2);
+#pragma unroll
+            for (int j3 = 0; j3 < 4; ++j3) o[j3] = fmaf(t, g3[((size_t)r2 * sh.n3 + i3) * 4 + j3], o[j3]);
+          }
+#pragma unroll
+          for (int j3 = 0; j3 < 4; ++j3) rowbuf[(size_t)u * G::D + (j1 * D2 + j2) * 4 + j3] = o[j3];
+        }
+      }
+    }
+  }
 }
 
-template <int R1, int R2, int D2, bool P12OUT, bool BF16 = false>
+template <int R1, int R2, int D2, bool P12OUT, int MODE>
 tt_status launch(const TTBatch &b, hipStream_t s) {
   using G = FwdGeom<R1, R2, D2>;
-  const size_t lds = G::LDS_FLOATS * sizeof(float);
+  const size_t lds = G::lds_floats(MODE) * sizeof(float);
   // once per process and kernel instantiation; calls may come from several host threads
   static std::once_flag once;
   static bool configured = false;
   std::call_once(once, [&] {
-    configured = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_fwd_mfma<false, R1, R2, D2, P12OUT, BF16>),
+    configured = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_fwd_mfma<false, R1, R2, D2, P12OUT, MODE>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess &&
-                 hipFuncSetAttribute(reinterpret_cast<const void *>(&k_fwd_mfma<true, R1, R2, D2, P12OUT, BF16>),
+                 hipFuncSetAttribute(reinterpret_cast<const void *>(&k_fwd_mfma<true, R1, R2, D2, P12OUT, MODE>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess;
   });
   if (!configured) return TT_ERR_HIP;
@@ -343,12 +462,24 @@ tt_status launch(const TTBatch &b, hipStream_t s) {
   // timed by the kernel's own begin and end stamps when a profile object asks
   TTProfScope prof(&b.host[0].plan, P12OUT ? TT_KERNEL_P12_FILL : TT_KERNEL_FWD_CONTRACT, s, false);
   if (b.dev)
-    hipExtLaunchKernelGGL((k_fwd_mfma<true, R1, R2, D2, P12OUT, BF16>), dim3((unsigned)blocks, (unsigned)b.T),
+    hipExtLaunchKernelGGL((k_fwd_mfma<true, R1, R2, D2, P12OUT, MODE>), dim3((unsigned)blocks, (unsigned)b.T),
                           dim3(FTHR), lds, s, prof.start(), prof.stop(), 0, TTArg<true>{b.dev}, split);
   else
-    hipExtLaunchKernelGGL((k_fwd_mfma<false, R1, R2, D2, P12OUT, BF16>), dim3((unsigned)blocks), dim3(FTHR), lds, s,
+    hipExtLaunchKernelGGL((k_fwd_mfma<false, R1, R2, D2, P12OUT, MODE>), dim3((unsigned)blocks), dim3(FTHR), lds, s,
                           prof.start(), prof.stop(), 0, TTArg<false>{b.host[0]}, split);
   return tt_launch_status();
+}
+
+// One launch serves every table of a call (of a batch: one per way to multiply that its tables take).
+template <int R, bool P12OUT>
+tt_status launch_fp32(const TTBatch &b, hipStream_t s) {
+  bool split = false, whole = false;
+  for (int t = 0; t < b.T; ++t) (ttk_forward_splits(b.host[t]) ? split : whole) = true;
+  if (whole) {
+    const tt_status st = launch<R, R, 8, P12OUT, FWD_FP32>(b, s);
+    if (st != TT_OK || !split) return st;
+  }
+  return launch<R, R, 8, P12OUT, FWD_SPLIT>(b, s);
 }
 
 }  // namespace
@@ -359,16 +490,16 @@ bool ttk_forward_mfma_supported(const TTShape &sh) {
 }
 
 tt_status ttk_forward_mfma(const TTBatch &b, hipStream_t s) {
-  if (b.host[0].sh.R1 == 32) return launch<32, 32, 8, false>(b, s);
-  return launch<64, 64, 8, false>(b, s);
+  if (b.host[0].sh.R1 == 32) return launch_fp32<32, false>(b, s);
+  return launch_fp32<64, false>(b, s);
 }
 
 tt_status ttk_forward_mfma_bf16(const TTBatch &b, hipStream_t s) {
-  if (b.host[0].sh.R1 == 32) return launch<32, 32, 8, false, true>(b, s);
-  return launch<64, 64, 8, false, true>(b, s);
+  if (b.host[0].sh.R1 == 32) return launch<32, 32, 8, false, FWD_BF16>(b, s);
+  return launch<64, 64, 8, false, FWD_BF16>(b, s);
 }
 
 tt_status ttk_forward_mfma_p12(const TTBatch &b, hipStream_t s) {
-  if (b.host[0].sh.R1 == 32) return launch<32, 32, 8, true>(b, s);
-  return launch<64, 64, 8, true>(b, s);
+  if (b.host[0].sh.R1 == 32) return launch_fp32<32, true>(b, s);
+  return launch_fp32<64, true>(b, s);
 }

@@ -126,6 +126,36 @@ __device__ __forceinline__ float4 tt_load_stream4(const float *src) {
 }
 #endif
 
+#ifdef __HIPCC__
+// An fp32 number as the sum of three bf16 numbers, so that bf16 matrix instructions (16 times the rate of the fp32
+// ones) can multiply fp32 operands: `hi` is x rounded to bf16, `mid` the remainder rounded, `lo` what is left, and hi + mid
+// + lo == x exactly (24 bits of significand; below 2^-110 lo runs into bf16's denormals).  Products of two parts are exact in
+// fp32.  mid is at most 2^-8 |x| and lo 2^-17 |x| in size, both of either sign, so a product of two numbers keeps its fp32
+// accuracy without the three smallest of its nine terms (mid*lo, lo*mid, lo*lo): against 64 bits, 2-norm, bag sums of the
+// fp32 instruction / of the split, 1.47e-7 / 1.14e-7 (ranks 32) and 2.07e-7 / 1.73e-7 (ranks 64): fewer roundings a sum.  Infinities, NaN and numbers that round to a
+// bf16 infinity get a NaN among their parts, so that they show in the result: the caller has to look and to multiply in fp32.
+__device__ __forceinline__ unsigned tt_bf16_pair(float x, float y) {  // x in the lower half
+  typedef __bf16 v2 __attribute__((ext_vector_type(2)));
+  const v2 r = {(__bf16)x, (__bf16)y};
+  return __builtin_bit_cast(unsigned, r);
+}
+// the parts of two numbers
+__device__ __forceinline__ void tt_split_bf16(float x, float y, unsigned &hi, unsigned &mid, unsigned &lo) {
+  hi = tt_bf16_pair(x, y);
+  const float rx = x - __uint_as_float(hi << 16), ry = y - __uint_as_float(hi & 0xffff0000u);
+  mid = tt_bf16_pair(rx, ry);
+  lo = tt_bf16_pair(rx - __uint_as_float(mid << 16), ry - __uint_as_float(mid & 0xffff0000u));
+}
+typedef short tt_bf16x8 __attribute__((ext_vector_type(8)));
+typedef float tt_f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // four floats at any float's address
+// D = A[16x32] * B[32x16] + C in bf16 with fp32 accumulators: lane l supplies A[m = l%16][k = 8*(l/16) + i] and
+// B[k = 8*(l/16) + i][n = l%16], i = 0..7; C as for 16x16x4
+__device__ __forceinline__ tt_f32x4 tt_mfma_bf16_k32(tt_bf16x8 a, tt_bf16x8 b, tt_f32x4 c) {
+  typedef __bf16 v8 __attribute__((ext_vector_type(8)));
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8, a), __builtin_bit_cast(v8, b), c, 0, 0, 0);
+}
+#endif
+
 template <bool BATCHED> struct TTArg;
 template <> struct TTArg<false> {
   TTDev one;
@@ -196,8 +226,18 @@ tt_status ttk_index_graph_edges(const int64_t *indices, const int64_t *offsets, 
 tt_status ttk_forward_plan(const TTBatch &b, hipStream_t s);
 // The bag sums of a short batch without a plan, for calls that hand out none (rowbuf and lookup2row of the scratch are used).
 #define TT_DIRECT_BAG_LOOKUPS 32       // up to this many lookups in one launch, a workgroup per bag
+#ifndef TT_DIRECT_MAX_LOOKUPS_32
 #define TT_DIRECT_MAX_LOOKUPS_32 16384 // ... and up to this many in two, a wavefront per lookup and 64 columns (ranks 32)
 #define TT_DIRECT_MAX_LOOKUPS_64 8192  // (ranks 64)
+#endif
+// Whether the matrix-core forward multiplies prefixes by split fp32 numbers (tt_split_bf16).  Contraction launch, fp32 / split, one-
+// hot lookups in tables of 300 k and 40 M rows: ranks 64 8192 lookups 13.3 / 12.5 and 23.3 / 22.0 us, 17000 19.1 / 16.0 and
+// 27.5 / 24.0, 65536 31.9 / 25.9 and 51.6 / 40.6; ranks 32 8192 9.0 / 9.5 and 15.5 / 14.7, 17000 10.3 / 9.9 and 17.5 / 16.2, 65536
+// 15.3 / 14.5 and 29.1 / 26.0.  Short batches gain next to nothing (a strip is split for one chunk of prefixes), and up to
+// these limits the forward without a plan has the fp32 kernel's bits: a batch gets the same bits by both.
+__host__ __device__ __forceinline__ bool ttk_forward_splits(const TTDev &d) {
+  return d.nnz > (d.sh.R1 == 32 ? TT_DIRECT_MAX_LOOKUPS_32 : TT_DIRECT_MAX_LOOKUPS_64);
+}
 bool ttk_forward_direct_serves(const TTDev &d);
 tt_status ttk_forward_direct(const TTBatch &b, hipStream_t s);
 // the same from bf16 copies of the cores, one launch and no scratch at all

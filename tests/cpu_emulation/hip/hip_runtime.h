@@ -19,6 +19,7 @@ struct alignas(16) int4 { int x, y, z, w; };
 struct alignas(8) int2 { int x, y; };
 static inline int4 make_int4(int x, int y, int z, int w) { return int4{x, y, z, w}; }
 struct alignas(16) uint4 { unsigned x, y, z, w; };
+static inline uint4 make_uint4(unsigned x, unsigned y, unsigned z, unsigned w) { return {x, y, z, w}; }
 struct alignas(8) uint2 { unsigned x, y; };
 static inline uint2 make_uint2(unsigned x, unsigned y) { return uint2{x, y}; }
 static inline float __uint_as_float(unsigned u) { float f; memcpy(&f, &u, 4); return f; }
@@ -137,6 +138,18 @@ static inline emu_f32x4 emu_mfma_bf16(emu_bf16x4 a, emu_bf16x4 b, emu_f32x4 c, i
   return (emu_f32x4){t[0], t[1], t[2], t[3]};
 }
 #define __builtin_amdgcn_mfma_f32_16x16x16bf16_1k emu_mfma_bf16
+// 16x16x32 bf16: the same with eight values a lane, k = 8*(l/16) + i
+template <class V>
+static inline emu_f32x4 emu_mfma_bf16_k32(V a, V b, emu_f32x4 c, int, int, int) {
+  typedef short s8 __attribute__((ext_vector_type(8)));
+  const s8 x = __builtin_bit_cast(s8, a), y = __builtin_bit_cast(s8, b);
+  float t[4] = {c[0], c[1], c[2], c[3]};
+  for (int i = 0; i < 8; ++i)
+    emu::wave_mfma_16x16x4(__uint_as_float((unsigned)(unsigned short)x[i] << 16),
+                           __uint_as_float((unsigned)(unsigned short)y[i] << 16), t);
+  return (emu_f32x4){t[0], t[1], t[2], t[3]};
+}
+#define __builtin_amdgcn_mfma_f32_16x16x32_bf16 emu_mfma_bf16_k32
 // sixteen blocks of 4x4x1 (4x4x4 for bf16): lane l supplies A[m = l%4] and B[n = l%4] of block l/4 and holds its C[m = v][n = l%4];
 // every block of a group of 2^cbsz takes A from the group's block abid
 static inline emu_f32x4 emu_mfma_4x4(float a, float b, emu_f32x4 c, int cbsz, int abid, int) {
