@@ -511,7 +511,8 @@ __host__ __device__ __forceinline__ WholeSplit whole_split(int W, int vec, int w
 }
 __host__ __device__ __forceinline__ int whole_want3(int n3) { return (512 + n3 - 1) / n3; }
 
-template <bool BATCHED, int VEC>
+// ROUNDS: up to two strips a prefix.
+template <bool BATCHED, int VEC, bool ROUNDS>
 __global__ void __launch_bounds__(TT_BLOCK)
 k_seg_whole(TTArg<BATCHED> arg, int blocks_a) {
   const TTDev &d = arg.get();
@@ -538,6 +539,47 @@ k_seg_whole(TTArg<BATCHED> arg, int blocks_a) {
     }
     return;
   }
+  // Sum of this lane group's positions, columns e ..., NS vectors a position.  A round is a chain of two loads (gather index,
+  // vector): the next round's indices are requested with this round's vectors, and the positions left over at the end are one
+  // round, not one each.  Whole launches, one left-over position after the other / this: multi-hot at ranks 32 (two strips)
+  // 12.5 / 9.4 us, ranks 12 and 20 6.8 / 5.9.
+  auto positions = [&](auto ns, int e, Vec<VEC> &acc) {
+    constexpr int NS = decltype(ns)::value, U = TT_SEG_WHOLE_UNROLL;
+    int row[U];  // -1: past the end
+    auto rows_at = [&](int pos) {
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        const int p = pos + k * groups;
+        row[k] = p >= b ? -1 : (gidx ? gidx[p] : p);
+      }
+    };
+    rows_at(a + g);
+    for (int pos = a + g; pos < b; pos += U * groups) {
+      Vec<VEC> x[U][NS];
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+#pragma unroll
+        for (int t = 0; t < NS; ++t) {
+          x[k][t].zero();
+          if (row[k] >= 0) x[k][t].load_stream(src + ((size_t)row[k] * NS + t) * W + e0 + e);  // hand-off buffers: read once
+        }
+      }
+      rows_at(pos + U * groups);
+#pragma unroll
+      for (int k = 0; k < U; ++k)
+#pragma unroll
+        for (int t = 1; t < NS; ++t) x[k][0].add(x[k][t]);
+      // in pairs, then into the running sum: a chain of a quarter of the additions, and of their rounding errors
+#pragma unroll
+      for (int w = 1; w < U; w <<= 1)
+#pragma unroll
+        for (int k = 0; k < U; k += 2 * w) x[k][0].add(x[k + w][0]);
+      acc.add(x[0][0]);
+    }
+  };
+  // The same for four strips a position (ranks 64): sixteen vectors in flight halve the wavefronts a compute unit holds, which
+  // costs the many short segments of fused tables more than it gives (nine tables at batch 4096 19.5 us a launch, 25 in rounds
+  // of sixteen, 22 in rounds of eight; one table 18.2, 17.6 and 18.8).
   auto load_pos = [&](int pos, int e, Vec<VEC> &x) {
     const int row = gidx ? gidx[pos] : pos;
     x.load_stream(src + (size_t)row * nsub * W + e0 + e);  // hand-off buffers: every vector is read once
@@ -550,22 +592,26 @@ k_seg_whole(TTArg<BATCHED> arg, int blocks_a) {
   for (int e = lane * VEC; e < Wp; e += lanes * VEC) {
     Vec<VEC> acc;
     acc.zero();
-    int pos = a + g;
-    for (; pos + (TT_SEG_WHOLE_UNROLL - 1) * groups < b; pos += TT_SEG_WHOLE_UNROLL * groups) {
-      Vec<VEC> x[TT_SEG_WHOLE_UNROLL];
+    if constexpr (ROUNDS) {
+      if (nsub == 1) positions(std::integral_constant<int, 1>{}, e, acc);  // uniform
+      else positions(std::integral_constant<int, 2>{}, e, acc);
+    } else {
+      int pos = a + g;
+      for (; pos + (TT_SEG_WHOLE_UNROLL - 1) * groups < b; pos += TT_SEG_WHOLE_UNROLL * groups) {
+        Vec<VEC> x[TT_SEG_WHOLE_UNROLL];
 #pragma unroll
-      for (int k = 0; k < TT_SEG_WHOLE_UNROLL; ++k) load_pos(pos + k * groups, e, x[k]);
-      // in pairs, then into the running sum: a chain of a quarter of the additions, and of their rounding errors
+        for (int k = 0; k < TT_SEG_WHOLE_UNROLL; ++k) load_pos(pos + k * groups, e, x[k]);
 #pragma unroll
-      for (int w = 1; w < TT_SEG_WHOLE_UNROLL; w <<= 1)
+        for (int w = 1; w < TT_SEG_WHOLE_UNROLL; w <<= 1)
 #pragma unroll
-        for (int k = 0; k < TT_SEG_WHOLE_UNROLL; k += 2 * w) x[k].add(x[k + w]);
-      acc.add(x[0]);
-    }
-    for (; pos < b; pos += groups) {
-      Vec<VEC> x;
-      load_pos(pos, e, x);
-      acc.add(x);
+          for (int k = 0; k < TT_SEG_WHOLE_UNROLL; k += 2 * w) x[k].add(x[k + w]);
+        acc.add(x[0]);
+      }
+      for (; pos < b; pos += groups) {
+        Vec<VEC> x;
+        load_pos(pos, e, x);
+        acc.add(x);
+      }
     }
     acc.store(red + (size_t)g * Wp + e);
   }
@@ -632,8 +678,11 @@ tt_status seg_sum_dg3_dg1(const TTBatch &b, hipStream_t s) {
     const size_t lds = sizeof(float) * (size_t)(lds3 > lds1 ? lds3 : lds1);
     const long long grid = blocks3 + blocks1;
     if (grid <= (mixed ? TT_SEG_MIXED_MAX_WGS : TT_MAX_WORKGROUPS)) {  // (millions of slices: the two-stage sum's workgroups follow the lookups)
-      if (vec == 4) TT_LAUNCH_T(k_seg_whole, 4, grid, TT_BLOCK, lds, s, b, (int)blocks3);
-      else TT_LAUNCH_T(k_seg_whole, 1, grid, TT_BLOCK, lds, s, b, (int)blocks3);
+      const bool rounds = tt_batch_max(b, [](const TTDev &d) { return (long long)d.strips; }) <= 2;
+      if (vec == 4 && rounds) TT_LAUNCH_T2(k_seg_whole, 4, true, grid, TT_BLOCK, lds, s, b, (int)blocks3);
+      else if (vec == 4) TT_LAUNCH_T2(k_seg_whole, 4, false, grid, TT_BLOCK, lds, s, b, (int)blocks3);
+      else if (rounds) TT_LAUNCH_T2(k_seg_whole, 1, true, grid, TT_BLOCK, lds, s, b, (int)blocks3);
+      else TT_LAUNCH_T2(k_seg_whole, 1, false, grid, TT_BLOCK, lds, s, b, (int)blocks3);
       return tt_launch_status();
     }
   }

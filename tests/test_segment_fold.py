@@ -32,3 +32,32 @@ def test_chunk_per_lane_group_equals_chunk_per_workgroup(routes, n, d, r, nb, ml
     a, b = (te._run(lib, shape, cores, idx, off, grad, 0.05) for lib in routes)
     for x, y in zip(a["plan"][1] + a["fused"] + a["updated"], b["plan"][1] + b["fused"] + b["updated"]):
         assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("r", [32, 64])
+def test_core_sums_into_unaligned_gradients(r):
+    """Two and four strips a prefix with four-byte stores (gradient buffers off the 16-byte grid): whole segments by rounds and
+    one position after the other, as the aligned sums up to the order of additions."""
+    lib, binding = te._load(te.emu_build.build_shared(te.BUILD_DIR))
+    shape, cores, idx, off, grad = wl.small_random_problem(31, n=(3, 5, 7), d=(4, 8, 4), r=(1, r, r, 1), num_bags=60, max_len=3, sigma=0.2)
+    cores = [np.ascontiguousarray(c, dtype=np.float32) for c in cores]
+    aligned = [te._aligned(4 * c.size).view(np.float32) for c in cores]
+    for a, c in zip(aligned, cores):
+        a[:] = c
+    idx, off = np.ascontiguousarray(idx, dtype=np.int64), np.ascontiguousarray(off, dtype=np.int64)
+    grad = np.ascontiguousarray(grad, dtype=np.float32)
+    nnz, nb = len(idx), len(off) - 1
+    table = te._table(binding, shape, aligned)
+    ws = te._aligned(lib.tt_workspace_bytes(ctypes.byref(table), nnz, nb))
+    plan = binding.CPlan()
+    assert lib.tt_index_reorder(ctypes.byref(table), te._ptr(idx), te._ptr(off), nnz, nb, None, te._ptr(ws), ws.nbytes,
+                                ctypes.byref(plan), None) == 0
+    got = []
+    for shift in (0, 1):
+        dg = [te._aligned(4 * c.size + 16).view(np.float32)[shift:shift + c.size] for c in cores]
+        arr = (ctypes.c_void_p * 3)(*[x.ctypes.data for x in dg])
+        assert lib.tt_emb_bag_backward(ctypes.byref(table), ctypes.byref(plan), te._ptr(idx), te._ptr(off), nnz, nb, te._ptr(grad),
+                                       arr, None) == 0
+        got.append([x.copy() for x in dg])
+    for x, y in zip(*got):
+        assert np.allclose(x, y, rtol=0, atol=1e-6 * np.abs(x).max())
