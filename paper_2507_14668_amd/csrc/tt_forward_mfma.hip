@@ -411,29 +411,28 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
     if (!s_not_finite) return;  // uniform
     for (int x = seg0; x < seg1; ++x) {
       const int4 m = pref_meta[x];
-      auto product = [&](int j1, int j2, int r2) {
+      for (int e = threadIdx.x; e < G::CC * R2; e += FTHR) {  // the prefix's products -> P12s[(j1, j2)][r2], or the reuse buffer
+        const int cc = e / R2, r2 = e - cc * R2, j1 = cc / G::JW, j2 = j2base + cc - j1 * G::JW;
         float sum = 0.f;
+#pragma unroll 8
         for (int r1 = 0; r1 < R1; ++r1)
           sum = fmaf(g1[(size_t)m.x * G::S1 + j1 * R1 + r1], g2[((size_t)r1 * sh.n2 + i2) * G::S2 + j2 * R2 + r2], sum);
-        return sum;
-      };
-      if constexpr (P12OUT) {
-        for (int e = threadIdx.x; e < G::CC * R2; e += FTHR) {
-          const int cc = e / R2, r2 = e - cc * R2, j1 = cc / G::JW, j2 = j2base + cc - j1 * G::JW;
-          p12buf[(size_t)m.w * (4 * D2 * R2) + (j1 * D2 + j2) * R2 + r2] = product(j1, j2, r2);
-        }
-      } else {
+        if constexpr (P12OUT) p12buf[(size_t)m.w * (4 * D2 * R2) + (j1 * D2 + j2) * R2 + r2] = sum;
+        else P12s[cc * G::Rp + r2] = sum;
+      }
+      if constexpr (!P12OUT) {
+        __syncthreads();
         for (int e = threadIdx.x; e < m.z * G::CC; e += FTHR) {
           const int u = m.y + e / G::CC, cc = e % G::CC, j1 = cc / G::JW, j2 = j2base + cc - j1 * G::JW, i3 = uniq_row[u] % sh.n3;
           float o[4] = {0.f, 0.f, 0.f, 0.f};
-          for (int r2 = 0; r2 < R2; ++r2) {
-            const float t = product(j1, j2, r2);
+#pragma unroll 4
+          for (int r2 = 0; r2 < R2; ++r2)
 #pragma unroll
-            for (int j3 = 0; j3 < 4; ++j3) o[j3] = fmaf(t, g3[((size_t)r2 * sh.n3 + i3) * 4 + j3], o[j3]);
-          }
+            for (int j3 = 0; j3 < 4; ++j3) o[j3] = fmaf(P12s[cc * G::Rp + r2], g3[((size_t)r2 * sh.n3 + i3) * 4 + j3], o[j3]);
 #pragma unroll
           for (int j3 = 0; j3 < 4; ++j3) rowbuf[(size_t)u * G::D + (j1 * D2 + j2) * 4 + j3] = o[j3];
         }
+        __syncthreads();  // the next prefix's products take the place of this one's
       }
     }
   }
