@@ -277,18 +277,21 @@ k_seg_stage1(TTArg<BATCHED> arg, SegLaunch L, int lanes) {
 // slot-0 partials of the following chunks, in chunk order.  What a workgroup costs is its chain of dependent loads
 // (segment id, segment range, partials), whatever it adds.
 //   Workgroup per chunk: the shortest chain, as long as the chip holds them in about two rounds.
-//   Lane group per chunk (`spread`): most owners add two vectors, which a lane group does by itself, so that
-// many chunks are through in one round.  Segments of many partials are left to all lane groups of the workgroup; those
+//   Lane group per chunk (SPREAD, and the kind's `spread`): most owners add two vectors, which a lane group does by itself, so
+// that many chunks are through in one round.  Segments of many partials are left to all lane groups of the workgroup; those
 // are the hot rows, neighbours in sorted order where ids are not permuted, so the chunks of a workgroup lie a grid
-// apart and no workgroup gets many of them.
+// apart and no workgroup gets many of them.  A kernel of its own: it needs more registers (73 against 46) and a list in LDS.
 // Stage 2 of the gradient merge at D = 128, per chunk / spread: 1125 chunks 5.0 / 6.6 us, 4600 8.3 / 9.8, 8192 10.1 / 8.4,
 // 10500 13.1 / 11.1, 12800 15.3 / 11.0; the sums are the same bit for bit.
 // With `dense`, workgroup (lane group) c also zero-fills segment c if it is empty.
-// LDS: red[groups][W]
+// LDS: red[groups][W], with SPREAD | long[groups] | count
 #ifndef TT_SEG2_SPREAD_CHUNKS
 #define TT_SEG2_SPREAD_CHUNKS 6144  // chunks above which a lane group takes one
 #endif
-template <bool BATCHED, int VEC>
+static size_t seg2_lds_bytes(int groups, int W, bool spread) {
+  return sizeof(float) * (size_t)groups * W + (spread ? sizeof(int) * (size_t)(groups + 1) : 0);
+}
+template <bool BATCHED, int VEC, bool SPREAD>
 __global__ void __launch_bounds__(TT_BLOCK)
 k_seg_stage2(TTArg<BATCHED> arg, SegLaunch L, int lanes) {
   const SegPick pk = seg_pick(L, arg.get());
@@ -298,11 +301,19 @@ k_seg_stage2(TTArg<BATCHED> arg, SegLaunch L, int lanes) {
   const int32_t *__restrict__ seg_src = sv.seg_src, *__restrict__ seg_off = sv.seg_off;
   float *__restrict__ out = sv.out;
   const float *__restrict__ partial = sv.partial + pk.poff;
-  extern __shared__ __align__(16) float red[];  // (16: it lies behind the static arrays)
+  extern __shared__ float red[];
   const int M = *sv.count_ptr;
   const int nchunks = (M + chunk - 1) / chunk;
   const int groups = blockDim.x / lanes, g = threadIdx.x / lanes, lane = threadIdx.x - g * lanes;
   const int gc = groups * chunk;
+  const bool spread = SPREAD && pk.spread;
+  const int mine = pk.bid + (spread ? g * pk.nblk : 0);
+  if (dense && (spread || g == 0) && mine < nseg && seg_off[mine] == seg_off[mine + 1]) {
+    Vec<VEC> z;
+    z.zero();
+    for (int e = lane * VEC; e < W; e += lanes * VEC)
+      z.store(out + seg_out_index(mine, e, out_inner, nseg));
+  }
   // Partials to add for the segment that chunk c owns: slot 0 of the chunks c+1 .. c1, except that stage 1
   // has left ONE partial (in the first chunk) for every run of `groups` chunks handled by one workgroup
   // that lies strictly inside the segment: the runs B0 .. B1.  Units in order: single chunks before the
@@ -313,9 +324,7 @@ k_seg_stage2(TTArg<BATCHED> arg, SegLaunch L, int lanes) {
       return u < nh ? c + 1 + u : (u < nh + nm ? (B0 + (u - nh)) * groups : (B1 + 1) * groups + (u - nh - nm));
     }
   };
-  __shared__ int s_long;
-  __shared__ Units s_list[TT_BLOCK];  // spread: segments left to the whole workgroup
-  auto units_of = [&](int c) {
+  auto units_of = [&](int c) __attribute__((always_inline)) {
     Units k;
     const int lo = c * chunk, hi = lo + chunk, end = hi < M ? hi : M;
     k.c = c;
@@ -332,12 +341,12 @@ k_seg_stage2(TTArg<BATCHED> arg, SegLaunch L, int lanes) {
     k.n = a >= lo && b > hi ? k.nh + k.nm + nt : 0;
     return k;
   };
-  auto finish = [&](const Vec<VEC> &acc, int s, int e) {
+  auto finish = [&](const Vec<VEC> &acc, int s, int e) __attribute__((always_inline)) {
     float *dst = out + seg_out_index(s, e, out_inner, nseg);
     if (sv.fused) acc.store_sgd(dst, sv.lr); else acc.store(dst);
   };
   // One segment by all lane groups: they take the units round-robin, their sums are added in group order.
-  auto fold = [&](const Units &k) {
+  auto fold = [&](const Units &k) __attribute__((always_inline)) {
     for (int e = lane * VEC; e < W; e += lanes * VEC) {
       Vec<VEC> acc;
       acc.zero();
@@ -369,45 +378,40 @@ k_seg_stage2(TTArg<BATCHED> arg, SegLaunch L, int lanes) {
       }
     }
   };
-  const int mine = pk.bid + (pk.spread ? g * pk.nblk : 0);
-  if (dense && (pk.spread || g == 0) && mine < nseg && seg_off[mine] == seg_off[mine + 1]) {
-    Vec<VEC> z;
-    z.zero();
-    for (int e = lane * VEC; e < W; e += lanes * VEC)
-      z.store(out + seg_out_index(mine, e, out_inner, nseg));
-  }
-  if (!pk.spread) {  // uniform
+  if (!spread) {  // uniform
     if (mine >= nchunks) return;
     const Units k = units_of(mine);
     if (k.n > 0) fold(k);
     return;
   }
-  if (threadIdx.x == 0) s_long = 0;
-  __syncthreads();
-  if (mine < nchunks) {
-    const Units k = units_of(mine);
-    if (k.n > TT_SEG2_UNROLL || k.n > groups) {
-      if (lane == 0) s_list[atomicAdd(&s_long, 1)] = k;  // (segments are independent: their order does not matter)
-    } else if (k.n > 0) {
-      for (int e = lane * VEC; e < W; e += lanes * VEC) {
-        Vec<VEC> acc, x[TT_SEG2_UNROLL];
-        acc.load(partial + ((size_t)mine * 2 + 1) * W + e);
+  if constexpr (SPREAD) {
+    int *longs = reinterpret_cast<int *>(red + (size_t)groups * W), *nlongs = longs + groups;  // chunks left to the whole workgroup
+    if (threadIdx.x == 0) *nlongs = 0;
+    __syncthreads();
+    if (mine < nchunks) {
+      const Units k = units_of(mine);
+      if (k.n > TT_SEG2_UNROLL || k.n > groups) {
+        if (lane == 0) longs[atomicAdd(nlongs, 1)] = mine;  // (segments are independent: their order does not matter)
+      } else if (k.n > 0) {
+        for (int e = lane * VEC; e < W; e += lanes * VEC) {
+          Vec<VEC> acc, x[TT_SEG2_UNROLL];
+          acc.load(partial + ((size_t)mine * 2 + 1) * W + e);
 #pragma unroll
-        for (int u = 0; u < TT_SEG2_UNROLL; ++u)
-          if (u < k.n) x[u].load(partial + ((size_t)k.chunk_of(u, groups) * 2) * W + e);
+          for (int u = 0; u < TT_SEG2_UNROLL; ++u)
+            if (u < k.n) x[u].load(partial + ((size_t)k.chunk_of(u, groups) * 2) * W + e);
 #pragma unroll
-        for (int u = 0; u < TT_SEG2_UNROLL; ++u)
-          if (u < k.n) acc.add(x[u]);
-        finish(acc, k.seg, e);
+          for (int u = 0; u < TT_SEG2_UNROLL; ++u)
+            if (u < k.n) acc.add(x[u]);
+          finish(acc, k.seg, e);
+        }
       }
     }
-  }
-  __syncthreads();
-  const int nlong = s_long;
-  for (int i = 0; i < nlong; ++i) {  // uniform
-    const Units k = s_list[i];
-    fold(k);
     __syncthreads();
+    const int n = *nlongs;
+    for (int i = 0; i < n; ++i) {  // uniform
+      fold(units_of(longs[i]));
+      __syncthreads();
+    }
   }
 }
 
@@ -450,7 +454,8 @@ static SegParams seg_params(const TTBatch &b, int kind, int chunk) {
   p.blocks1 = tt_ceil_div(p.nchunks, p.groups);
   if (p.blocks1 > 8192) p.blocks1 = 8192;
   p.blocks2 = p.nchunks > max_seg ? p.nchunks : max_seg;  // dense kinds also zero-fill empty segments
-  p.spread = p.nchunks > TT_SEG2_SPREAD_CHUNKS;
+  // (the sums of the widest core-0 slices take 64 KB of LDS by themselves, the most that any kernel here asks for)
+  p.spread = p.nchunks > TT_SEG2_SPREAD_CHUNKS && seg2_lds_bytes(p.groups, p.W, true) <= 65536;
   if (p.spread) p.blocks2 = tt_ceil_div(p.blocks2, p.groups);
   return p;
 }
@@ -470,8 +475,12 @@ static tt_status seg_launch(const TTBatch &b, const SegParams &pa, int kind, con
   L2.blocks = (int)pa.blocks2;
   const long long g2 = pa.blocks2 + (pb ? pb->blocks2 : 0);
   if (g2 > 0) {
-    if (pa.vec == 4) TT_LAUNCH_T(k_seg_stage2, 4, g2, TT_BLOCK, lds, s, b, L2, pa.lanes);
-    else TT_LAUNCH_T(k_seg_stage2, 1, g2, TT_BLOCK, lds, s, b, L2, pa.lanes);
+    const bool spread = L2.spread || L2.spread_b;
+    const size_t lds2 = seg2_lds_bytes(pa.groups, pa.W, spread);
+    if (pa.vec == 4 && spread) TT_LAUNCH_T2(k_seg_stage2, 4, true, g2, TT_BLOCK, lds2, s, b, L2, pa.lanes);
+    else if (pa.vec == 4) TT_LAUNCH_T2(k_seg_stage2, 4, false, g2, TT_BLOCK, lds2, s, b, L2, pa.lanes);
+    else if (spread) TT_LAUNCH_T2(k_seg_stage2, 1, true, g2, TT_BLOCK, lds2, s, b, L2, pa.lanes);
+    else TT_LAUNCH_T2(k_seg_stage2, 1, false, g2, TT_BLOCK, lds2, s, b, L2, pa.lanes);
   }
   return tt_launch_status();
 }
