@@ -18,11 +18,17 @@
 // (i2, strip) to several workgroups (each loads the strip; the outputs are per row, so nothing has
 // to be combined).
 //
-// Longer batches split F1's operands into three bf16 parts each (FWD_SPLIT): six 16x16x32 bf16 MFMAs of 8.2 ns take the place of
+// Longer batches split F1's operands into three bf16 parts each (FWD_SPLIT): eight 16x16x32 bf16 MFMAs of 8.2 ns take the place of
 // eight 16x16x4 fp32 ones of 14.4.  The strip is split once per workgroup and the core-0 tile when it is staged, so the loop has
-// no conversions.  One table with 65 k one-hot lookups at ranks 64: 53.9 -> 42.0 us a launch, nine tables fused at batch 4096: 49 ->
-// 42.3; multi-hot at ranks 32 29.0 -> 26.0, the prefix products alone 18.7 -> 16.5.  The operand tile has to lie on 16 bytes:
-// with the dynamic LDS at any float's address the 16-byte reads made it 68 us.
+// no conversions.  The products hi * hi have an accumulator of their own: they are exact, an instruction adds its 32 of them
+// nearly so, and the seven smaller terms come to them in one addition at the end, so that a sum is rounded at its full size
+// about once per instruction instead of once per term (measurements at tt_split_bf16).  One table of 40 M rows with 65 k one-
+// hot lookups at ranks 64: 58.1 -> 50.2 us a launch, of 300 k rows 31.9 -> 29.9; multi-hot at ranks 32 30.3 -> 28.5, the
+// prefix products alone 18.5 -> 17.2.  Six terms into one accumulator: 44.8 us, but sums of few non-zero
+// terms were less exact than the fp32 instruction's.  Row tiles side by side, or operands a step ahead, spill at ranks 64 (52 to 53 us).
+// Operands or products that the split does not serve send the rest of a workgroup's chunks to the fp32 instruction (all cores
+// NaN: 67 us at ranks 64 where the fp32 kernel takes 54, 31 where it takes 29 at ranks 32).
+// The operand tile has to lie on 16 bytes: with the dynamic LDS at any float's address the 16-byte reads cost a third more.
 //
 // Operand layout of __builtin_amdgcn_mfma_f32_16x16x4f32 (D = A[16x4] * B[4x16] + C):
 //   lane l supplies A[m = l%16][k = l/16] and B[k = l/16][n = l%16];
@@ -104,7 +110,9 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
   __shared__ int s_i1[FMETA], s_u0[FMETA], s_nr[FMETA], s_slot[FMETA];
   __shared__ int s_item_off[2][TT_MP + 1];
   __shared__ int s_i3[2][TT_MP][FWD_I3_STAGE];
-  __shared__ int s_not_finite;  // split: a product was not finite
+  // Split: set where a chunk (by parity: the next one is staged while this one's flag is read) has operands or products that
+  // the split does not serve.
+  __shared__ int s_unfit[2];
 
   // Workgroup index = ((i2 / 8) * (strips * split) + (strip, part)) * 8 + i2 % 8: workgroups are
   // dealt to the 8 XCDs round-robin, so all strips and parts of one i2 run on XCD i2 % 8, close in
@@ -122,18 +130,22 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
   // tile column lm stands for strip column 32*wave + 2*lm + nt.  Requested before the plan is looked at.
   float2 bq[BF16 ? 1 : G::KS1];  // (split: row 32*kb + 8*lq + i in bq[8*kb + i])
   uint4 bqb[BF16 ? R1 / 16 : 1];  // BF16: per 16 values of r1, columns 2*lm and 2*lm + 1 with four r1 each
-  if constexpr (BF16) {
+  auto load_strip = [&](auto how) __attribute__((always_inline)) {
+    constexpr int HOW = decltype(how)::value;
+    if constexpr (HOW == FWD_BF16) {
 #pragma unroll
-    for (int ks = 0; ks < R1 / 16; ++ks)
-      bqb[ks] = *reinterpret_cast<const uint4 *>(g2b + (((size_t)i2 * (R1 / 4) + 4 * ks + lq) * G::S2 + strip * 256 +
-                                                        32 * wave + 2 * lm) * 4);
-  } else {
+      for (int ks = 0; ks < R1 / 16; ++ks)
+        bqb[ks] = *reinterpret_cast<const uint4 *>(g2b + (((size_t)i2 * (R1 / 4) + 4 * ks + lq) * G::S2 + strip * 256 +
+                                                          32 * wave + 2 * lm) * 4);
+    } else {
 #pragma unroll
-    for (int ks = 0; ks < G::KS1; ++ks) {
-      const int r1 = SPLIT ? 32 * (ks >> 3) + 8 * lq + (ks & 7) : 4 * ks + lq;
-      bq[ks] = *reinterpret_cast<const float2 *>(g2 + ((size_t)r1 * sh.n2 + i2) * G::S2 + strip * 256 + 32 * wave + 2 * lm);
+      for (int ks = 0; ks < G::KS1; ++ks) {
+        const int r1 = HOW == FWD_SPLIT ? 32 * (ks >> 3) + 8 * lq + (ks & 7) : 4 * ks + lq;
+        bq[ks] = *reinterpret_cast<const float2 *>(g2 + ((size_t)r1 * sh.n2 + i2) * G::S2 + strip * 256 + 32 * wave + 2 * lm);
+      }
     }
-  }
+  };
+  load_strip(std::integral_constant<int, MODE>{});
 
   int seg0 = i2_seg[i2], seg1 = i2_seg[i2 + 1];
   if (split > 1) {  // the chunks of this (i2, strip) are dealt in contiguous runs to `split` workgroups
@@ -145,295 +157,285 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
   }
   if (seg0 == seg1) return;  // uniform: no prefix for this workgroup
 
-  // Global-memory operands of the NEXT chunk (core-0 rows, row ids of its first rows) are fetched
-  // into registers while the current chunk computes.
-  float g1n[SPLIT ? 4 : G::GPT];
-  int rown = 0;
-  auto fetch_meta = [&](int base) __attribute__((always_inline)) {  // plan entries of prefixes base .. base+63 -> LDS
-    if (threadIdx.x < FMETA) {
-      int i1 = -1, u0 = 0, nr = 0, slot = 0;
-      if (base + (int)threadIdx.x < seg1) {
-        const int4 m = pref_meta[base + threadIdx.x];  // i1, first row slot, rows, prefix slot
-        i1 = m.x; u0 = m.y; nr = m.z; slot = m.w;
-      }
-      s_i1[threadIdx.x] = i1; s_u0[threadIdx.x] = u0; s_nr[threadIdx.x] = nr; s_slot[threadIdx.x] = slot;
-    }
-  };
-  // (split: a thread holds four consecutive r1 of a row; at R1 = 32 two threads hold the same four, since a load under
-  // a branch would have to wait for the stores in front of it)
-  const int arow = (threadIdx.x & 15) + 16 * ((threadIdx.x / (4 * R1)) & 1), ar1 = 4 * ((threadIdx.x >> 4) & (R1 / 4 - 1));
-  auto fetch_chunk = [&](int mo) __attribute__((always_inline)) {  // mo = offset of the chunk inside the staged plan entries
-    // unconditional (slice 0 stands in for a prefix the chunk does not have; it is replaced by
-    // zero when the chunk is staged, so that no load sits under a branch)
-    if constexpr (!SPLIT) {
-#pragma unroll
-      for (int k = 0; k < G::GPT; ++k) {
-        const int e = threadIdx.x + k * FTHR, row = e / R1, r1 = e - row * R1;
-        const int i1 = s_i1[mo + (row >> 2)];
-        const size_t at = (size_t)(i1 >= 0 ? i1 : 0) * G::S1 + (row & 3) * R1 + r1;
-        g1n[k] = BF16 ? bf16_to_float(g1b[at]) : g1[at];
-      }
-    } else {
-      const int i1 = s_i1[mo + (arow >> 2)];
-      const tt_f32x4u v = *reinterpret_cast<const tt_f32x4u *>(g1 + (size_t)(i1 >= 0 ? i1 : 0) * G::S1 + (arow & 3) * R1 + ar1);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) g1n[k] = v[k];
-    }
-    const int p = threadIdx.x / FWD_I3_STAGE, r = threadIdx.x - p * FWD_I3_STAGE;
-    rown = uniq_row[s_u0[mo + p] + (r < s_nr[mo + p] ? r : 0)];
-  };
-  auto stage_chunk = [&](int par, int mo) __attribute__((always_inline)) {  // registers -> LDS
-    if constexpr (!SPLIT) {
-#pragma unroll
-      for (int k = 0; k < G::GPT; ++k) {
-        const int e = threadIdx.x + k * FTHR, row = e / R1, r1 = e - row * R1;
-        const float v = s_i1[mo + (row >> 2)] >= 0 ? g1n[k] : 0.f;  // zero rows for prefixes the chunk does not have
-        if constexpr (BF16) Asb[row * RSB + r1] = (unsigned short)(__float_as_uint(v) >> 16);  // exact: v is a bf16 value
-        else As[row * G::RS + r1] = v;
-      }
-    } else if (8 * R1 == FTHR || threadIdx.x < 8 * R1) {
-      const bool have = s_i1[mo + (arow >> 2)] >= 0;
-      uint2 hi, mid, lo;
-      tt_split_bf16(have ? g1n[0] : 0.f, have ? g1n[1] : 0.f, hi.x, mid.x, lo.x);
-      tt_split_bf16(have ? g1n[2] : 0.f, have ? g1n[3] : 0.f, hi.y, mid.y, lo.y);
-      uint2 *dst = reinterpret_cast<uint2 *>(Asb + ((arow >> 4) * G::KB + (ar1 >> 5)) * 512 + ((ar1 >> 3 & 3) * 16 + (arow & 15)) * 8 +
-                                             (ar1 & 4));
-      dst[0] = hi;
-      dst[G::PLANE / 4] = mid;
-      dst[G::PLANE / 2] = lo;
-    }
-    s_i3[par][threadIdx.x / FWD_I3_STAGE][threadIdx.x % FWD_I3_STAGE] = rown % sh.n3;
-    if (wave == 0) {  // quads per prefix of the chunk, running total (scan over the first 8 lanes)
-      const int q4 = lane < TT_MP ? (s_nr[mo + lane] + 3) >> 2 : 0;
-      int incl = q4;
-#pragma unroll
-      for (int o = 1; o < TT_MP; o <<= 1) {
-        const int t = __shfl_up(incl, o, TT_WAVE);
-        if (lane >= o) incl += t;
-      }
-      if (lane < TT_MP) s_item_off[par][lane] = incl - q4;
-      if (lane == TT_MP - 1) s_item_off[par][TT_MP] = incl;
-    }
-  };
-
-  if (SPLIT && threadIdx.x == 0) s_not_finite = 0;
-  fetch_meta(seg0);
-  __syncthreads();
-  fetch_chunk(0);
-  // the strip as F1's B operand: per part, k step and tile column eight bf16 values
-  uint4 bs[SPLIT ? 3 : 1][SPLIT ? G::KB : 1][2];
-  if constexpr (SPLIT) {
-#pragma unroll
-    for (int kb = 0; kb < G::KB; ++kb)
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
-        unsigned w[3][4];
-#pragma unroll
-        for (int i = 0; i < 8; i += 2)
-          tt_split_bf16(nt ? bq[8 * kb + i].y : bq[8 * kb + i].x, nt ? bq[8 * kb + i + 1].y : bq[8 * kb + i + 1].x, w[0][i / 2],
-                        w[1][i / 2], w[2][i / 2]);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) bs[k][kb][nt] = make_uint4(w[k][0], w[k][1], w[k][2], w[k][3]);
-      }
-  }
-  stage_chunk(0, 0);
-  int par = 0;
-
-  for (int cs = seg0; cs < seg1; cs += TT_MP) {
-    const int mo = (cs - seg0) % FMETA;  // this chunk's offset in s_i1 / s_u0 / s_nr
-    const bool more = cs + TT_MP < seg1, refill = mo + TT_MP == FMETA;
-    __syncthreads();  // this chunk's staging is visible; the previous chunk's readers of P12 are done
-    if (more && !refill) fetch_chunk(mo + TT_MP);  // next chunk's operands, staged after F1
-
-    // ---- F1: C[32 x 32 per wavefront] on MFMA -> P12s[p][(j1, j2)][r2] ---------------------------
-    auto f1 = [&](auto tiles) __attribute__((always_inline)) {
-      constexpr int MT = decltype(tiles)::value;
-      f32x4 acc[MT][2];
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt) acc[mt][nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
-      if constexpr (BF16) {
-#pragma unroll
-        for (int ks = 0; ks < R1 / 16; ++ks) {
-          bf16x4 av[MT], bv[2];
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt)
-            av[mt] = *reinterpret_cast<const bf16x4 *>(Asb + (16 * mt + lm) * RSB + 16 * ks + 4 * lq);
-          const uint2 b0 = make_uint2(bqb[ks].x, bqb[ks].y), b1 = make_uint2(bqb[ks].z, bqb[ks].w);
-          bv[0] = *reinterpret_cast<const bf16x4 *>(&b0);
-          bv[1] = *reinterpret_cast<const bf16x4 *>(&b1);
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt)
-              acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av[mt], bv[nt], acc[mt][nt], 0, 0, 0);
+  // The prefixes from `first` on, multiplied as `how` says.  Returns the chunk that it has to leave to the fp32 instructions, or seg1.
+  auto run = [&](auto how, const int first) __attribute__((always_inline)) -> int {
+    constexpr int HOW = decltype(how)::value;
+    // Global-memory operands of the NEXT chunk (core-0 rows, row ids of its first rows) are fetched
+    // into registers while the current chunk computes.
+    float g1n[HOW == FWD_SPLIT ? 4 : G::GPT];
+    int rown = 0;
+    auto fetch_meta = [&](int base) __attribute__((always_inline)) {  // plan entries of prefixes base .. base+63 -> LDS
+      if (threadIdx.x < FMETA) {
+        int i1 = -1, u0 = 0, nr = 0, slot = 0;
+        if (base + (int)threadIdx.x < seg1) {
+          const int4 m = pref_meta[base + threadIdx.x];  // i1, first row slot, rows, prefix slot
+          i1 = m.x; u0 = m.y; nr = m.z; slot = m.w;
         }
-      } else if constexpr (!SPLIT) {
+        s_i1[threadIdx.x] = i1; s_u0[threadIdx.x] = u0; s_nr[threadIdx.x] = nr; s_slot[threadIdx.x] = slot;
+      }
+    };
+    // (split: a thread holds four consecutive r1 of a row; at R1 = 32 two threads hold the same four, since a load under
+    // a branch would have to wait for the stores in front of it)
+    const int arow = (threadIdx.x & 15) + 16 * ((threadIdx.x / (4 * R1)) & 1), ar1 = 4 * ((threadIdx.x >> 4) & (R1 / 4 - 1));
+    auto fetch_chunk = [&](int mo) __attribute__((always_inline)) {  // mo = offset of the chunk inside the staged plan entries
+      // unconditional (slice 0 stands in for a prefix the chunk does not have; it is replaced by
+      // zero when the chunk is staged, so that no load sits under a branch)
+      if constexpr (HOW != FWD_SPLIT) {
 #pragma unroll
-        for (int ks = 0; ks < G::KS1; ++ks) {
-          float av[MT];
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) av[mt] = As[(16 * mt + lm) * G::RS + 4 * ks + lq];
-          const float bv[2] = {bq[ks].x, bq[ks].y};
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt)
-              acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[mt], bv[nt], acc[mt][nt], 0, 0, 0);
+        for (int k = 0; k < G::GPT; ++k) {
+          const int e = threadIdx.x + k * FTHR, row = e / R1, r1 = e - row * R1;
+          const int i1 = s_i1[mo + (row >> 2)];
+          const size_t at = (size_t)(i1 >= 0 ? i1 : 0) * G::S1 + (row & 3) * R1 + r1;
+          g1n[k] = BF16 ? bf16_to_float(g1b[at]) : g1[at];
         }
       } else {
-        auto a_part = [&](int part, int mt, int kb) __attribute__((always_inline)) {
-          return *reinterpret_cast<const uint4 *>(Asb + part * G::PLANE + (mt * G::KB + kb) * 512 + lane * 8);
-        };
+        const int i1 = s_i1[mo + (arow >> 2)];
+        const tt_f32x4u v = *reinterpret_cast<const tt_f32x4u *>(g1 + (size_t)(i1 >= 0 ? i1 : 0) * G::S1 + (arow & 3) * R1 + ar1);
 #pragma unroll
-        for (int kb = 0; kb < G::KB; ++kb) {
-          uint4 av[3][MT];
+        for (int k = 0; k < 4; ++k) g1n[k] = v[k];
+      }
+      const int p = threadIdx.x / FWD_I3_STAGE, r = threadIdx.x - p * FWD_I3_STAGE;
+      rown = uniq_row[s_u0[mo + p] + (r < s_nr[mo + p] ? r : 0)];
+    };
+    auto stage_chunk = [&](int par, int mo) __attribute__((always_inline)) {  // registers -> LDS
+      if constexpr (HOW != FWD_SPLIT) {
 #pragma unroll
-          for (int part = 0; part < 3; ++part)
+        for (int k = 0; k < G::GPT; ++k) {
+          const int e = threadIdx.x + k * FTHR, row = e / R1, r1 = e - row * R1;
+          const float v = s_i1[mo + (row >> 2)] >= 0 ? g1n[k] : 0.f;  // zero rows for prefixes the chunk does not have
+          if constexpr (BF16) Asb[row * RSB + r1] = (unsigned short)(__float_as_uint(v) >> 16);  // exact: v is a bf16 value
+          else As[row * G::RS + r1] = v;
+        }
+      } else if (8 * R1 == FTHR || threadIdx.x < 8 * R1) {
+        const bool have = s_i1[mo + (arow >> 2)] >= 0;
+        if (have && tt_split_smallest(tt_split_smallest(~0u, g1n[0], g1n[1]), g1n[2], g1n[3]) < TT_SPLIT_MIN) s_unfit[par] = 1;
+        uint2 hi, mid, lo;
+        tt_split_bf16(have ? g1n[0] : 0.f, have ? g1n[1] : 0.f, hi.x, mid.x, lo.x);
+        tt_split_bf16(have ? g1n[2] : 0.f, have ? g1n[3] : 0.f, hi.y, mid.y, lo.y);
+        uint2 *dst = reinterpret_cast<uint2 *>(Asb + ((arow >> 4) * G::KB + (ar1 >> 5)) * 512 + ((ar1 >> 3 & 3) * 16 + (arow & 15)) * 8 +
+                                               (ar1 & 4));
+        dst[0] = hi;
+        dst[G::PLANE / 4] = mid;
+        dst[G::PLANE / 2] = lo;
+      }
+      s_i3[par][threadIdx.x / FWD_I3_STAGE][threadIdx.x % FWD_I3_STAGE] = rown % sh.n3;
+      if (wave == 0) {  // quads per prefix of the chunk, running total (scan over the first 8 lanes)
+        const int q4 = lane < TT_MP ? (s_nr[mo + lane] + 3) >> 2 : 0;
+        int incl = q4;
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) av[part][mt] = a_part(part, mt, kb);
-          tt_static_for<0, 6>([&](auto term) __attribute__((always_inline)) {  // the smallest products first
-            constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
-            constexpr int ta = pa[decltype(term)::value], tb = pb[decltype(term)::value];
+        for (int o = 1; o < TT_MP; o <<= 1) {
+          const int t = __shfl_up(incl, o, TT_WAVE);
+          if (lane >= o) incl += t;
+        }
+        if (lane < TT_MP) s_item_off[par][lane] = incl - q4;
+        if (lane == TT_MP - 1) s_item_off[par][TT_MP] = incl;
+      }
+    };
+
+    if (HOW == FWD_SPLIT && threadIdx.x < 2) s_unfit[threadIdx.x] = 0;
+    fetch_meta(first);
+    __syncthreads();
+    fetch_chunk(0);
+    // the strip as F1's B operand: per part, k step and tile column eight bf16 values
+    uint4 bs[HOW == FWD_SPLIT ? 3 : 1][HOW == FWD_SPLIT ? G::KB : 1][2];
+    if constexpr (HOW == FWD_SPLIT) {
+      unsigned smallest = ~0u;
+#pragma unroll
+      for (int kb = 0; kb < G::KB; ++kb)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) {
+          unsigned w[3][4];
+#pragma unroll
+          for (int i = 0; i < 8; i += 2) {
+            const float x = nt ? bq[8 * kb + i].y : bq[8 * kb + i].x, y = nt ? bq[8 * kb + i + 1].y : bq[8 * kb + i + 1].x;
+            smallest = tt_split_smallest(smallest, x, y);
+            tt_split_bf16(x, y, w[0][i / 2], w[1][i / 2], w[2][i / 2]);
+          }
+#pragma unroll
+          for (int k = 0; k < 3; ++k) bs[k][kb][nt] = make_uint4(w[k][0], w[k][1], w[k][2], w[k][3]);
+        }
+      if (smallest < TT_SPLIT_MIN) s_unfit[0] = 1;
+    }
+    stage_chunk(0, 0);
+    int par = 0;
+
+    for (int cs = first; cs < seg1; cs += TT_MP) {
+      const int mo = (cs - first) % FMETA;  // this chunk's offset in s_i1 / s_u0 / s_nr
+      const bool more = cs + TT_MP < seg1, refill = mo + TT_MP == FMETA;
+      __syncthreads();  // this chunk's staging is visible; the previous chunk's readers of P12 are done
+      if (more && !refill) fetch_chunk(mo + TT_MP);  // next chunk's operands, staged after F1
+
+      // ---- F1: C[32 x 32 per wavefront] on MFMA -> P12s[p][(j1, j2)][r2] ---------------------------
+      auto f1 = [&](auto tiles) __attribute__((always_inline)) {
+        constexpr int MT = decltype(tiles)::value;
+        f32x4 acc[MT][2];
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+          for (int nt = 0; nt < 2; ++nt) acc[mt][nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        if constexpr (BF16) {
+#pragma unroll
+          for (int ks = 0; ks < R1 / 16; ++ks) {
+            bf16x4 av[MT], bv[2];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+              av[mt] = *reinterpret_cast<const bf16x4 *>(Asb + (16 * mt + lm) * RSB + 16 * ks + 4 * lq);
+            const uint2 b0 = make_uint2(bqb[ks].x, bqb[ks].y), b1 = make_uint2(bqb[ks].z, bqb[ks].w);
+            bv[0] = *reinterpret_cast<const bf16x4 *>(&b0);
+            bv[1] = *reinterpret_cast<const bf16x4 *>(&b1);
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
               for (int nt = 0; nt < 2; ++nt)
-                acc[mt][nt] = tt_mfma_bf16_k32(*reinterpret_cast<const tt_bf16x8 *>(&av[ta][mt]),
-                                               *reinterpret_cast<const tt_bf16x8 *>(&bs[tb][kb][nt]), acc[mt][nt]);
-          });
+                acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av[mt], bv[nt], acc[mt][nt], 0, 0, 0);
+          }
+        } else if constexpr (HOW != FWD_SPLIT) {
+#pragma unroll
+          for (int ks = 0; ks < G::KS1; ++ks) {
+            float av[MT];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) av[mt] = As[(16 * mt + lm) * G::RS + 4 * ks + lq];
+            const float bv[2] = {bq[ks].x, bq[ks].y};
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+              for (int nt = 0; nt < 2; ++nt)
+                acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[mt], bv[nt], acc[mt][nt], 0, 0, 0);
+          }
+        } else {
+          float z = 0.f;
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) {
+            f32x4 main[2];
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt) main[nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            // a part of A after the other, so that one is held at a time
+            tt_static_for<0, 3>([&](auto part) __attribute__((always_inline)) {
+              constexpr int pa = 2 - decltype(part)::value;
+              tt_bf16x8 av[G::KB];
+#pragma unroll
+              for (int kb = 0; kb < G::KB; ++kb)
+                av[kb] = *reinterpret_cast<const tt_bf16x8 *>(Asb + pa * G::PLANE + (mt * G::KB + kb) * 512 + lane * 8);
+#pragma unroll
+              for (int pb = pa == 2 ? 1 : 2; pb >= 0; --pb)
+#pragma unroll
+                for (int kb = 0; kb < G::KB; ++kb)
+#pragma unroll
+                  for (int nt = 0; nt < 2; ++nt) {
+                    f32x4 &c = pa + pb == 0 ? main[nt] : acc[mt][nt];
+                    c = tt_mfma_bf16_k32(av[kb], *reinterpret_cast<const tt_bf16x8 *>(&bs[pb][kb][nt]), c);
+                  }
+            });
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+              for (int v = 0; v < 4; ++v) {
+                acc[mt][nt][v] += main[nt][v];
+                z = fmaf(acc[mt][nt][v], 0.f, z);
+              }
+          }
+          if (z != 0.f) s_unfit[par] = 1;  // (zero times a number is zero, times an infinity or NaN is NaN)
         }
-        float z = 0.f;
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
+        for (int mt = 0; mt < MT; ++mt) {
+          const int p = 4 * mt + lq;  // C row m = 4*lq + v  ->  prefix 4*mt + lq, j1 = v
 #pragma unroll
-          for (int nt = 0; nt < 2; ++nt)
+          for (int nt = 0; nt < 2; ++nt) {
+            const int cl = 32 * wave + 2 * lm + nt, j2loc = cl / R2, r2 = cl - j2loc * R2;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) z = fmaf(acc[mt][nt][v], 0.f, z);
-        if (z != 0.f) s_not_finite = 1;
-      }
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        const int p = 4 * mt + lq;  // C row m = 4*lq + v  ->  prefix 4*mt + lq, j1 = v
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
-          const int cl = 32 * wave + 2 * lm + nt, j2loc = cl / R2, r2 = cl - j2loc * R2;
-#pragma unroll
-          for (int v = 0; v < 4; ++v)
-            P12s[p * G::PS + (v * G::JW + j2loc) * G::Rp + r2] = acc[mt][nt][v];
+            for (int v = 0; v < 4; ++v)
+              P12s[p * G::PS + (v * G::JW + j2loc) * G::Rp + r2] = acc[mt][nt][v];
+          }
         }
-      }
-    };
-    // A chunk of at most 4 prefixes fills one of the two row tiles.  At R1 = 64 only, as in the backward kernel
-    // (nine fused tables at batch 4096: 51.9 -> 48.0 us a launch).
-    if (R1 == 64 && seg1 - cs <= TT_MP / 2) f1(std::integral_constant<int, 1>{});
-    else f1(std::integral_constant<int, 2>{});
-    __syncthreads();  // P12 of the chunk is complete; the core-0 tile is free
-    if (more && !refill) stage_chunk(par ^ 1, mo + TT_MP);
+      };
+      // A chunk of at most 4 prefixes fills one of the two row tiles.  At R1 = 64 only, as in the backward kernel
+      // (nine fused tables at batch 4096: 51.9 -> 48.0 us a launch).
+      if (R1 == 64 && seg1 - cs <= TT_MP / 2) f1(std::integral_constant<int, 1>{});
+      else f1(std::integral_constant<int, 2>{});
+      __syncthreads();  // P12 of the chunk is complete; the core-0 tile is free
+      if (HOW == FWD_SPLIT && s_unfit[par]) return cs;  // uniform
+      if (more && !refill) stage_chunk(par ^ 1, mo + TT_MP);
 
-    if constexpr (P12OUT) {  // the chunk's products -> reuse buffer, as float4 along r2
-      constexpr int Q4 = G::CC * R2 / 4;  // float4 per prefix and strip
-      for (int e = threadIdx.x; e < TT_MP * Q4; e += FTHR) {
-        const int p = e / Q4, rem = e - p * Q4, cc = rem / (R2 / 4), r4 = rem - cc * (R2 / 4);
-        if (s_i1[mo + p] < 0) continue;
-        const int j1 = cc / G::JW, j2 = j2base + (cc - j1 * G::JW);
-        const float *src = P12s + p * G::PS + cc * G::Rp + 4 * r4;
-        *reinterpret_cast<float4 *>(p12buf + (size_t)s_slot[mo + p] * (4 * D2 * R2) + (j1 * D2 + j2) * R2 + 4 * r4) =
-            make_float4(src[0], src[1], src[2], src[3]);
-      }
-    }
-    // ---- F2: items = (prefix, four distinct rows), dealt round-robin to the wavefronts -------
-    const int total = P12OUT ? 0 : s_item_off[par][TT_MP];
-    struct Item { int p, ubase, nrow; float a[G::KS2]; };
-    auto fetch = [&](int it, Item &x) __attribute__((always_inline)) {
-      int p = 0;
-#pragma unroll
-      for (int k = 1; k < TT_MP; ++k) p += (s_item_off[par][k] <= it) ? 1 : 0;
-      // p = number of k in 1..TT_MP-1 with item_off[k] <= it = the prefix whose range holds `it`
-      const int quad = it - s_item_off[par][p];
-      x.p = p;
-      x.ubase = s_u0[mo + p] + 4 * quad;
-      const int left = s_nr[mo + p] - 4 * quad;
-      x.nrow = left < 4 ? left : 4;
-      // A operand: G3[r2][i3(row)][j3], m = (row, j3) = lm, k = r2
-      const int arow = 4 * quad + ((lm >> 2) < x.nrow ? (lm >> 2) : x.nrow - 1);
-      const int i3 = arow < FWD_I3_STAGE ? s_i3[par][p][arow] : uniq_row[s_u0[mo + p] + arow] % sh.n3;
-      const size_t a0 = ((size_t)lq * sh.n3 + i3) * 4 + (lm & 3);  // G3[r2 = 4*ks + lq][i3][j3], as stored
-#pragma unroll
-      for (int ks = 0; ks < G::KS2; ++ks) {
-        const size_t at = a0 + (size_t)16 * ks * sh.n3;
-        x.a[ks] = BF16 ? bf16_to_float(g3b[at]) : g3[at];
-      }
-    };
-    auto compute = [&](const Item &x) __attribute__((always_inline)) {
-      const float *bp = P12s + x.p * G::PS + lm * G::Rp + lq;
-      f32x4 o[G::NT2];
-#pragma unroll
-      for (int nt = 0; nt < G::NT2; ++nt) o[nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int ks = 0; ks < G::KS2; ++ks)
-#pragma unroll
-        for (int nt = 0; nt < G::NT2; ++nt)
-          o[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.a[ks], bp[16 * nt * G::Rp + 4 * ks], o[nt], 0, 0, 0);
-      // C[m = (row = lq, j3 = v)][n = cc]: one float4 of row ubase+lq at columns (j1, j2, 0..3)
-      if (lq < x.nrow) {
-#pragma unroll
-        for (int nt = 0; nt < G::NT2; ++nt) {
-          const int cc = 16 * nt + lm, j1 = cc / G::JW, j2 = j2base + (cc - j1 * G::JW);
-          *reinterpret_cast<float4 *>(rowbuf + (size_t)(x.ubase + lq) * G::D + (j1 * D2 + j2) * 4) =
-              make_float4(o[nt][0], o[nt][1], o[nt][2], o[nt][3]);
+      if constexpr (P12OUT) {  // the chunk's products -> reuse buffer, as float4 along r2
+        constexpr int Q4 = G::CC * R2 / 4;  // float4 per prefix and strip
+        for (int e = threadIdx.x; e < TT_MP * Q4; e += FTHR) {
+          const int p = e / Q4, rem = e - p * Q4, cc = rem / (R2 / 4), r4 = rem - cc * (R2 / 4);
+          if (s_i1[mo + p] < 0) continue;
+          const int j1 = cc / G::JW, j2 = j2base + (cc - j1 * G::JW);
+          const float *src = P12s + p * G::PS + cc * G::Rp + 4 * r4;
+          *reinterpret_cast<float4 *>(p12buf + (size_t)s_slot[mo + p] * (4 * D2 * R2) + (j1 * D2 + j2) * R2 + 4 * r4) =
+              make_float4(src[0], src[1], src[2], src[3]);
         }
       }
-    };
-    constexpr int NWV = FTHR / 64;
-    // (four wavefronts per SIMD cover each other's gathers; keeping a second item's operands in
-    // registers to prefetch it was measured and costs more in spilled registers than it hides)
-    for (int it = wave; it < total; it += NWV) {
-      Item x;
-      fetch(it, x);
-      compute(x);
-    }
-    if (more && refill) {  // uniform: the staged plan entries are used up, fetch the next 64
-      __syncthreads();  // every reader of the plan entries is done
-      fetch_meta(cs + TT_MP);
-      __syncthreads();
-      fetch_chunk(0);
-      stage_chunk(par ^ 1, 0);
-    }
-    par ^= 1;
-  }
-
-  if constexpr (SPLIT) {
-    // Infinities and NaN in the cores, or products beyond fp32: everything of this workgroup once more, in fp32
-    // as the formulas are written, so that the splitting never shows.
-    __syncthreads();
-    if (!s_not_finite) return;  // uniform
-    for (int x = seg0; x < seg1; ++x) {
-      const int4 m = pref_meta[x];
-      for (int e = threadIdx.x; e < G::CC * R2; e += FTHR) {  // the prefix's products -> P12s[(j1, j2)][r2], or the reuse buffer
-        const int cc = e / R2, r2 = e - cc * R2, j1 = cc / G::JW, j2 = j2base + cc - j1 * G::JW;
-        float sum = 0.f;
-#pragma unroll 8
-        for (int r1 = 0; r1 < R1; ++r1)
-          sum = fmaf(g1[(size_t)m.x * G::S1 + j1 * R1 + r1], g2[((size_t)r1 * sh.n2 + i2) * G::S2 + j2 * R2 + r2], sum);
-        if constexpr (P12OUT) p12buf[(size_t)m.w * (4 * D2 * R2) + (j1 * D2 + j2) * R2 + r2] = sum;
-        else P12s[cc * G::Rp + r2] = sum;
+      // ---- F2: items = (prefix, four distinct rows), dealt round-robin to the wavefronts -------
+      const int total = P12OUT ? 0 : s_item_off[par][TT_MP];
+      struct Item { int p, ubase, nrow; float a[G::KS2]; };
+      auto fetch = [&](int it, Item &x) __attribute__((always_inline)) {
+        int p = 0;
+#pragma unroll
+        for (int k = 1; k < TT_MP; ++k) p += (s_item_off[par][k] <= it) ? 1 : 0;
+        // p = number of k in 1..TT_MP-1 with item_off[k] <= it = the prefix whose range holds `it`
+        const int quad = it - s_item_off[par][p];
+        x.p = p;
+        x.ubase = s_u0[mo + p] + 4 * quad;
+        const int left = s_nr[mo + p] - 4 * quad;
+        x.nrow = left < 4 ? left : 4;
+        // A operand: G3[r2][i3(row)][j3], m = (row, j3) = lm, k = r2
+        const int arow = 4 * quad + ((lm >> 2) < x.nrow ? (lm >> 2) : x.nrow - 1);
+        const int i3 = arow < FWD_I3_STAGE ? s_i3[par][p][arow] : uniq_row[s_u0[mo + p] + arow] % sh.n3;
+        const size_t a0 = ((size_t)lq * sh.n3 + i3) * 4 + (lm & 3);  // G3[r2 = 4*ks + lq][i3][j3], as stored
+#pragma unroll
+        for (int ks = 0; ks < G::KS2; ++ks) {
+          const size_t at = a0 + (size_t)16 * ks * sh.n3;
+          x.a[ks] = BF16 ? bf16_to_float(g3b[at]) : g3[at];
+        }
+      };
+      auto compute = [&](const Item &x) __attribute__((always_inline)) {
+        const float *bp = P12s + x.p * G::PS + lm * G::Rp + lq;
+        f32x4 o[G::NT2];
+#pragma unroll
+        for (int nt = 0; nt < G::NT2; ++nt) o[nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < G::KS2; ++ks)
+#pragma unroll
+          for (int nt = 0; nt < G::NT2; ++nt)
+            o[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.a[ks], bp[16 * nt * G::Rp + 4 * ks], o[nt], 0, 0, 0);
+        // C[m = (row = lq, j3 = v)][n = cc]: one float4 of row ubase+lq at columns (j1, j2, 0..3)
+        if (lq < x.nrow) {
+#pragma unroll
+          for (int nt = 0; nt < G::NT2; ++nt) {
+            const int cc = 16 * nt + lm, j1 = cc / G::JW, j2 = j2base + (cc - j1 * G::JW);
+            *reinterpret_cast<float4 *>(rowbuf + (size_t)(x.ubase + lq) * G::D + (j1 * D2 + j2) * 4) =
+                make_float4(o[nt][0], o[nt][1], o[nt][2], o[nt][3]);
+          }
+        }
+      };
+      constexpr int NWV = FTHR / 64;
+      // (four wavefronts per SIMD cover each other's gathers; keeping a second item's operands in
+      // registers to prefetch it was measured and costs more in spilled registers than it hides)
+      for (int it = wave; it < total; it += NWV) {
+        Item x;
+        fetch(it, x);
+        compute(x);
       }
-      if constexpr (!P12OUT) {
+      if (more && refill) {  // uniform: the staged plan entries are used up, fetch the next 64
+        __syncthreads();  // every reader of the plan entries is done
+        fetch_meta(cs + TT_MP);
         __syncthreads();
-        for (int e = threadIdx.x; e < m.z * G::CC; e += FTHR) {
-          const int u = m.y + e / G::CC, cc = e % G::CC, j1 = cc / G::JW, j2 = j2base + cc - j1 * G::JW, i3 = uniq_row[u] % sh.n3;
-          float o[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-          for (int r2 = 0; r2 < R2; ++r2)
-#pragma unroll
-            for (int j3 = 0; j3 < 4; ++j3) o[j3] = fmaf(P12s[cc * G::Rp + r2], g3[((size_t)r2 * sh.n3 + i3) * 4 + j3], o[j3]);
-#pragma unroll
-          for (int j3 = 0; j3 < 4; ++j3) rowbuf[(size_t)u * G::D + (j1 * D2 + j2) * 4 + j3] = o[j3];
-        }
-        __syncthreads();  // the next prefix's products take the place of this one's
+        fetch_chunk(0);
+        stage_chunk(par ^ 1, 0);
       }
+      par ^= 1;
+    }
+    return seg1;
+  };
+  const int rest = run(std::integral_constant<int, MODE>{}, seg0);
+  if constexpr (SPLIT) {
+    // Infinities and NaN in the cores, products beyond fp32, operands too small to split: from here on in fp32, with the same
+    // bits as a short batch.
+    if (rest < seg1) {  // uniform
+      load_strip(std::integral_constant<int, FWD_FP32>{});
+      run(std::integral_constant<int, FWD_FP32>{}, rest);
     }
   }
 }

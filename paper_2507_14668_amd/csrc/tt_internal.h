@@ -129,11 +129,13 @@ __device__ __forceinline__ float4 tt_load_stream4(const float *src) {
 #ifdef __HIPCC__
 // An fp32 number as the sum of three bf16 numbers, so that bf16 matrix instructions (16 times the rate of the fp32
 // ones) can multiply fp32 operands: `hi` is x rounded to bf16, `mid` the remainder rounded, `lo` what is left, and hi + mid
-// + lo == x exactly (24 bits of significand; below 2^-110 lo runs into bf16's denormals).  Products of two parts are exact in
-// fp32.  mid is at most 2^-8 |x| and lo 2^-17 |x| in size, both of either sign, so a product of two numbers keeps its fp32
-// accuracy without the three smallest of its nine terms (mid*lo, lo*mid, lo*lo): against 64 bits, 2-norm, bag sums of the
-// fp32 instruction / of the split, 1.47e-7 / 1.14e-7 (ranks 32) and 2.07e-7 / 1.73e-7 (ranks 64): fewer roundings a sum.  Infinities, NaN and numbers that round to a
-// bf16 infinity get a NaN among their parts, so that they show in the result: the caller has to look and to multiply in fp32.
+// + lo == x exactly (24 bits of significand) for zero and sizes from TT_SPLIT_MIN on.  Products of two parts are exact in fp32.  mid is
+// at most 2^-8 |x| and lo 2^-17 |x| in size, both of either sign, so of the nine terms of a product lo*lo (2^-34) can be left
+// out; without mid*lo and lo*mid a single product is up to 1.7 units of 2^-24 off instead of 1.0.  With hi*hi summed
+// apart from the smaller terms, error of the prefix products against 64 bits, 2-norm, fp32 instruction / split: one non-zero
+// term 2.53e-8 / 2.53e-8, two 3.12e-8 / 2.55e-8, four 4.01e-8 / 2.62e-8, ranks 32 1.03e-7 / 3.9e-8, ranks 64 1.44e-7 / 4.9e-8.
+// Infinities, NaN and numbers that round to a bf16 infinity get a NaN among their parts, so that they show in the result.  Numbers
+// below TT_SPLIT_MIN = 2^-40 might get parts, or products of parts, in the denormal range.  For both the caller has to look, and to multiply in fp32.
 __device__ __forceinline__ unsigned tt_bf16_pair(float x, float y) {  // x in the lower half
   typedef __bf16 v2 __attribute__((ext_vector_type(2)));
   const v2 r = {(__bf16)x, (__bf16)y};
@@ -145,6 +147,15 @@ __device__ __forceinline__ void tt_split_bf16(float x, float y, unsigned &hi, un
   const float rx = x - __uint_as_float(hi << 16), ry = y - __uint_as_float(hi & 0xffff0000u);
   mid = tt_bf16_pair(rx, ry);
   lo = tt_bf16_pair(rx - __uint_as_float(mid << 16), ry - __uint_as_float(mid & 0xffff0000u));
+}
+// Sizes are compared as the bits of |x| one up, minus one: zero, which splits like any other number, counts as the largest.
+#ifndef TT_SPLIT_MIN
+#define TT_SPLIT_MIN (2u * (127 - 40) << 23)
+#endif
+__device__ __forceinline__ unsigned tt_split_smallest(unsigned m, float x, float y) {
+  const unsigned a = (__float_as_uint(x) << 1) - 1, b = (__float_as_uint(y) << 1) - 1;
+  m = a < m ? a : m;
+  return b < m ? b : m;
 }
 typedef short tt_bf16x8 __attribute__((ext_vector_type(8)));
 typedef float tt_f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // four floats at any float's address
@@ -228,15 +239,25 @@ tt_status ttk_forward_plan(const TTBatch &b, hipStream_t s);
 #define TT_DIRECT_BAG_LOOKUPS 32       // up to this many lookups in one launch, a workgroup per bag
 #ifndef TT_DIRECT_MAX_LOOKUPS_32
 #define TT_DIRECT_MAX_LOOKUPS_32 16384 // ... and up to this many in two, a wavefront per lookup and 64 columns (ranks 32)
+#endif
+#ifndef TT_DIRECT_MAX_LOOKUPS_64
 #define TT_DIRECT_MAX_LOOKUPS_64 8192  // (ranks 64)
 #endif
-// Whether the matrix-core forward multiplies prefixes by split fp32 numbers (tt_split_bf16).  Contraction launch, fp32 / split, one-
-// hot lookups in tables of 300 k and 40 M rows: ranks 64 8192 lookups 13.3 / 12.5 and 23.3 / 22.0 us, 17000 19.1 / 16.0 and
-// 27.5 / 24.0, 65536 31.9 / 25.9 and 51.6 / 40.6; ranks 32 8192 9.0 / 9.5 and 15.5 / 14.7, 17000 10.3 / 9.9 and 17.5 / 16.2, 65536
-// 15.3 / 14.5 and 29.1 / 26.0.  Short batches gain next to nothing (a strip is split for one chunk of prefixes), and up to
-// these limits the forward without a plan has the fp32 kernel's bits: a batch gets the same bits by both.
+// Whether the matrix-core forward multiplies prefixes by split fp32 numbers (tt_split_bf16): above this many lookups.  Contraction
+// launch, fp32 / split, one-hot lookups in tables of 300 k and 40 M rows: ranks 64 17000 lookups 19.1 / 17.8 us, 65536 31.9 /
+// 29.9 and 58.1 / 50.2; ranks 32 17000 10.5 / 10.1, 65536 15.5 / 14.8.  Short batches gain next to nothing (a strip is split
+// for one chunk of prefixes).  The last bits of a row follow the number of lookups of its call through this limit.
+// The forward without a plan has the fp32 kernel's bits, and a batch gets the same bits by both: it stays below the limit.
+#ifndef TT_FORWARD_SPLIT_ABOVE_32
+#define TT_FORWARD_SPLIT_ABOVE_32 16384
+#endif
+#ifndef TT_FORWARD_SPLIT_ABOVE_64
+#define TT_FORWARD_SPLIT_ABOVE_64 8192
+#endif
+static_assert(TT_DIRECT_MAX_LOOKUPS_32 <= TT_FORWARD_SPLIT_ABOVE_32 && TT_DIRECT_MAX_LOOKUPS_64 <= TT_FORWARD_SPLIT_ABOVE_64,
+              "the forward without a plan has the bits of the fp32 instructions");
 __host__ __device__ __forceinline__ bool ttk_forward_splits(const TTDev &d) {
-  return d.nnz > (d.sh.R1 == 32 ? TT_DIRECT_MAX_LOOKUPS_32 : TT_DIRECT_MAX_LOOKUPS_64);
+  return d.nnz > (d.sh.R1 == 32 ? TT_FORWARD_SPLIT_ABOVE_32 : TT_FORWARD_SPLIT_ABOVE_64);
 }
 bool ttk_forward_direct_serves(const TTDev &d);
 tt_status ttk_forward_direct(const TTBatch &b, hipStream_t s);

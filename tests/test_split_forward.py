@@ -11,7 +11,13 @@ pytestmark = te.pytestmark
 
 @pytest.fixture(scope="module")
 def emu_split():
-    return te._load(te.emu_build.build_shared(te.BUILD_DIR, "split", ["-DTT_DIRECT_MAX_LOOKUPS_32=0", "-DTT_DIRECT_MAX_LOOKUPS_64=0"]))
+    return te._load(te.emu_build.build_shared(te.BUILD_DIR, "split", ["-D%s_%d=0" % (m, r) for r in (32, 64)
+                                                                for m in ("TT_DIRECT_MAX_LOOKUPS", "TT_FORWARD_SPLIT_ABOVE")]))
+
+
+@pytest.fixture(scope="module")
+def emu():
+    return te._load(te.emu_build.build_shared(te.BUILD_DIR))  # short batches: the fp32 instruction
 
 
 def _problem(r, n, nb, seed):
@@ -59,3 +65,62 @@ def test_infinities_nan_and_the_largest_numbers(emu_split, r, core, value):
     if value == value and abs(value) < np.inf:
         assert fin.any()
     assert np.allclose(got[fin], want[fin], rtol=1e-4, atol=1e-5 * np.abs(want[fin]).max(initial=0.0))
+
+
+def _products(r, n, seed, terms):
+    """A problem whose bag sums are the prefix products (core 2 picks one r2 per column), `terms` non-zero r1 a row of core 0;
+    every row once, and the products in 64 bits."""
+    rng = np.random.default_rng(seed)
+    n = (n[0], n[1], r // 4)
+    shape = wl.TableShape(n[0] * n[1] * n[2], n, (4, 8, 4), (1, r, r, 1))
+    c0 = rng.standard_normal((n[0], 4, r)) * (rng.random((n[0], 4, r)).argsort(-1) < terms)
+    c1 = rng.standard_normal((r, n[1], 8, r))
+    cores = [c0.astype(np.float32), c1.astype(np.float32), np.eye(r, dtype=np.float32).reshape(r, n[2], 4)]
+    idx = np.arange(shape.num_rows)
+    return shape, cores, idx, np.arange(shape.num_rows + 1)
+
+
+def _product_sums(emu, problem):
+    shape, cores, idx, off = problem
+    return te._run(emu, shape, [c.reshape(-1) for c in cores], idx, off, np.zeros(len(idx) * 128, np.float32), 0.0)["plan"][0]
+
+
+def _exact_products(problem):
+    shape, (c0, c1, _), idx, _ = problem
+    p = np.tensordot(c0.astype(np.float64), c1.astype(np.float64), 1).transpose(0, 2, 1, 3, 4)  # [i1][i2][j1][j2][r2]
+    p = p.reshape(-1, 32, shape.n[2], 4).transpose(0, 2, 1, 3)
+    return p.reshape(len(idx), 128)
+
+
+# One term: a product rounded once by either, so the errors are the same to half a percent (each of the eight terms left out shows).
+# More terms: fewer roundings at full size.  (Emulated, the instruction adds its terms one after the other in fp32; the GPU
+# test has the hardware's sums.)
+@pytest.mark.parametrize("r", [32, 64])
+@pytest.mark.parametrize("terms,most", [(1, 1.005), (2, 1.005), (4, 1.005), (64, 1.05)])
+def test_no_less_exact_than_the_fp32_instruction(emu, emu_split, r, terms, most):
+    problem = _products(r, (9, 2), 3 * r + terms, terms)
+    want = _exact_products(problem)
+    whole, split = (np.linalg.norm(_product_sums(e, problem) - want) / np.linalg.norm(want) for e in (emu, emu_split))
+    assert split <= most * whole and split <= 6e-7
+
+
+# core 0 so small, and core 1 so large, that parts or products of parts would be denormal: the fp32 instruction's bits, also from
+# the second chunk of prefixes on only, and from a strip on
+@pytest.mark.parametrize("r", [32, 64])
+@pytest.mark.parametrize("where", ["all", "chunk", "strip"])
+def test_operands_too_small_to_split(emu, emu_split, r, where):
+    problem = _products(r, (19, 2), r, r)
+    c0, c1, _ = problem[1]
+    if where == "all":
+        c0 *= np.float32(2.0 ** -116)
+        c1 *= np.float32(2.0 ** 100)
+    elif where == "chunk":
+        c0[8:, 2, 5] *= np.float32(2.0 ** -100)
+    else:
+        c1[3, :, 7, 1] *= np.float32(2.0 ** -100)  # (the last strip; the others are split)
+    whole, split = (_product_sums(e, problem).reshape(19, -1, 4, 8, 4) for e in (emu, emu_split))
+    same = slice(8, None) if where == "chunk" else slice(None)
+    cols = slice(8 - 256 // r, 8) if where == "strip" else slice(None)
+    assert np.array_equal(whole[same, :, :, cols], split[same, :, :, cols])
+    want = _exact_products(problem).reshape(whole.shape)
+    assert np.abs(split - want).max() <= 1e-6 * np.abs(want).max()
