@@ -27,7 +27,7 @@
 // prefix products alone 18.5 -> 17.2.  Six terms into one accumulator: 44.8 us, but sums of few non-zero
 // terms were less exact than the fp32 instruction's.  Row tiles side by side, or operands a step ahead, spill at ranks 64 (52 to 53 us).
 // Operands or products that the split does not serve send the rest of a workgroup's chunks to the fp32 instruction (all cores
-// NaN: 67 us at ranks 64 where the fp32 kernel takes 54, 31 where it takes 29 at ranks 32).
+// NaN: 63 us at ranks 64 where the fp32 kernel takes 54, 30.5 where it takes 28.7 at ranks 32; one NaN in a product 68 and 32).
 // The operand tile has to lie on 16 bytes: with the dynamic LDS at any float's address the 16-byte reads cost a third more.
 //
 // Operand layout of __builtin_amdgcn_mfma_f32_16x16x4f32 (D = A[16x4] * B[4x16] + C):
@@ -110,9 +110,9 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
   __shared__ int s_i1[FMETA], s_u0[FMETA], s_nr[FMETA], s_slot[FMETA];
   __shared__ int s_item_off[2][TT_MP + 1];
   __shared__ int s_i3[2][TT_MP][FWD_I3_STAGE];
-  // Split: set where a chunk (by parity: the next one is staged while this one's flag is read) has operands or products that
-  // the split does not serve.
-  __shared__ int s_unfit[2];
+  // Split: set where a chunk (by parity: the next one is staged while this one's flag is read) or the strip [2] has operands
+  // or products that the split does not serve.
+  __shared__ int s_unfit[3];
 
   // Workgroup index = ((i2 / 8) * (strips * split) + (strip, part)) * 8 + i2 % 8: workgroups are
   // dealt to the 8 XCDs round-robin, so all strips and parts of one i2 run on XCD i2 % 8, close in
@@ -158,6 +158,7 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
   if (seg0 == seg1) return;  // uniform: no prefix for this workgroup
 
   // The prefixes from `first` on, multiplied as `how` says.  Returns the chunk that it has to leave to the fp32 instructions, or seg1.
+  // (It starts behind seg0, or again at seg0, in the fp32 phase of a split kernel only: the plan entries are then staged.)
   auto run = [&](auto how, const int first) __attribute__((always_inline)) -> int {
     constexpr int HOW = decltype(how)::value;
     // Global-memory operands of the NEXT chunk (core-0 rows, row ids of its first rows) are fetched
@@ -232,14 +233,18 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
       }
     };
 
-    if (HOW == FWD_SPLIT && threadIdx.x < 2) s_unfit[threadIdx.x] = 0;
-    fetch_meta(first);
-    __syncthreads();
-    fetch_chunk(0);
+    const int mo0 = (first - seg0) % FMETA;
+    if constexpr (HOW == MODE) {
+      if (SPLIT && threadIdx.x < 3) s_unfit[threadIdx.x] = 0;
+      fetch_meta(first);
+      __syncthreads();
+    }
+    fetch_chunk(mo0);
     // the strip as F1's B operand: per part, k step and tile column eight bf16 values
     uint4 bs[HOW == FWD_SPLIT ? 3 : 1][HOW == FWD_SPLIT ? G::KB : 1][2];
     if constexpr (HOW == FWD_SPLIT) {
       unsigned smallest = ~0u;
+      float z = 0.f;
 #pragma unroll
       for (int kb = 0; kb < G::KB; ++kb)
 #pragma unroll
@@ -249,20 +254,22 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
           for (int i = 0; i < 8; i += 2) {
             const float x = nt ? bq[8 * kb + i].y : bq[8 * kb + i].x, y = nt ? bq[8 * kb + i + 1].y : bq[8 * kb + i + 1].x;
             smallest = tt_split_smallest(smallest, x, y);
+            z = fmaf(x, 0.f, fmaf(y, 0.f, z));
             tt_split_bf16(x, y, w[0][i / 2], w[1][i / 2], w[2][i / 2]);
           }
 #pragma unroll
           for (int k = 0; k < 3; ++k) bs[k][kb][nt] = make_uint4(w[k][0], w[k][1], w[k][2], w[k][3]);
         }
-      if (smallest < TT_SPLIT_MIN) s_unfit[0] = 1;
+      if (smallest < TT_SPLIT_MIN || z != 0.f) s_unfit[2] = 1;  // (zero times a number is zero, times an infinity or NaN is NaN)
     }
-    stage_chunk(0, 0);
+    stage_chunk(0, mo0);
     int par = 0;
 
     for (int cs = first; cs < seg1; cs += TT_MP) {
-      const int mo = (cs - first) % FMETA;  // this chunk's offset in s_i1 / s_u0 / s_nr
+      const int mo = (cs - seg0) % FMETA;  // this chunk's offset in s_i1 / s_u0 / s_nr
       const bool more = cs + TT_MP < seg1, refill = mo + TT_MP == FMETA;
       __syncthreads();  // this chunk's staging is visible; the previous chunk's readers of P12 are done
+      if (HOW == FWD_SPLIT && cs == first && s_unfit[2]) return cs;  // uniform
       if (more && !refill) fetch_chunk(mo + TT_MP);  // next chunk's operands, staged after F1
 
       // ---- F1: C[32 x 32 per wavefront] on MFMA -> P12s[p][(j1, j2)][r2] ---------------------------
@@ -334,7 +341,7 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
                 z = fmaf(acc[mt][nt][v], 0.f, z);
               }
           }
-          if (z != 0.f) s_unfit[par] = 1;  // (zero times a number is zero, times an infinity or NaN is NaN)
+          if (z != 0.f) s_unfit[par] = 1;
         }
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
