@@ -516,25 +516,34 @@ tt_status ttk_forward_naive(const TTBatch &b, hipStream_t s) {
 //   ranks 64   20 lookups in one bag 26.4 / 8.6     2048 50.6 / 26.8, 45.2 / 25.7, 33.1 / 20.2     8192 102 / 86, 80 / 77, 64 / 58
 //   (ranks 64, 12000: 118 / 120, 83 / 108, 65 / 83, hence the limits)
 // One launch up to TT_DIRECT_BAG_LOOKUPS: 64 lookups in one bag take it 13.2 (ranks 32) and 22.4, the two launches 13.2 and 14.3;
-// in 64 bags 4.9 and 6.8, 7.4 and 8.2.
+// in 64 bags 4.9 and 6.8, 7.4 and 8.2.  ... and as long as its workgroups, four or eight a bag with lookups or without, are few: 1 /
+// 16 / 32 lookups in one launch and in two (7.7 whatever the bags), ranks 32 512 bags 4.9 / 5.5 / 6.7, 768 5.7 / 6.5 / 7.7, 1024
+// 6.6 / 7.5 / 8.6, 16384 67 / 69 / 71; ranks 64 96 bags 5.2 / 6.5 / 6.5, 128 5.7 / 8.7 / 11.5, 256 7.6 / 10.6 / 14.5, 16384 300.
+#define TT_DIRECT_BAG_MAX_BAGS_32 768
+#define TT_DIRECT_BAG_MAX_BAGS_64 96
+static bool direct_in_one_launch(const TTDev &d) {
+  return d.nnz <= TT_DIRECT_BAG_LOOKUPS && d.num_bags <= (d.sh.R1 == 32 ? TT_DIRECT_BAG_MAX_BAGS_32 : TT_DIRECT_BAG_MAX_BAGS_64);
+}
 bool ttk_forward_direct_serves(const TTDev &d) {
   // (rowbuf has a row per lookup unless the table itself has fewer)
   return d.mfma && d.nnz <= (d.sh.R1 == 32 ? TT_DIRECT_MAX_LOOKUPS_32 : TT_DIRECT_MAX_LOOKUPS_64) && d.num_bags <= TT_SMALL_MAX_BAGS &&
-         (d.nnz <= TT_DIRECT_BAG_LOOKUPS || d.plan.max_rows == d.nnz);
+         (direct_in_one_launch(d) || d.plan.max_rows == d.nnz);
 }
 
 tt_status ttk_forward_direct(const TTBatch &b, hipStream_t s) {
   const TTDev &d = b.host[0];
   if (d.num_bags == 0) return TT_OK;
   const int groups = d.sh.S2 / TT_WAVE, nt = TT_WAVE * DIRECT_WAVES;
-  if (d.nnz <= TT_DIRECT_BAG_LOOKUPS) {
+  if (direct_in_one_launch(d)) {
     if (d.sh.R1 == 32) TT_LAUNCH_T2(k_fwd_direct, 32, true, d.num_bags * groups, nt, 0, s, b);
     else TT_LAUNCH_T2(k_fwd_direct, 64, true, d.num_bags * groups, nt, 0, s, b);
     return tt_launch_status();
   }
   const int wgs = tt_ceil_div(d.nnz, DIRECT_WAVES) * groups;
-  if (d.sh.R1 == 32) TT_LAUNCH_T2(k_fwd_direct, 32, false, wgs, nt, 0, s, b);
-  else TT_LAUNCH_T2(k_fwd_direct, 64, false, wgs, nt, 0, s, b);
+  if (d.nnz > 0) {
+    if (d.sh.R1 == 32) TT_LAUNCH_T2(k_fwd_direct, 32, false, wgs, nt, 0, s, b);
+    else TT_LAUNCH_T2(k_fwd_direct, 64, false, wgs, nt, 0, s, b);
+  }
   return ttk_bag_sum(b, s);
 }
 
