@@ -386,9 +386,11 @@ k_bag_direct_bf16(TTArg<BATCHED> a) {
 #pragma unroll
   for (int k = 0; k < NV; ++k) acc[k] = tot[k] = 0.f;
   int in_block = 0;
-  for (int base = l0 + wave; base < l1; base += BAGB_WAVES * TT_WAVE) {  // uniform per wavefront
-    const int mine = base + BAGB_WAVES * lane;  // the wavefront's next 64 lookups, one per lane
-    const long long at = mine < l1 ? indices[mine] : -1;
+  const int64_t *__restrict__ bag = indices + l0;
+  const unsigned len = (unsigned)(l1 - l0);  // (unsigned: the last step may end behind 2^31)
+  for (unsigned base = wave; base < len; base += BAGB_WAVES * TT_WAVE) {  // uniform per wavefront
+    const unsigned mine = base + BAGB_WAVES * lane;  // the wavefront's next 64 lookups, one per lane
+    const long long at = mine < len ? bag[mine] : -1;
     const int row = at >= 0 && at < sh.num_rows ? (int)at : -1;  // an invalid lookup adds nothing
     for (unsigned long long left = __ballot(row >= 0); left != 0; left &= left - 1) {
       const int x = __builtin_amdgcn_readlane(row, __ffsll(left) - 1);

@@ -97,3 +97,41 @@ def test_direct_bf16_forward_matches_oracle_and_plan(emu, ora, r, n, lens, spoil
     np.testing.assert_allclose(out, ref, rtol=0, atol=5e-6 * np.abs(ref).max())
     if not spoil:
         g.assert_close_rows(out, ora.forward(shape, [round_to_bf16(c) for c in raw], idx, off), g.FWD_RTOL, shape.dim, "direct bf16 forward")
+
+
+def test_direct_bf16_forward_of_the_last_lookups_of_2_31(tmp_path):
+    """A bag that ends where 32-bit positions end (compiled so that they wrap).  In a process of its own: the indices are a sparse file of 16 GB of which the bag's
+    pages are touched, and reading elsewhere ends the process."""
+    import subprocess
+    import sys
+    script = """
+import ctypes, sys
+import numpy as np
+sys.path[:0] = %r
+import tt_workloads as wl
+from test_cpu_emulation import BUILD_DIR, _aligned, _load, _ptr, _table, emu_build
+lib, binding = _load(%r)
+vp, i64 = ctypes.c_void_p, ctypes.c_int64
+lib.tt_cores_to_bf16.argtypes = [vp, vp, ctypes.c_size_t, vp]
+lib.tt_bf16_cores_bytes.restype, lib.tt_bf16_cores_bytes.argtypes = ctypes.c_size_t, [vp]
+lib.tt_emb_bag_forward_bf16_direct.argtypes = [vp, vp, vp, vp, i64, i64, vp, vp]
+shape, raw, _, _, _ = wl.small_random_problem(9, n=(5, 3, 7), d=(4, 8, 4), r=(1, 32, 32, 1), sigma=0.2)
+cores = [_aligned(np.asarray(c).size * 4).view(np.float32) for c in raw]
+for c, x in zip(cores, raw):
+    c[:] = np.asarray(x, np.float32).reshape(-1)
+table = _table(binding, shape, cores)
+bf = _aligned(lib.tt_bf16_cores_bytes(ctypes.byref(table)))
+assert lib.tt_cores_to_bf16(ctypes.byref(table), _ptr(bf), bf.nbytes, None) == 0
+rng, out = np.random.default_rng(0), []
+last = rng.integers(0, shape.num_rows, 300)
+for nnz in (300, 2 ** 31 - 2):
+    idx = np.memmap(%r, np.int64, "w+", shape=(nnz,))
+    idx[-300:] = last
+    off = np.array([nnz - 300, nnz], np.int64)
+    out.append(np.full(shape.dim, np.nan, np.float32))
+    assert lib.tt_emb_bag_forward_bf16_direct(ctypes.byref(table), _ptr(bf), _ptr(idx), _ptr(off), nnz, 1, _ptr(out[-1]), None) == 0
+assert np.array_equal(*out) and np.isfinite(out[0]).all()
+""" % ([p for p in sys.path if p], emu_build.build_shared(BUILD_DIR, "wrap", ["-fwrapv"]), str(tmp_path / "indices"))
+    res = subprocess.run([sys.executable, "-c", script], capture_output=True, text=True, timeout=300)
+    (tmp_path / "indices").unlink(missing_ok=True)
+    assert res.returncode == 0, res.stderr[-2000:]
