@@ -556,9 +556,12 @@ tt_status ttk_forward_direct(const TTBatch &b, hipStream_t s) {
 //   ranks 64   2048 39 / 10.3, 35 / 10.7, 27 / 9.5         5161 67 / 22.6, 63 / 23.3, 52 / 19.5   10000 79 / 37, 67 / 41, 54 / 31
 //              20000 97 / 71, 77 / 75, 54 / 59
 // One-lookup bags, ranks 64: 5000 62 / 40, 15000 70 / 117; 20000 bags with ten lookups in all: 49 / 86 (ranks 32 50 / 33).
-// A bag that holds thousands of lookups takes the planned bag sum and this about the same time (ranks 64, 5000 in one bag 679 / 782,
-// in 100 bags 88 / 59).
+// One or two bags that hold all lookups are chains, of planned row reads or of this.  At ranks 64 a step of this is the longer one:
+// one bag 500 lookups 85 / 80, 1500 224 / 234, 5000 717 / 774; two bags 5000 406 / 389, 8000 603 / 621; three 14000 861 / 725.  At
+// ranks 32 it is the shorter one (one bag 500 87 / 64, 46000 6219 / 5641).  (A single long bag among many short ones, 8 %
+// slower at ranks 64, cannot be told from the sizes.)
 bool ttk_bag_direct_bf16_pays(const TTShape &sh, long long nnz, long long bags) {
+  if (sh.R1 == 64 && ((bags == 1 && nnz > 1000) || (bags == 2 && nnz > 6000))) return false;
   const long long ns = sh.R1 == 32 ? (19 * nnz + 28 * bags) / 20 : (31 * nnz + 43 * bags) / 10;
   return ns <= (nnz <= TT_SMALL_MAX_LOOKUPS ? 13000 : 45000);
 }

@@ -135,3 +135,16 @@ assert np.array_equal(*out) and np.isfinite(out[0]).all()
     res = subprocess.run([sys.executable, "-c", script], capture_output=True, text=True, timeout=300)
     (tmp_path / "indices").unlink(missing_ok=True)
     assert res.returncode == 0, res.stderr[-2000:]
+
+
+# which way the module goes, on both sides of every limit: short sums of costs, and at ranks 64 one or two bags with all lookups
+@pytest.mark.parametrize("r,nnz,bags,pays", [
+    (32, 0, 0, 1), (32, 2048, 300, 1), (32, 46000, 1, 1), (32, 46000, 900, 1), (32, 47400, 900, 0), (32, 50, 9000, 1), (32, 50, 9300, 0),
+    (64, 1000, 1, 1), (64, 1001, 1, 0), (64, 5000, 1, 0), (64, 6000, 2, 1), (64, 6001, 2, 0), (64, 14000, 3, 1), (64, 14600, 3, 0),
+    (64, 2048, 300, 1), (64, 20000, 2000, 0)])
+def test_where_the_bf16_forward_goes_without_a_plan(emu, r, nnz, bags, pays):
+    lib, binding = emu
+    lib.tt_forward_bf16_direct_pays.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int64]
+    shape = wl.TableShape(105, (5, 3, 7), (4, 8, 4), (1, r, r, 1))
+    table = _table(binding, shape, [np.zeros(4, np.float32)] * 3)
+    assert lib.tt_forward_bf16_direct_pays(ctypes.byref(table), nnz, bags) == pays
