@@ -49,7 +49,9 @@ def _ptr(a):
 
 
 def _aligned(nbytes):
-    raw = np.empty(nbytes + 256, dtype=np.uint8)
+    # all ones (NaN as a float): a block that an earlier call has freed would still hold the right results, and a kernel that
+    # writes nothing would pass
+    raw = np.full(nbytes + 256, 0xFF, dtype=np.uint8)
     off = (-raw.ctypes.data) % 256
     return raw[off:off + nbytes]
 
