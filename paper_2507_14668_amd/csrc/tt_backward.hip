@@ -280,16 +280,26 @@ k_seg_stage1(TTArg<BATCHED> arg, SegLaunch L, int lanes) {
 //   Lane group per chunk (SPREAD, and the kind's `spread`): most owners add two vectors, which a lane group does by itself, so
 // that many chunks are through in one round.  Segments of many partials are left to all lane groups of the workgroup; those
 // are the hot rows, neighbours in sorted order where ids are not permuted, so the chunks of a workgroup lie a grid
-// apart and no workgroup gets many of them.  A kernel of its own: it needs more registers (73 against 46) and a list in LDS.
+// apart and no workgroup gets many of them.  A kernel of its own: it needs more registers (72 against 46) and a list in LDS.
 // Stage 2 of the gradient merge at D = 128, per chunk / spread: 1125 chunks 5.0 / 6.6 us, 4600 8.3 / 9.8, 8192 10.1 / 8.4,
 // 10500 13.1 / 11.1, 12800 15.3 / 11.0; the sums are the same bit for bit.
 // With `dense`, workgroup (lane group) c also zero-fills segment c if it is empty.
-// LDS: red[groups][W], with SPREAD | long[groups] | count
+// LDS: red[groups][W], with SPREAD | SegUnits long[groups] | count
 #ifndef TT_SEG2_SPREAD_CHUNKS
 #define TT_SEG2_SPREAD_CHUNKS 6144  // chunks above which a lane group takes one
 #endif
+// Partials to add for the segment that chunk c owns: slot 0 of the chunks c+1 .. c1, except that stage 1
+// has left ONE partial (in the first chunk) for every run of `groups` chunks handled by one workgroup
+// that lies strictly inside the segment: the runs B0 .. B1.  Units in order: single chunks before the
+// runs, one per run, single chunks after.
+struct SegUnits {
+  int seg, c, B0, B1, nh, nm, n;  // n of them
+  __device__ __forceinline__ int chunk_of(int u, int groups) const {
+    return u < nh ? c + 1 + u : (u < nh + nm ? (B0 + (u - nh)) * groups : (B1 + 1) * groups + (u - nh - nm));
+  }
+};
 static size_t seg2_lds_bytes(int groups, int W, bool spread) {
-  return sizeof(float) * (size_t)groups * W + (spread ? sizeof(int) * (size_t)(groups + 1) : 0);
+  return sizeof(float) * (size_t)groups * W + (spread ? sizeof(SegUnits) * (size_t)groups + sizeof(int) : 0);
 }
 template <bool BATCHED, int VEC, bool SPREAD>
 __global__ void __launch_bounds__(TT_BLOCK)
@@ -314,39 +324,32 @@ k_seg_stage2(TTArg<BATCHED> arg, SegLaunch L, int lanes) {
     for (int e = lane * VEC; e < W; e += lanes * VEC)
       z.store(out + seg_out_index(mine, e, out_inner, nseg));
   }
-  // Partials to add for the segment that chunk c owns: slot 0 of the chunks c+1 .. c1, except that stage 1
-  // has left ONE partial (in the first chunk) for every run of `groups` chunks handled by one workgroup
-  // that lies strictly inside the segment: the runs B0 .. B1.  Units in order: single chunks before the
-  // runs, one per run, single chunks after.
-  struct Units {
-    int seg, c, B0, B1, nh, nm, n;  // n = 0: no segment starts in the chunk and runs past it
-    __device__ __forceinline__ int chunk_of(int u, int groups) const {
-      return u < nh ? c + 1 + u : (u < nh + nm ? (B0 + (u - nh)) * groups : (B1 + 1) * groups + (u - nh - nm));
-    }
-  };
-  auto units_of = [&](int c) __attribute__((always_inline)) {
-    Units k;
+  // Whether a segment starts in chunk c and runs past it, at positions a .. b (most chunks have none, and counting its partials divides).
+  auto owns = [&](int c, SegUnits &k, int &a, int &b) __attribute__((always_inline)) {
     const int lo = c * chunk, hi = lo + chunk, end = hi < M ? hi : M;
     k.c = c;
     k.seg = seg_src[end - 1] / seg_div;
-    const int a = seg_off[k.seg], b = seg_off[k.seg + 1], c1 = (b - 1) / chunk;
+    a = seg_off[k.seg]; b = seg_off[k.seg + 1];
+    return a >= lo && b > hi;
+  };
+  auto count = [&](SegUnits &k, int a, int b) __attribute__((always_inline)) {
+    const int c1 = (b - 1) / chunk;
     k.B0 = a / gc + 1; k.B1 = (b + gc - 1) / gc - 2;
-    k.nh = c1 - c; k.nm = 0;
+    k.nh = c1 - k.c; k.nm = 0;
     int nt = 0;
     if (k.B0 <= k.B1) {
-      k.nh = k.B0 * groups - (c + 1);
+      k.nh = k.B0 * groups - (k.c + 1);
       k.nm = k.B1 - k.B0 + 1;
       nt = c1 - (k.B1 + 1) * groups + 1;
     }
-    k.n = a >= lo && b > hi ? k.nh + k.nm + nt : 0;
-    return k;
+    k.n = k.nh + k.nm + nt;
   };
   auto finish = [&](const Vec<VEC> &acc, int s, int e) __attribute__((always_inline)) {
     float *dst = out + seg_out_index(s, e, out_inner, nseg);
     if (sv.fused) acc.store_sgd(dst, sv.lr); else acc.store(dst);
   };
   // One segment by all lane groups: they take the units round-robin, their sums are added in group order.
-  auto fold = [&](const Units &k) __attribute__((always_inline)) {
+  auto fold = [&](const SegUnits &k) __attribute__((always_inline)) {
     for (int e = lane * VEC; e < W; e += lanes * VEC) {
       Vec<VEC> acc;
       acc.zero();
@@ -380,19 +383,25 @@ k_seg_stage2(TTArg<BATCHED> arg, SegLaunch L, int lanes) {
   };
   if (!spread) {  // uniform
     if (mine >= nchunks) return;
-    const Units k = units_of(mine);
-    if (k.n > 0) fold(k);
+    SegUnits k;
+    int a, b;
+    if (!owns(mine, k, a, b)) return;
+    count(k, a, b);
+    fold(k);
     return;
   }
   if constexpr (SPREAD) {
-    int *longs = reinterpret_cast<int *>(red + (size_t)groups * W), *nlongs = longs + groups;  // chunks left to the whole workgroup
+    SegUnits *longs = reinterpret_cast<SegUnits *>(red + (size_t)groups * W);  // segments left to the whole workgroup
+    int *nlongs = reinterpret_cast<int *>(longs + groups);
     if (threadIdx.x == 0) *nlongs = 0;
     __syncthreads();
-    if (mine < nchunks) {
-      const Units k = units_of(mine);
+    SegUnits k;
+    int a, b;
+    if (mine < nchunks && owns(mine, k, a, b)) {
+      count(k, a, b);
       if (k.n > TT_SEG2_UNROLL || k.n > groups) {
-        if (lane == 0) longs[atomicAdd(nlongs, 1)] = mine;  // (segments are independent: their order does not matter)
-      } else if (k.n > 0) {
+        if (lane == 0) longs[atomicAdd(nlongs, 1)] = k;  // (segments are independent: their order does not matter)
+      } else {
         for (int e = lane * VEC; e < W; e += lanes * VEC) {
           Vec<VEC> acc, x[TT_SEG2_UNROLL];
           acc.load(partial + ((size_t)mine * 2 + 1) * W + e);
@@ -409,7 +418,7 @@ k_seg_stage2(TTArg<BATCHED> arg, SegLaunch L, int lanes) {
     __syncthreads();
     const int n = *nlongs;
     for (int i = 0; i < n; ++i) {  // uniform
-      fold(units_of(longs[i]));
+      fold(longs[i]);
       __syncthreads();
     }
   }
