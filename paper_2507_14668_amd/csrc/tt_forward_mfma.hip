@@ -22,12 +22,13 @@
 // eight 16x16x4 fp32 ones of 14.4.  The strip is split once per workgroup and the core-0 tile when it is staged, so the loop has
 // no conversions.  The products hi * hi have an accumulator of their own: they are exact, an instruction adds its 32 of them
 // nearly so, and the seven smaller terms come to them in one addition at the end, so that a sum is rounded at its full size
-// about once per instruction instead of once per term (measurements at tt_split_bf16).  One table of 40 M rows with 65 k one-
-// hot lookups at ranks 64: 58.1 -> 50.2 us a launch, of 300 k rows 31.9 -> 29.9; multi-hot at ranks 32 30.3 -> 28.5, the
-// prefix products alone 18.5 -> 17.2.  Six terms into one accumulator: 44.8 us, but sums of few non-zero
-// terms were less exact than the fp32 instruction's.  Row tiles side by side, or operands a step ahead, spill at ranks 64 (52 to 53 us).
+// about once per instruction instead of once per term (measurements at tt_split_bf16).  Launches, fp32 instruction / this: 65 k one-
+// hot lookups at ranks 64 in a table of 40 M rows 56.4 / 48.9 us, of 300 k 31.5 / 28.5; nine tables fused at batch 4096 (one or two
+// chunks a workgroup) 48.2 / 45.2; multi-hot at ranks 32 30.5 / 29.2, the prefix products alone 18.9 / 17.6.  Six terms into one
+// accumulator took 44.3, 26.2, 42.2, 27.4 and 16.4, but sums of few non-zero terms were less exact than the fp32 instruction's.  A
+// row tile after the other: both at once, or operands a step ahead, spill at ranks 64, which costs 1 to 4 us.
 // Operands or products that the split does not serve send the rest of a workgroup's chunks to the fp32 instruction (all cores
-// NaN: 63 us at ranks 64 where the fp32 kernel takes 54, 30.5 where it takes 28.7 at ranks 32; one NaN in a product 68 and 32).
+// NaN: 64 us at ranks 64 where the fp32 kernel takes 54, 32 where it takes 28.8 at ranks 32).
 // The operand tile has to lie on 16 bytes: with the dynamic LDS at any float's address the 16-byte reads cost a third more.
 //
 // Operand layout of __builtin_amdgcn_mfma_f32_16x16x4f32 (D = A[16x4] * B[4x16] + C):
@@ -122,16 +123,15 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
   if (i2 >= sh.n2) return;  // padding of the last group of 8, or a table of the batch with fewer i2 values
   const int strip = sub / split, part = sub - strip * split;
   const int j2base = strip * G::JW;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int lm = lane & 15, lq = lane >> 4;
 
   // This wavefront's 32 columns of the strip of G2[:, i2], all r1 (B operand of F1), as one float2
   // per row and lane: lane lm holds columns 2*lm, 2*lm + 1, and MFMA tile nt takes component nt, i.e.
   // tile column lm stands for strip column 32*wave + 2*lm + nt.  Requested before the plan is looked at.
   float2 bq[BF16 ? 1 : G::KS1];  // (split: row 32*kb + 8*lq + i in bq[8*kb + i])
   uint4 bqb[BF16 ? R1 / 16 : 1];  // BF16: per 16 values of r1, columns 2*lm and 2*lm + 1 with four r1 each
-  auto load_strip = [&](auto how) __attribute__((always_inline)) {
+  auto load_strip = [&](auto how, const int tid) __attribute__((always_inline)) {
     constexpr int HOW = decltype(how)::value;
+    const int lane = tid & 63, wave = tid >> 6, lm = lane & 15, lq = lane >> 4;
     if constexpr (HOW == FWD_BF16) {
 #pragma unroll
       for (int ks = 0; ks < R1 / 16; ++ks)
@@ -145,7 +145,7 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
       }
     }
   };
-  load_strip(std::integral_constant<int, MODE>{});
+  load_strip(std::integral_constant<int, MODE>{}, (int)threadIdx.x);
 
   int seg0 = i2_seg[i2], seg1 = i2_seg[i2 + 1];
   if (split > 1) {  // the chunks of this (i2, strip) are dealt in contiguous runs to `split` workgroups
@@ -159,32 +159,33 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
 
   // The prefixes from `first` on, multiplied as `how` says.  Returns the chunk that it has to leave to the fp32 instructions, or seg1.
   // (It starts behind seg0, or again at seg0, in the fp32 phase of a split kernel only: the plan entries are then staged.)
-  auto run = [&](auto how, const int first) __attribute__((always_inline)) -> int {
+  auto run = [&](auto how, const int first, const int tid) __attribute__((always_inline)) -> int {
     constexpr int HOW = decltype(how)::value;
+    const int lane = tid & 63, wave = tid >> 6, lm = lane & 15, lq = lane >> 4;
     // Global-memory operands of the NEXT chunk (core-0 rows, row ids of its first rows) are fetched
     // into registers while the current chunk computes.
     float g1n[HOW == FWD_SPLIT ? 4 : G::GPT];
     int rown = 0;
     auto fetch_meta = [&](int base) __attribute__((always_inline)) {  // plan entries of prefixes base .. base+63 -> LDS
-      if (threadIdx.x < FMETA) {
+      if (tid < FMETA) {
         int i1 = -1, u0 = 0, nr = 0, slot = 0;
-        if (base + (int)threadIdx.x < seg1) {
-          const int4 m = pref_meta[base + threadIdx.x];  // i1, first row slot, rows, prefix slot
+        if (base + tid < seg1) {
+          const int4 m = pref_meta[base + tid];  // i1, first row slot, rows, prefix slot
           i1 = m.x; u0 = m.y; nr = m.z; slot = m.w;
         }
-        s_i1[threadIdx.x] = i1; s_u0[threadIdx.x] = u0; s_nr[threadIdx.x] = nr; s_slot[threadIdx.x] = slot;
+        s_i1[tid] = i1; s_u0[tid] = u0; s_nr[tid] = nr; s_slot[tid] = slot;
       }
     };
     // (split: a thread holds four consecutive r1 of a row; at R1 = 32 two threads hold the same four, since a load under
     // a branch would have to wait for the stores in front of it)
-    const int arow = (threadIdx.x & 15) + 16 * ((threadIdx.x / (4 * R1)) & 1), ar1 = 4 * ((threadIdx.x >> 4) & (R1 / 4 - 1));
+    const int arow = (tid & 15) + 16 * ((tid / (4 * R1)) & 1), ar1 = 4 * ((tid >> 4) & (R1 / 4 - 1));
     auto fetch_chunk = [&](int mo) __attribute__((always_inline)) {  // mo = offset of the chunk inside the staged plan entries
       // unconditional (slice 0 stands in for a prefix the chunk does not have; it is replaced by
       // zero when the chunk is staged, so that no load sits under a branch)
       if constexpr (HOW != FWD_SPLIT) {
 #pragma unroll
         for (int k = 0; k < G::GPT; ++k) {
-          const int e = threadIdx.x + k * FTHR, row = e / R1, r1 = e - row * R1;
+          const int e = tid + k * FTHR, row = e / R1, r1 = e - row * R1;
           const int i1 = s_i1[mo + (row >> 2)];
           const size_t at = (size_t)(i1 >= 0 ? i1 : 0) * G::S1 + (row & 3) * R1 + r1;
           g1n[k] = BF16 ? bf16_to_float(g1b[at]) : g1[at];
@@ -195,21 +196,25 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) g1n[k] = v[k];
       }
-      const int p = threadIdx.x / FWD_I3_STAGE, r = threadIdx.x - p * FWD_I3_STAGE;
-      rown = uniq_row[s_u0[mo + p] + (r < s_nr[mo + p] ? r : 0)];
+      if constexpr (!P12OUT) {
+        const int p = tid / FWD_I3_STAGE, r = tid - p * FWD_I3_STAGE;
+        rown = uniq_row[s_u0[mo + p] + (r < s_nr[mo + p] ? r : 0)];
+      }
     };
     auto stage_chunk = [&](int par, int mo) __attribute__((always_inline)) {  // registers -> LDS
       if constexpr (HOW != FWD_SPLIT) {
 #pragma unroll
         for (int k = 0; k < G::GPT; ++k) {
-          const int e = threadIdx.x + k * FTHR, row = e / R1, r1 = e - row * R1;
+          const int e = tid + k * FTHR, row = e / R1, r1 = e - row * R1;
           const float v = s_i1[mo + (row >> 2)] >= 0 ? g1n[k] : 0.f;  // zero rows for prefixes the chunk does not have
           if constexpr (BF16) Asb[row * RSB + r1] = (unsigned short)(__float_as_uint(v) >> 16);  // exact: v is a bf16 value
           else As[row * G::RS + r1] = v;
         }
-      } else if (8 * R1 == FTHR || threadIdx.x < 8 * R1) {
+      } else if (8 * R1 == FTHR || tid < 8 * R1) {
         const bool have = s_i1[mo + (arow >> 2)] >= 0;
-        if (have && tt_split_smallest(tt_split_smallest(~0u, g1n[0], g1n[1]), g1n[2], g1n[3]) < TT_SPLIT_MIN) s_unfit[par] = 1;
+        if (tt_min3_abs(tt_min3_abs(1.f, g1n[0], g1n[1]), g1n[2], g1n[3]) < TT_SPLIT_MIN && have &&
+            (tt_split_small(g1n[0]) || tt_split_small(g1n[1]) || tt_split_small(g1n[2]) || tt_split_small(g1n[3])))
+          s_unfit[par] = 1;
         uint2 hi, mid, lo;
         tt_split_bf16(have ? g1n[0] : 0.f, have ? g1n[1] : 0.f, hi.x, mid.x, lo.x);
         tt_split_bf16(have ? g1n[2] : 0.f, have ? g1n[3] : 0.f, hi.y, mid.y, lo.y);
@@ -219,7 +224,8 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
         dst[G::PLANE / 4] = mid;
         dst[G::PLANE / 2] = lo;
       }
-      s_i3[par][threadIdx.x / FWD_I3_STAGE][threadIdx.x % FWD_I3_STAGE] = rown % sh.n3;
+      if constexpr (P12OUT) return;  // (the rows are for F2)
+      s_i3[par][tid / FWD_I3_STAGE][tid % FWD_I3_STAGE] = rown % sh.n3;
       if (wave == 0) {  // quads per prefix of the chunk, running total (scan over the first 8 lanes)
         const int q4 = lane < TT_MP ? (s_nr[mo + lane] + 3) >> 2 : 0;
         int incl = q4;
@@ -235,7 +241,7 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
 
     const int mo0 = (first - seg0) % FMETA;
     if constexpr (HOW == MODE) {
-      if (SPLIT && threadIdx.x < 3) s_unfit[threadIdx.x] = 0;
+      if (SPLIT && tid < 3) s_unfit[tid] = 0;
       fetch_meta(first);
       __syncthreads();
     }
@@ -243,8 +249,15 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
     // the strip as F1's B operand: per part, k step and tile column eight bf16 values
     uint4 bs[HOW == FWD_SPLIT ? 3 : 1][HOW == FWD_SPLIT ? G::KB : 1][2];
     if constexpr (HOW == FWD_SPLIT) {
-      unsigned smallest = ~0u;
-      float z = 0.f;
+      float smallest = 1.f;
+#pragma unroll
+      for (int ks = 0; ks < G::KS1; ++ks) smallest = tt_min3_abs(smallest, bq[ks].x, bq[ks].y);
+      if (smallest < TT_SPLIT_MIN) {  // a number below the limit, or a zero
+        bool small = false;
+#pragma unroll
+        for (int ks = 0; ks < G::KS1; ++ks) small = small || tt_split_small(bq[ks].x) || tt_split_small(bq[ks].y);
+        if (small) s_unfit[2] = 1;
+      }
 #pragma unroll
       for (int kb = 0; kb < G::KB; ++kb)
 #pragma unroll
@@ -253,14 +266,11 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
 #pragma unroll
           for (int i = 0; i < 8; i += 2) {
             const float x = nt ? bq[8 * kb + i].y : bq[8 * kb + i].x, y = nt ? bq[8 * kb + i + 1].y : bq[8 * kb + i + 1].x;
-            smallest = tt_split_smallest(smallest, x, y);
-            z = fmaf(x, 0.f, fmaf(y, 0.f, z));
             tt_split_bf16(x, y, w[0][i / 2], w[1][i / 2], w[2][i / 2]);
           }
 #pragma unroll
           for (int k = 0; k < 3; ++k) bs[k][kb][nt] = make_uint4(w[k][0], w[k][1], w[k][2], w[k][3]);
         }
-      if (smallest < TT_SPLIT_MIN || z != 0.f) s_unfit[2] = 1;  // (zero times a number is zero, times an infinity or NaN is NaN)
     }
     stage_chunk(0, mo0);
     int par = 0;
@@ -341,7 +351,7 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
                 z = fmaf(acc[mt][nt][v], 0.f, z);
               }
           }
-          if (z != 0.f) s_unfit[par] = 1;
+          if (z != 0.f) s_unfit[par] = 1;  // (zero times a number is zero, times an infinity or NaN is NaN)
         }
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
@@ -365,7 +375,7 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
 
       if constexpr (P12OUT) {  // the chunk's products -> reuse buffer, as float4 along r2
         constexpr int Q4 = G::CC * R2 / 4;  // float4 per prefix and strip
-        for (int e = threadIdx.x; e < TT_MP * Q4; e += FTHR) {
+        for (int e = tid; e < TT_MP * Q4; e += FTHR) {
           const int p = e / Q4, rem = e - p * Q4, cc = rem / (R2 / 4), r4 = rem - cc * (R2 / 4);
           if (s_i1[mo + p] < 0) continue;
           const int j1 = cc / G::JW, j2 = j2base + (cc - j1 * G::JW);
@@ -436,13 +446,15 @@ k_fwd_mfma(TTArg<BATCHED> a, int split) {
     }
     return seg1;
   };
-  const int rest = run(std::integral_constant<int, MODE>{}, seg0);
+  const int rest = run(std::integral_constant<int, MODE>{}, seg0, (int)threadIdx.x);
   if constexpr (SPLIT) {
     // Infinities and NaN in the cores, products beyond fp32, operands too small to split: from here on in fp32, with the same
-    // bits as a short batch.
+    // bits as a short batch.  The thread index is made anew so that no address of this phase is kept in a register throughout the
+    // first one: two or three spills, and with them scratch memory, cost 3 us a launch.
     if (rest < seg1) {  // uniform
-      load_strip(std::integral_constant<int, FWD_FP32>{});
-      run(std::integral_constant<int, FWD_FP32>{}, rest);
+      const int tid = tt_anew((int)threadIdx.x);
+      load_strip(std::integral_constant<int, FWD_FP32>{}, tid);
+      run(std::integral_constant<int, FWD_FP32>{}, rest, tid);
     }
   }
 }

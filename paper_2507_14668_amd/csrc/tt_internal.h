@@ -148,15 +148,26 @@ __device__ __forceinline__ void tt_split_bf16(float x, float y, unsigned &hi, un
   mid = tt_bf16_pair(rx, ry);
   lo = tt_bf16_pair(rx - __uint_as_float(mid << 16), ry - __uint_as_float(mid & 0xffff0000u));
 }
-// Sizes are compared as the bits of |x| one up, minus one: zero, which splits like any other number, counts as the largest.
 #ifndef TT_SPLIT_MIN
-#define TT_SPLIT_MIN (2u * (127 - 40) << 23)
+#define TT_SPLIT_MIN 0x1p-40f
 #endif
-__device__ __forceinline__ unsigned tt_split_smallest(unsigned m, float x, float y) {
-  const unsigned a = (__float_as_uint(x) << 1) - 1, b = (__float_as_uint(y) << 1) - 1;
-  m = a < m ? a : m;
-  return b < m ? b : m;
+// the smallest of m, |x| and |y| (NaN counts as large), in one instruction: fminf costs two more to quiet its operands
+__device__ __forceinline__ float tt_min3_abs(float m, float x, float y) {
+#ifdef __HIP_DEVICE_COMPILE__
+  asm("v_min3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(x), "v"(y));
+  return m;
+#else
+  return fminf(m, fminf(fabsf(x), fabsf(y)));
+#endif
 }
+// x, as a value that the compiler does not know to be x
+__device__ __forceinline__ int tt_anew(int x) {
+#ifdef __HIP_DEVICE_COMPILE__
+  asm volatile("" : "+v"(x));
+#endif
+  return x;
+}
+__device__ __forceinline__ bool tt_split_small(float x) { return x != 0.f && fabsf(x) < TT_SPLIT_MIN; }
 typedef short tt_bf16x8 __attribute__((ext_vector_type(8)));
 typedef float tt_f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // four floats at any float's address
 // D = A[16x32] * B[32x16] + C in bf16 with fp32 accumulators: lane l supplies A[m = l%16][k = 8*(l/16) + i] and
@@ -244,8 +255,8 @@ tt_status ttk_forward_plan(const TTBatch &b, hipStream_t s);
 #define TT_DIRECT_MAX_LOOKUPS_64 8192  // (ranks 64)
 #endif
 // Whether the matrix-core forward multiplies prefixes by split fp32 numbers (tt_split_bf16): above this many lookups.  Contraction
-// launch, fp32 / split, one-hot lookups in tables of 300 k and 40 M rows: ranks 64 17000 lookups 19.1 / 17.8 us, 65536 31.9 /
-// 29.9 and 58.1 / 50.2; ranks 32 17000 10.5 / 10.1, 65536 15.5 / 14.8.  Short batches gain next to nothing (a strip is split
+// launch, fp32 / split, one-hot lookups in tables of 300 k and 40 M rows: ranks 64 17000 lookups 19.2 / 17.9 us, 65536 31.5 /
+// 28.5 and 56.4 / 48.9; ranks 32 17000 10.4 / 10.5, 65536 15.6 / 14.8.  Short batches gain next to nothing (a strip is split
 // for one chunk of prefixes).  The last bits of a row follow the number of lookups of its call through this limit.
 // The forward without a plan has the fp32 kernel's bits, and a batch gets the same bits by both: it stays below the limit.
 #ifndef TT_FORWARD_SPLIT_ABOVE_32

@@ -1,5 +1,7 @@
 """The matrix-core forward on split fp32 numbers (kernels compiled for the CPU, the route taken at every size in a variant of
 its own) against 64 bits, and with infinities, NaN and the largest numbers against the arm without a plan."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -81,8 +83,17 @@ def _products(r, n, seed, terms):
 
 
 def _product_sums(emu, problem):
-    shape, cores, idx, off = problem
-    return te._run(emu, shape, [c.reshape(-1) for c in cores], idx, off, np.zeros(len(idx) * 128, np.float32), 0.0)["plan"][0]
+    (lib, binding), (shape, raw, idx, off) = emu, problem
+    cores = [te._aligned(4 * c.size).view(np.float32) for c in raw]
+    for c, x in zip(cores, raw):
+        c[:] = x.reshape(-1)
+    table, nnz, plan = te._table(binding, shape, cores), len(idx), binding.CPlan()
+    ws = te._aligned(lib.tt_workspace_bytes(ctypes.byref(table), nnz, nnz))
+    assert lib.tt_index_reorder(ctypes.byref(table), te._ptr(idx), te._ptr(off), nnz, nnz, None, te._ptr(ws), ws.nbytes,
+                                ctypes.byref(plan), None) == 0
+    out = np.full((nnz, shape.dim), np.nan, np.float32)
+    assert lib.tt_emb_bag_forward(ctypes.byref(table), ctypes.byref(plan), te._ptr(idx), te._ptr(off), nnz, nnz, te._ptr(out), None) == 0
+    return out
 
 
 def _exact_products(problem):
