@@ -164,6 +164,12 @@ tt_status tt_index_reorder(const tt_table *table, const int64_t *indices, const 
  *   out  DEVICE float[num_bags][D], overwritten.
  * The remap given to tt_index_reorder is baked into the plan; the naive arm
  * reads `indices` as they are.
+ * Accuracy and bits: sums are fp32 and reproducible, the same batch gives the same bits.  The last
+ * bits of a row may differ between batches: for d = (4, 8, 4) and ranks (32, 32) / (64, 64) the planned
+ * arm forms prefix products on the fp32 matrix instruction up to 16384 / 8192 lookups in the call, and above
+ * on bf16 ones, of operands split into three parts (no less exact, infinities and NaN as in fp32).
+ * So one row in two batches on either side of that limit, or in a table alone and in a fused one, agrees
+ * to fp32 rounding.  tt_emb_bag_forward_sample follows the same limit.
  */
 tt_status tt_emb_bag_forward(const tt_table *table, const tt_plan *plan, const int64_t *indices,
                              const int64_t *offsets, int64_t nnz, int64_t num_bags, float *out,
@@ -258,7 +264,8 @@ tt_status tt_emb_bag_forward_bf16(const tt_table *table, const void *bf16_cores,
  * same tolerance as tt_emb_bag_forward_bf16; invalid indices are skipped and malformed offsets clamped, and
  * there is no plan that would report them.  tt_forward_bf16_direct_pays says (1 / 0, from the
  * sizes alone) whether this is the faster way for a batch whose plan serves nothing else; 0 on invalid
- * arguments.
+ * arguments.  The two ways add in different orders: a program that asks tt_forward_bf16_direct_pays, as
+ * the Python module's forward_bf16 does, gets a bag's last bits by the sizes of its batch.
  */
 int tt_forward_bf16_direct_pays(const tt_table *table, int64_t nnz, int64_t num_bags);
 tt_status tt_emb_bag_forward_bf16_direct(const tt_table *table, const void *bf16_cores, const int64_t *indices,

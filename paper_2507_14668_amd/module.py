@@ -142,7 +142,8 @@ class TTEmbeddingBag(torch.nn.Module):
 
     @torch.no_grad()
     def forward_bf16(self, input, offsets=None):
-        """Inference forward on the bf16 copies of the cores (fp32 accumulation); no autograd graph."""
+        """Inference forward on the bf16 copies of the cores (fp32 accumulation); no autograd graph.
+        Short batches are summed without a plan, in another order: a bag's last bits follow the sizes of its batch."""
         if self._bf16_cores is None:
             self.bf16_inference()
         if input.dtype != torch.int64:
