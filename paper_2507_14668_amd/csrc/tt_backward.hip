@@ -529,11 +529,26 @@ __host__ __device__ __forceinline__ WholeSplit whole_split(int W, int vec, int w
 }
 __host__ __device__ __forceinline__ int whole_want3(int n3) { return (512 + n3 - 1) / n3; }
 
-// ROUNDS: up to two strips a prefix.
+// Whether a table's positions go in rounds (below): up to two strips a prefix, and segments that fill a round.  What a round sets up
+// costs a short segment more than it saves.  Launches, one position after the other / rounds, distinct rows by i3 (at most) in
+// brackets: ranks 32 4.4 / 5.1 us (22), 4.5 / 5.2 (43), 6.6 / 5.9 (47), 6.1 / 5.1 (87), 342 i3 7.2 / 8.0 (23), 8.5 / 8.2 (47);
+// one strip, ranks 12 and 20 4.6 / 4.9 (8), 5.0 / 5.3 (16), 5.6 / 4.8 (33), ranks 16 and 4 3.9 / 4.4 (8), 4.7 / 4.7 (30), 6.1 / 5.2 (61).
+// Skewed lookups have fewer rows than the capacity that the rule knows: up to 0.8 us lost above the limits, 1 to 9 won from twice them on.
+#ifndef TT_SEG_ROUNDS_MIN_1
+#define TT_SEG_ROUNDS_MIN_1 32  // positions per segment by capacity: one strip a prefix
+#endif
+#ifndef TT_SEG_ROUNDS_MIN_2
+#define TT_SEG_ROUNDS_MIN_2 45  // ... two
+#endif
+__host__ __device__ __forceinline__ bool seg_whole_rounds(const TTDev &d) {
+  const long long least = d.strips == 1 ? TT_SEG_ROUNDS_MIN_1 : TT_SEG_ROUNDS_MIN_2;
+  return d.strips <= 2 && (d.plan.max_rows >= least * d.sh.n3 || d.plan.max_prefixes >= least * d.sh.n1);
+}
 template <bool BATCHED, int VEC, bool ROUNDS>
 __global__ void __launch_bounds__(TT_BLOCK)
 k_seg_whole(TTArg<BATCHED> arg, int blocks_a) {
   const TTDev &d = arg.get();
+  if (BATCHED && seg_whole_rounds(d) != ROUNDS) return;  // uniform: the other launch serves this table
   const bool second = (int)blockIdx.x >= blocks_a;
   const SegView sv = seg_view(d, second ? SEG_DG1 : SEG_DG3);
   const WholeSplit split = whole_split(sv.W, VEC, second ? TT_SEG_WHOLE_PARTS : whole_want3(d.sh.n3));
@@ -595,8 +610,8 @@ k_seg_whole(TTArg<BATCHED> arg, int blocks_a) {
       acc.add(x[0][0]);
     }
   };
-  // The same for four strips a position (ranks 64): sixteen vectors in flight halve the wavefronts a compute unit holds, which
-  // costs the many short segments of fused tables more than it gives (nine tables at batch 4096 19.5 us a launch, 25 in rounds
+  // One position after the other.  Four strips a position (ranks 64): sixteen vectors in flight halve the wavefronts a compute unit
+  // holds, which costs the many short segments of fused tables more than it gives (nine tables at batch 4096 19.5 us a launch, 25 in rounds
   // of sixteen, 22 in rounds of eight; one table 18.2, 17.6 and 18.8).
   auto load_pos = [&](int pos, int e, Vec<VEC> &x) {
     const int row = gidx ? gidx[pos] : pos;
@@ -696,11 +711,16 @@ tt_status seg_sum_dg3_dg1(const TTBatch &b, hipStream_t s) {
     const size_t lds = sizeof(float) * (size_t)(lds3 > lds1 ? lds3 : lds1);
     const long long grid = blocks3 + blocks1;
     if (grid <= (mixed ? TT_SEG_MIXED_MAX_WGS : TT_MAX_WORKGROUPS)) {  // (millions of slices: the two-stage sum's workgroups follow the lookups)
-      const bool rounds = tt_batch_max(b, [](const TTDev &d) { return (long long)d.strips; }) <= 2;
-      if (vec == 4 && rounds) TT_LAUNCH_T2(k_seg_whole, 4, true, grid, TT_BLOCK, lds, s, b, (int)blocks3);
-      else if (vec == 4) TT_LAUNCH_T2(k_seg_whole, 4, false, grid, TT_BLOCK, lds, s, b, (int)blocks3);
-      else if (rounds) TT_LAUNCH_T2(k_seg_whole, 1, true, grid, TT_BLOCK, lds, s, b, (int)blocks3);
-      else TT_LAUNCH_T2(k_seg_whole, 1, false, grid, TT_BLOCK, lds, s, b, (int)blocks3);
+      bool rounds = false, single = false;  // (a batch: a launch each that its tables take)
+      for (int t = 0; t < b.T; ++t) (seg_whole_rounds(b.host[t]) ? rounds : single) = true;
+      if (rounds) {
+        if (vec == 4) TT_LAUNCH_T2(k_seg_whole, 4, true, grid, TT_BLOCK, lds, s, b, (int)blocks3);
+        else TT_LAUNCH_T2(k_seg_whole, 1, true, grid, TT_BLOCK, lds, s, b, (int)blocks3);
+      }
+      if (single) {
+        if (vec == 4) TT_LAUNCH_T2(k_seg_whole, 4, false, grid, TT_BLOCK, lds, s, b, (int)blocks3);
+        else TT_LAUNCH_T2(k_seg_whole, 1, false, grid, TT_BLOCK, lds, s, b, (int)blocks3);
+      }
       return tt_launch_status();
     }
   }

@@ -61,3 +61,22 @@ def test_core_sums_into_unaligned_gradients(r):
         got.append([x.copy() for x in dg])
     for x, y in zip(*got):
         assert np.allclose(x, y, rtol=0, atol=1e-6 * np.abs(x).max())
+
+
+@pytest.fixture(scope="module")
+def emu():
+    return te._load(te.emu_build.build_shared(te.BUILD_DIR))
+
+
+@pytest.mark.parametrize("n,d,r,nnz,rounds", [
+    ((8, 8, 2), (2, 4, 6), (1, 12, 20, 1), 63, False), ((8, 8, 2), (2, 4, 6), (1, 12, 20, 1), 64, True),  # one strip: rows per i3
+    ((1, 40, 4), (2, 3, 2), (1, 4, 8, 1), 31, False), ((1, 40, 4), (2, 3, 2), (1, 4, 8, 1), 32, True),    # prefixes per i1
+    ((9, 9, 3), (4, 8, 4), (1, 32, 32, 1), 134, False), ((9, 9, 3), (4, 8, 4), (1, 32, 32, 1), 135, True),  # two strips
+    ((9, 9, 3), (4, 8, 4), (1, 64, 64, 1), 135, False),                                                     # four
+])
+def test_whole_segments_by_rounds_from_a_length_on(emu, capfd, monkeypatch, n, d, r, nnz, rounds):
+    """Which batches' whole segments go in rounds, and the gradients of both ways against 64 bits."""
+    launches, dg, ref = te._backward_with_trace(emu, capfd, monkeypatch, n, d, r, nnz)
+    assert [("true" in ln.split("k_seg_whole", 1)[1]) for ln in launches if "k_seg_whole" in ln] == [rounds], launches
+    for a, b in zip(dg, ref):  # sums of up to 135 terms in 32 bits
+        assert np.linalg.norm(a - b) <= 2e-6 * np.linalg.norm(b)
